@@ -8,8 +8,8 @@ Families and what they stand for:
   stage2      one training step over the four bottlenecks of stage 2 (strided 3x3, strided projection, identity blocks).
   stem        one training step over the 7x7 / stride 2 stem (no gradient to the image).
   block       one block through the two calls of the C interface as they stand: forward, L1 gradient, and a backward call
-              that masks its own gradient, adds a shortcut gradient and returns the residual's gradient; bf16 with channel
-              counts of every kind and the fp32 configuration.
+              that masks its own gradient and adds a shortcut gradient; bf16 with channel counts of every kind and the
+              fp32 configuration.
 
 A pass of the first four is the prepared sequence that ``runner.Sequencer`` records; a pass of the last is three calls of
 ``binding``.  All inputs are drawn on the GPU from the seed, from the distributions the workloads use.
@@ -28,11 +28,11 @@ from paper_2205_10357_amd import workloads as wl
 def listed():
     return [
         # the fp32 correctness configuration: one 3x3 block, batch 1 (smallest call: launches and latency)
-        dict(name="block_f32_16", family="block", dtype="f32", n=1, h=16, w=16, c_in=16, c_out=16, k=3, stride=1, residual=False),
-        # one block called through the interface, channels a multiple of 64: masks its own gradient, returns dres
-        dict(name="block_3x3_128", family="block", dtype="bf16", n=32, h=28, w=28, c_in=128, c_out=128, k=3, stride=1, residual=True),
+        dict(name="block_f32_16", family="block", dtype="f32", n=1, h=16, w=16, c_in=16, c_out=16, k=3, stride=1),
+        # one block called through the interface, channels a multiple of 64: masks its own gradient
+        dict(name="block_3x3_128", family="block", dtype="bf16", n=32, h=28, w=28, c_in=128, c_out=128, k=3, stride=1),
         # channel counts that are multiples of 8 only, odd image, stride 2
-        dict(name="block_3x3_ragged", family="block", dtype="bf16", n=19, h=45, w=37, c_in=72, c_out=104, k=3, stride=2, residual=False),
+        dict(name="block_3x3_ragged", family="block", dtype="bf16", n=19, h=45, w=37, c_in=72, c_out=104, k=3, stride=2),
         # serving one image: latency of 55 small launches
         dict(name="infer_n1", family="infer", n=1, hw=224),
         # a small batch of images whose size is no multiple of 32
@@ -62,11 +62,11 @@ def draw(rng):
     family = rng.choice(["block", "block", "block_f32", "infer", "infer", "bottleneck", "bottleneck", "stage2", "stem"])
     if family == "block_f32":
         return dict(family="block", dtype="f32", n=rng.randint(1, 4), h=rng.randint(8, 24), w=rng.randint(8, 24), c_in=rng.randint(4, 32),
-                    c_out=rng.randint(4, 32), k=rng.choice([1, 3]), stride=rng.choice([1, 2]), residual=rng.random() < 0.5)
+                    c_out=rng.randint(4, 32), k=rng.choice([1, 3]), stride=rng.choice([1, 2]))
     if family == "block":
         ch = lambda: 64 * rng.randint(1, 4) if rng.random() < 0.5 else 8 * rng.randint(2, 32)
         return dict(family="block", dtype="bf16", n=_log_int(rng, 1, 64), h=rng.randint(7, 56), w=rng.randint(7, 56), c_in=ch(), c_out=ch(),
-                    k=rng.choice([1, 3]), stride=rng.choice([1, 1, 2]), residual=rng.random() < 0.5)
+                    k=rng.choice([1, 3]), stride=rng.choice([1, 1, 2]))
     if family == "infer":
         return dict(family="infer", n=_log_int(rng, 1, 100), hw=rng.randint(128, 240))
     if family == "bottleneck":
@@ -148,8 +148,7 @@ def _prepare_block(case, d):
     dt = torch.float32 if case["dtype"] == "f32" else torch.bfloat16
     xs, ys = (desc.N, desc.H, desc.W, desc.C_in), (desc.N, desc.Ho, desc.Wo, desc.C_out)
     s = dict(desc=desc, x=d.uniform(xs, dt), t=d.uniform(ys, dt), addend=d.normal(xs, dt, 1.0 / math.prod(ys)), **d.params(desc.C_out, desc.KH, desc.C_in, dt))
-    s["res"] = d.normal(ys, dt) if case["residual"] else None
-    for key, shape, t in (("y", ys, dt), ("dy", ys, dt), ("dres", ys, dt), ("dx", xs, dt), ("dW", s["W"].shape, torch.float32),
+    for key, shape, t in (("y", ys, dt), ("dy", ys, dt), ("dx", xs, dt), ("dW", s["W"].shape, torch.float32),
                           ("dscale", (desc.C_out,), torch.float32), ("dshift", (desc.C_out,), torch.float32)):
         s[key] = torch.zeros(shape, dtype=t, device=d.device)
     for key, which in (("ws_fwd", B.SOL_PASS_FWD), ("ws_bwd", B.SOL_PASS_BWD)):
@@ -161,11 +160,11 @@ def _prepare_block(case, d):
 def run(state):
     if isinstance(state, dict):
         s = state
-        B.sol_block_fwd(s["desc"], s["x"], s["W"], s["scale"], s["shift"], s["res"], s["y"], s["ws_fwd"])
+        B.sol_block_fwd(s["desc"], s["x"], s["W"], s["scale"], s["shift"], None, s["y"], s["ws_fwd"])
         B.sol_l1_loss_grad(s["desc"].dtype, s["y"], s["t"], s["dy"], s["y"].numel())
-        B.sol_block_bwd(s["desc"], s["dy"], s["x"], s["W"], s["y"], s["dx"], s["dW"], s["dscale"], s["dshift"], s["scale"], s["dres"],
+        B.sol_block_bwd(s["desc"], s["dy"], s["x"], s["W"], s["y"], s["dx"], s["dW"], s["dscale"], s["dshift"], s["scale"], None,
                         s["addend"], None, None, s["ws_bwd"])
-        return {key: s[key] for key in ("y", "dx", "dres", "dW", "dscale", "dshift")}
+        return {key: s[key] for key in ("y", "dx", "dW", "dscale", "dshift")}
     seq = state
     seq.step_prepared()
     last = seq.act[seq.ops[-1].out]
@@ -188,9 +187,9 @@ def work(case):
         es = 4 if case["dtype"] == "f32" else 2
         x, y = d.N * d.H * d.W * d.C_in, d.N * d.Ho * d.Wo * d.C_out
         wt = d.C_out * d.KH * d.KW * d.C_in
-        fwd = (x + wt + y + (y if case["residual"] else 0)) * es
+        fwd = (x + wt + y) * es
         loss = 3 * y * es
-        bwd = (2 * y + x + wt + y + 2 * x) * es + wt * 4                  # dy, y, x, W, dres, addend, dx; dW in fp32
+        bwd = (2 * y + x + wt + 2 * x) * es + wt * 4                      # dy, y, x, W, addend, dx; dW in fp32
         return dict(bytes=fwd + loss + bwd + 5 * d.C_out * 4, flops=3 * 2 * y * d.KH * d.KW * d.C_in)
     ops, c = _ops(case)
     train = case["family"] != "infer"
@@ -217,10 +216,13 @@ def work(case):
 
 
 def tolerance(case):
-    """About four times the distance of a pass from the same pass with fp64 sums and the same roundings at the stores.  One
-    block: 5e-5 in bf16 (rare one-ulp flips of a stored value), 6e-7 in fp32.  In a chain such flips travel on: a sign change
-    of y - t in the loss gradient or a ReLU that opens decides 0.4 % of the bottleneck's input gradient, 2.5 % of stage 2's;
-    53 layers of inference end 0.9 % apart."""
+    """Measured against a pass with fp64 sums and the same roundings at the stores, and against one with the sums in another
+    order.  A stored bf16 value that rounds the other way is 1e-5 of a tensor, but the path has steps: where y - t or a
+    pre-activation lies within a rounding of zero the gradient of that pixel jumps.  One such pixel of millions is 8e-4 of a
+    block's input gradient and up to 0.4 root mean squares of the bottleneck's (its shortcut carries the jump undiluted).  In
+    a chain they add up: bottleneck 0.4 %, stage 2 2.5 %; 53 layers of inference, without steps, end 0.9 % apart.  fp32
+    blocks: 6e-7."""
     if case["family"] == "block" and case["dtype"] == "f32":
         return dict(rel=2.5e-6)
-    return dict(rel={"block": 2e-4, "stem": 2e-4, "bottleneck": 1.5e-2, "stage2": 1e-1, "infer": 3.5e-2}[case["family"]])
+    return {"block": dict(rel=4e-3, max=1.0), "stem": dict(rel=2e-3, max=1.0), "bottleneck": dict(rel=1.5e-2, max=1.0),
+            "stage2": dict(rel=3e-2, max=1.0), "infer": dict(rel=3e-2, max=0.3)}[case["family"]]
