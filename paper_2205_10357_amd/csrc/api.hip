@@ -58,12 +58,12 @@ inline void clear_stale_error() { (void)hipGetLastError(); }
 enum Knob {
     K_IGEMM_TILE, K_IGEMM_FAST, K_FAST_TILE, K_FAST_SHORTK, K_FAST_MANY, K_FAST_STAGES, K_WGRAD_SPLITS, K_WGRAD_TARGET,
     K_SMALLC, K_FILL_UNTOUCHED, K_WGRAD_FAST, K_PACK_FUSED, K_WGRAD_STAGES, K_PREMASK, K_PANEL, K_PANEL_TILES,
-    K_REDUCE_RIDES, K_COUNT
+    K_REDUCE_RIDES, K_WIDE, K_COUNT
 };
 const char* const kKnobNames[K_COUNT] = {
     "SOL_IGEMM_TILE", "SOL_IGEMM_FAST", "SOL_FAST_TILE", "SOL_FAST_SHORTK", "SOL_FAST_MANY", "SOL_FAST_STAGES",
     "SOL_WGRAD_SPLITS", "SOL_WGRAD_TARGET", "SOL_SMALLC", "SOL_FILL_UNTOUCHED", "SOL_WGRAD_FAST", "SOL_PACK_FUSED",
-    "SOL_WGRAD_STAGES", "SOL_PREMASK", "SOL_PANEL", "SOL_PANEL_TILES", "SOL_REDUCE_RIDES"};
+    "SOL_WGRAD_STAGES", "SOL_PREMASK", "SOL_PANEL", "SOL_PANEL_TILES", "SOL_REDUCE_RIDES", "SOL_WIDE"};
 constexpr int kKnobUnset = INT32_MIN;
 std::atomic<int> g_knobs[K_COUNT];
 std::atomic<bool> g_knobs_loaded{false};
@@ -141,10 +141,91 @@ int reduce_rider_blocks(int gemm_wgs, bool small_tile, const ReduceParams* rider
     return idle >= 32 ? idle : 0;
 }
 
-// Fills tile-dependent fields of the launch (tile counts, class offsets) and launches either the
-// pipelined kernel (source channels % 64 == 0, output channels % 8 == 0, no mask on the gathered
-// operand) or the general one.  SOL_IGEMM_FAST=0 forces the general kernel; SOL_FAST_TILE /
-// SOL_FAST_STAGES override the pipelined kernel's tile and ring depth (tuning experiments).
+// Which kernel family and tile a pipelined launch takes.
+enum GemmFamily { GEMM_FAST, GEMM_WIDE };
+struct GemmChoice {
+    GemmFamily family;
+    int tile;
+};
+
+// Tiles of bp x bc (powers of two: every launch asks about a dozen shapes, which must not cost it a dozen divisions).
+int tiles_of(const IgemmParams& p, const long long* rows, int bp, int bc) {
+    const int lp = __builtin_ctz((unsigned)bp), lc = __builtin_ctz((unsigned)bc);
+    long long t = 0;
+    for (int c = 0; c < p.ncls; ++c) t += (rows[c] + bp - 1) >> lp;
+    t *= (p.Nc + bc - 1) >> lc;
+    return t < INT_MAX ? (int)t : INT_MAX;
+}
+
+// The choice between the four-wave tiles (`tile`: what the thresholds of run_igemm picked), the eight-wave tiles,
+// by expected time.  All of them
+// are bound by what a compute unit copies into LDS and multiplies, plus fixed costs per round of workgroups, so a launch
+// of T workgroups with nk 64-deep slices takes, in ns (fits to launches over the benchmark network's layers at 1 .. 128
+// images, inputs not in L2; 256 compute units):
+//   64 x 64, two per compute unit              3600 + nk * max(200, 153 * ceil(T / 256))
+//   128 x 64, three per compute unit           5000 + nk * max(300, 450 T / 256)
+//   128 x 128, eight waves                     ceil(T / 256) * (5100 + 390 nk)
+//   256 x 128 and 128 x 256, eight waves       ceil(T / 256) * (6500 + 900 nk)
+// Short reductions (nk < 8) in many tiles are bound by HBM, which the fits do not know: they keep the four-wave tiles
+// (1x1, 401408 pixels, 256 -> 128: 72 us with 128 x 64, 76 us with 256 x 128).
+// Four- and eight-wave tiles add a reduction in the same order.
+GemmChoice choose_gemm(const IgemmParams& p, const long long* rows, int tile, const ReduceParams* rider) {
+    long long all_rows = 0, work = 0;
+    for (int c = 0; c < p.ncls; ++c) {
+        all_rows += rows[c];
+        work += rows[c] * p.cls[c].Th * p.cls[c].Tw * (p.Cs / 64);
+    }
+    const long long nk = p.ncls == 1 ? (long long)p.cls[0].Th * p.cls[0].Tw * (p.Cs / 64)          // slices of an average row
+                       : all_rows > 0 ? (work + all_rows - 1) / all_rows : 0;
+    auto rounds = [](long long t) { return (t + 255) >> 8; };
+    // A split reduction that rides along: on the compute units that large tiles leave idle it moves about 25 bytes per ns
+    // and unit (a launch of its own, 4000 ns, where fewer than 32 are idle); among many small workgroups it fills gaps.
+    const long long rider_bytes = rider ? (long long)rider->splits * rider->C_out * rider->K * 4 : 0;
+    auto with_rider = [&](long long e, long long t, bool small) {
+        if (!rider) return e;
+        if (small) return e + (rider_bytes >> 13);
+        const int idle = (int)(-t & 255);
+        if (idle < 32) return e + 4000 + (rider_bytes >> 12);
+        const long long r = 2500 + (long long)((float)rider_bytes / (float)(idle * 25));
+        return r > e ? r : e;
+    };
+    struct Best {
+        GemmChoice choice{GEMM_FAST, 0};
+        long long alone = INT64_MAX, loaded = INT64_MAX;      // least time without / with the rider, choice by the latter
+        void offer(GemmChoice c, long long a, long long l) {
+            if (a < alone) alone = a;
+            if (l < loaded) {
+                loaded = l;
+                choice = c;
+            }
+        }
+    } plain;
+    int bp, bc;
+    auto offer_fast = [&](int t) {
+        igemm_fast_tile_shape(t, &bp, &bc);
+        const long long n = tiles_of(p, rows, bp, bc), r = rounds(n);
+        const long long e = t == 2 ? 3600 + nk * (153 * r > 200 ? 153 * r : 200)
+                          : t == 1 ? 5000 + nk * (n < 171 ? 300 : (450 * n) >> 8)
+                                   : r * (5100 + 390 * nk);
+        plain.offer(GemmChoice{GEMM_FAST, t}, e, with_rider(e, n, t == 1 || t == 2));
+    };
+    offer_fast(tile);
+    if (knob(K_WIDE, 0) >= 0 && nk >= 8 && p.Nc > 64) {
+        if (tile != 1) offer_fast(1);
+        for (int w = 0; w < WIDE_TILES; ++w) {
+            igemm_wide_tile_shape(w, &bp, &bc);
+            const long long n = tiles_of(p, rows, bp, bc);
+            const long long e = rounds(n) * (w == WIDE_128x128 ? 5100 + 390 * nk : 6500 + 900 * nk);
+            plain.offer(GemmChoice{GEMM_WIDE, w}, e, with_rider(e, n, false));
+        }
+    }
+    return plain.choice;
+}
+
+// Fills tile-dependent fields of the launch (tile counts, class offsets) and launches either a pipelined kernel (source
+// channels % 64 == 0, output channels % 8 == 0, no mask on the gathered operand) or the general one.  SOL_IGEMM_FAST=0
+// forces the general kernel; SOL_FAST_TILE / SOL_FAST_STAGES override the pipelined kernel's tile and ring depth,
+// SOL_WIDE = n > 0 forces tile n - 1 of that family, -1 switches it off (tuning experiments).
 // `rider`: a split reduction the launch may carry along (see above); *rode tells whether it did.
 int run_igemm(IgemmParams& p, const long long* rows, bool mask, const sol_plan& tuned, hipStream_t stream,
               const ReduceParams* rider = nullptr, bool* rode = nullptr) {
@@ -171,6 +252,7 @@ int run_igemm(IgemmParams& p, const long long* rows, bool mask, const sol_plan& 
     const bool fast_ok = !mask && few_taps && addressable && (p.Cs % 64) == 0 && (p.Nc % 8) == 0 &&
                          knob(K_IGEMM_FAST, 1) != 0;
     int bp, bc, tile = 0, stages = 0;
+    GemmChoice choice{GEMM_FAST, 0};
     bool many_tiles = false;
     // 1x1 / stride 1 with a short reduction and a wide output: a workgroup keeps its pixel panel in LDS and walks over
     // several channel tiles (tile code 4)
@@ -184,11 +266,10 @@ int run_igemm(IgemmParams& p, const long long* rows, bool mask, const sol_plan& 
         tile = knob(K_FAST_TILE, -1);
         if (tile < 0 || tile > 4) tile = tuned.tile;              // an installed plan; the environment wins (experiments)
         if (tile == 4 && !panel_ok) tile = -1;                    // a plan for the panel kernel on a launch it cannot run
-        if (tile < 0 || tile > 4) {
+        const bool free_choice = tile < 0 || tile > 4;
+        if (free_choice) {
             // 128 x 128 unless that leaves most compute units idle or the GEMM is narrow
-            long long t128 = 0;
-            for (int c = 0; c < p.ncls; ++c) t128 += (rows[c] + 127) / 128;
-            t128 *= (p.Nc + 127) / 128;
+            const long long t128 = tiles_of(p, rows, 128, 128);
             tile = p.Nc <= 64 ? 1 : (t128 >= 160 ? 0 : 1);
             // short reductions are dominated by per-workgroup latency (prologue, epilogue): many small
             // workgroups per compute unit hide it better than few large ones
@@ -198,11 +279,8 @@ int run_igemm(IgemmParams& p, const long long* rows, bool mask, const sol_plan& 
             // best or within a few percent of best from ~3 tiles of 128 x 128 per compute unit upwards)
             many_tiles = t128 >= knob(K_FAST_MANY, 700) * (slices <= 4 ? 2 : 1);   // short reductions: 64 x 64 holds up longer
             if (many_tiles) tile = 1;
-            long long t = 0;
             igemm_fast_tile_shape(tile, &bp, &bc);
-            for (int c = 0; c < p.ncls; ++c) t += (rows[c] + bp - 1) / bp;
-            t *= (p.Nc + bc - 1) / bc;
-            if (t < 160) tile = 2;
+            if (tiles_of(p, rows, bp, bc) < 160) tile = 2;
             // the panel kernel where its launch is one wave of workgroups that fills most of the chip
             if (panel_ok) {
                 const long long panels = (rows[0] + 127) / 128;
@@ -216,11 +294,19 @@ int run_igemm(IgemmParams& p, const long long* rows, bool mask, const sol_plan& 
             trace_point(stream, attach(false) ? SOL_TRACE_IGEMM_PANEL_REDUCE : SOL_TRACE_IGEMM_PANEL);
             return launch_igemm_panel(p, stream) == hipSuccess ? SOL_OK : SOL_ERR_LAUNCH;
         }
+        choice = free_choice ? choose_gemm(p, rows, tile, knob(K_REDUCE_RIDES, 1) != 0 ? rider : nullptr) : GemmChoice{GEMM_FAST, tile};
+        if (choice.family == GEMM_FAST && choice.tile != tile) {
+            tile = choice.tile;
+            many_tiles = true;
+        }
         stages = knob(K_FAST_STAGES, 0);
         if (stages < 2 || stages > 4) stages = tuned.stages;
         if (stages < 2 || stages > 4) stages = (slices <= 4 || many_tiles) ? 2 : (slices <= 8 ? 3 : 4);
         if (tile == 3 && stages > 3) stages = 3;
-        igemm_fast_tile_shape(tile, &bp, &bc);
+        if (choice.family == GEMM_FAST && tile == 0 && stages == 4) choice = GemmChoice{GEMM_WIDE, WIDE_128x128};
+        if (const int w = knob(K_WIDE, 0); w > 0 && w <= WIDE_TILES) choice = GemmChoice{GEMM_WIDE, w - 1};
+        if (choice.family == GEMM_WIDE) igemm_wide_tile_shape(choice.tile, &bp, &bc);
+        else igemm_fast_tile_shape(tile, &bp, &bc);
     } else {
         tile = pick_igemm_tile(rows, p.ncls, p.Nc);
         igemm_tile_shape(tile, &bp, &bc);
@@ -241,10 +327,11 @@ int run_igemm(IgemmParams& p, const long long* rows, bool mask, const sol_plan& 
     }
     p.total_tiles = tiles_p * p.tiles_c;
     hipError_t e;
-    const bool rides = fast_ok && attach(tile == 1 || tile == 2);
+    const bool rides = fast_ok && attach(choice.family == GEMM_FAST && (tile == 1 || tile == 2));
     trace_point(stream, rides ? SOL_TRACE_IGEMM_REDUCE : fast_ok ? SOL_TRACE_IGEMM : SOL_TRACE_IGEMM_GENERAL);
-    if (fast_ok) e = launch_igemm_fast(p, tile, stages, stream);
-    else e = launch_igemm(p, tile, (p.Cs % 8) == 0, mask, stream);
+    if (!fast_ok) e = launch_igemm(p, tile, (p.Cs % 8) == 0, mask, stream);
+    else if (choice.family == GEMM_WIDE) e = launch_igemm_wide(p, choice.tile, stream);
+    else e = launch_igemm_fast(p, tile, stages, stream);
     return e == hipSuccess ? SOL_OK : SOL_ERR_LAUNCH;
 }
 

@@ -528,13 +528,13 @@ static hipError_t launch_fast_tile(const IgemmParams& p, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// tile: 0 = 128 x 128, 1 = 128 pixels x 64 channels, 2 = 64 x 64, 3 = 256 x 128; stages: 2, 3 or 4
+// tile: 0 = 128 x 128, 1 = 128 pixels x 64 channels, 2 = 64 x 64, 3 = 256 x 128; stages: 2, 3 or 4 (128 x 128 with four
+// stages is the eight-wave kernel of igemm_wide.hip)
 hipError_t launch_igemm_fast(const IgemmParams& p, int tile, int stages, hipStream_t stream) {
     if (p.total_tiles <= 0) return hipSuccess;
     switch (tile * 8 + stages) {
         case 0 * 8 + 2: return launch_fast_tile<128, 128, 2, 2, 2>(p, stream);
         case 0 * 8 + 3: return launch_fast_tile<128, 128, 2, 2, 3>(p, stream);
-        case 0 * 8 + 4: return launch_fast_tile<128, 128, 2, 2, 4>(p, stream);
         case 1 * 8 + 2: return launch_fast_tile<128, 64, 2, 2, 2>(p, stream);
         case 1 * 8 + 3: return launch_fast_tile<128, 64, 2, 2, 3>(p, stream);
         case 1 * 8 + 4: return launch_fast_tile<128, 64, 2, 2, 4>(p, stream);

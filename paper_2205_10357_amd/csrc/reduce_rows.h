@@ -5,8 +5,9 @@
 
 namespace sol {
 
-// floats of LDS the row reduction needs (256 split sums + 4 wave sums)
-constexpr int kReduceLdsFloats = 260;
+// floats of LDS the row reduction needs in a workgroup of nt threads (a split sum per thread, a sum per wave)
+constexpr int reduce_lds_floats(int nt) { return nt + nt / 64; }
+constexpr int kReduceLdsFloats = reduce_lds_floats(256);
 // most splits a thread has in flight per chunk; reads of up to this many splits beyond the last are issued (and return 0)
 constexpr int kReduceBatch = 16;
 
@@ -18,30 +19,30 @@ inline bool reduce_rows_ok(const ReduceParams& p) {
            ((long long)p.splits + kReduceBatch) * p.C_out * p.K * 4 <= 0x7fffffffLL;
 }
 
-// A team of TS threads (TS = 64, 128 or 256; 256 / TS teams in the workgroup) finishes row `co` of the weight
+// A team of TS threads (TS = 64, 128 or 256; NT / TS teams in the workgroup of NT) finishes row `co` of the weight
 // gradient: fixed-order sum over the splits, dW = scale * G, dscale = <W[co,:], G[co,:]> via wavefront shuffles,
-// dshift = sum of the split column sums.  Workgroups `block`, `block + nblocks`, ... take 256 / TS rows each per pass.
+// dshift = sum of the split column sums.  Workgroups `block`, `block + nblocks`, ... take NT / TS rows each per pass.
 // A thread takes 4 consecutive elements at a time, CH such chunks TS * 4 apart, with kReduceBatch splits of each in
 // flight.  Whatever CH is, every element adds its splits one after the other (+0 for splits that do not exist) and a
 // thread adds its elements to the dscale sum in rising order.  TS < 256 needs K <= 4 TS and splits <= TS, and then
 // adds the same numbers in the same order as TS = 256 does.  reduce_rows_ok(p) must hold.  `scratch`:
-// kReduceLdsFloats floats of LDS.  All 256 threads must call (barriers inside).
+// reduce_lds_floats(NT) floats of LDS.  All NT threads must call (barriers inside).
 // (A compute unit whose loads miss the L2 moves about 25 GB/s whatever it has in flight beyond this: two rows per
 // team at once took as long per byte.)
-template <int TS, int CH, int BATCH = kReduceBatch>
+template <int TS, int CH, int BATCH = kReduceBatch, int NT = 256>
 __device__ __forceinline__ void reduce_rows_vec(const ReduceParams& p, int block, int nblocks, float* scratch) {
     static_assert(TS == 64 || TS == 128 || TS == 256, "one, two or four waves per row");
     static_assert(BATCH >= 1 && BATCH <= kReduceBatch, "reduce_rows_ok allows for kReduceBatch splits beyond the last");
-    constexpr int TEAMS = 256 / TS;
+    constexpr int TEAMS = NT / TS;
     const int tid = threadIdx.x, team = tid / TS, t = tid % TS;
     const unsigned split_bytes = (unsigned)p.C_out * (unsigned)p.K * 4u;
     const buffer_rsrc_t part_rs = make_buffer_rsrc(p.partial, (unsigned)p.splits * split_bytes);
     constexpr unsigned kNowhere = 0x80000000u;      // beyond the buffer whatever split offset is added
-    float* ssum = scratch;            // [256]
-    float* wsum = scratch + 256;      // [4]
+    float* ssum = scratch;            // [NT]
+    float* wsum = scratch + NT;       // [NT / 64]
     for (int co0 = block * TEAMS; co0 < p.C_out; co0 += nblocks * TEAMS) {
         const int co = co0 + team;
-        const bool live = co < p.C_out;
+        const bool live = team < TEAMS && co < p.C_out;      // threads beyond the last whole team stay idle
         const long long row = (long long)(live ? co : 0) * p.K;
         float dot = 0.f, mine = 0.f;
         if (live) {
@@ -101,7 +102,7 @@ __device__ __forceinline__ void reduce_rows_vec(const ReduceParams& p, int block
         __syncthreads();
         if (live && t == 0) {
             float ds;
-            if constexpr (TS == 256) ds = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+            if constexpr (TS == 256) ds = (wsum[4 * team] + wsum[4 * team + 1]) + (wsum[4 * team + 2] + wsum[4 * team + 3]);
             else if constexpr (TS == 128) ds = wsum[2 * team] + wsum[2 * team + 1];
             else ds = wsum[team];
             float db = 0.f;
@@ -117,14 +118,14 @@ __device__ __forceinline__ void reduce_rows_vec(const ReduceParams& p, int block
 // Workgroup `block` of `nblocks` that ride along with another kernel's launch: the narrowest team that covers a row,
 // up to three chunks per thread at a time where rows are longer than the workgroup.
 // SLIM: for host kernels with a small register budget (one chunk, 8 splits in flight).
-template <bool SLIM>
+template <bool SLIM, int NT = 256>
 __device__ __forceinline__ void reduce_rows_riding(const ReduceParams& p, int block, int nblocks, float* scratch) {
     constexpr int B = SLIM ? 8 : kReduceBatch;
-    if (p.K <= 256) reduce_rows_vec<64, 1, B>(p, block, nblocks, scratch);
-    else if (p.K <= 512) reduce_rows_vec<128, 1, B>(p, block, nblocks, scratch);
-    else if (SLIM || p.K <= 1024) reduce_rows_vec<256, 1, B>(p, block, nblocks, scratch);
-    else if (p.K <= 2048) reduce_rows_vec<256, 2, B>(p, block, nblocks, scratch);
-    else reduce_rows_vec<256, 3, B>(p, block, nblocks, scratch);
+    if (p.K <= 256) reduce_rows_vec<64, 1, B, NT>(p, block, nblocks, scratch);
+    else if (p.K <= 512) reduce_rows_vec<128, 1, B, NT>(p, block, nblocks, scratch);
+    else if (SLIM || p.K <= 1024) reduce_rows_vec<256, 1, B, NT>(p, block, nblocks, scratch);
+    else if (p.K <= 2048) reduce_rows_vec<256, 2, B, NT>(p, block, nblocks, scratch);
+    else reduce_rows_vec<256, 3, B, NT>(p, block, nblocks, scratch);
 }
 
 // what a launch must satisfy to carry the reduction along (the narrow teams hold one split sum per thread)

@@ -1,0 +1,47 @@
+"""GPU parity of the implicit-GEMM family that the launch planner chooses by size: eight-wave tiles.  Every tile is forced on shapes around its edges (rows and channels one below, at and above a tile,
+fewer slices than waves or ring stages, strided row classes, a class without taps) and compared with the CPU checker."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from paper_2205_10357_amd import binding as B                 # noqa: E402
+from paper_2205_10357_amd import workloads as wl              # noqa: E402
+from tests import parity_util as pu                           # noqa: E402
+
+SHAPES = {
+    "one_slice_few_rows": dict(N=1, H=3, W=5, C_in=64, C_out=64, K=1, stride=1, pad=0, res=True),
+    "rows_one_over_a_tile": dict(N=1, H=3, W=43, C_in=64, C_out=136, K=3, stride=1, pad=1, res=True),
+    "rows_one_under_a_tile": dict(N=1, H=5, W=51, C_in=128, C_out=264, K=3, stride=1, pad=1),
+    "long_reduction_few_rows": dict(N=1, H=4, W=4, C_in=512, C_out=72, K=3, stride=1, pad=1),
+    "strided_classes": dict(N=2, H=15, W=13, C_in=64, C_out=128, K=3, stride=2, pad=1),
+    "strided_1x1": dict(N=2, H=9, W=11, C_in=192, C_out=320, K=1, stride=2, pad=0, relu=False),
+}
+
+
+def run_forced(shape, family, n, sol_env, rides=False):
+    sol_env(family, n)
+    case = pu.make_case(211, **SHAPES[shape])
+    r = np.random.default_rng(212)
+    dxm = wl.snap_to_bf16(np.maximum(r.standard_normal(case["x"].shape), 0).astype(np.float32))
+    ad = wl.snap_to_bf16(r.standard_normal(case["x"].shape).astype(np.float32))
+    if rides:
+        sol_env("SOL_REDUCE_RIDES", 3)
+    print(f"[{family}={n}] {shape}", flush=True)
+    got = pu.gpu_block(case, addend=ad, dx_mask=dxm, premasked=True)
+    pu.check_block(case, got, addend=ad, dx_mask=dxm, premasked=True)
+    return got
+
+
+@pytest.mark.parametrize("tile", [1, 2, 3])
+@pytest.mark.parametrize("shape", list(SHAPES), ids=list(SHAPES))
+def test_eight_wave_tiles(shape, tile, sol_env):
+    """Also bit for bit against the four-wave 64 x 64 tile (same order of the reduction), with riding reductions."""
+    got = run_forced(shape, "SOL_WIDE", tile, sol_env, rides=True)
+    sol_env("SOL_WIDE", -1)
+    sol_env("SOL_FAST_TILE", 2)
+    ref = run_forced(shape, "SOL_FAST_STAGES", 2, sol_env)
+    for key in ("y", "dx"):
+        assert np.array_equal(got[key], ref[key]), key
