@@ -1,4 +1,5 @@
-"""GPU parity of the implicit-GEMM family that the launch planner chooses by size: eight-wave tiles.  Every tile is forced on shapes around its edges (rows and channels one below, at and above a tile,
+"""GPU parity of the implicit-GEMM families that the launch planner chooses by size: eight-wave tiles and tiles whose
+waves split the reduction.  Every tile is forced on shapes around its edges (rows and channels one below, at and above a tile,
 fewer slices than waves or ring stages, strided row classes, a class without taps) and compared with the CPU checker."""
 import numpy as np
 import pytest
@@ -42,6 +43,16 @@ def test_eight_wave_tiles(shape, tile, sol_env):
     got = run_forced(shape, "SOL_WIDE", tile, sol_env, rides=True)
     sol_env("SOL_WIDE", -1)
     sol_env("SOL_FAST_TILE", 2)
-    ref = run_forced(shape, "SOL_FAST_STAGES", 2, sol_env)
+    ref = run_forced(shape, "SOL_KSPLIT", -1, sol_env)
     for key in ("y", "dx"):
         assert np.array_equal(got[key], ref[key]), key
+
+
+@pytest.mark.parametrize("tile", [1, 2, 3, 4])
+@pytest.mark.parametrize("shape", list(SHAPES), ids=list(SHAPES))
+def test_tiles_whose_waves_split_the_reduction(shape, tile, sol_env):
+    """Twice: the partial tiles are added in a fixed order, so the bits repeat; the second time with riding reductions."""
+    a = run_forced(shape, "SOL_KSPLIT", tile, sol_env)
+    b = run_forced(shape, "SOL_KSPLIT", tile, sol_env, rides=True)
+    for key in ("y", "dx", "dW", "dscale", "dshift"):
+        assert np.array_equal(a[key], b[key]), key
