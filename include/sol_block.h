@@ -163,7 +163,8 @@ SOL_API size_t sol_block_workspace_bytes(const sol_block_desc* desc, int pass);
  * splits: 0 = library's choice; the workspace size of the backward pass depends on it, so install
  * plans before asking sol_block_workspace_bytes.  Plans only apply where the pipelined bf16 kernels
  * run; elsewhere they are ignored.  They change speed, never which result is correct: forward and
- * data gradient do not depend on the plan at all, the weight gradient only in the order of its fp32
+ * data gradient have the same bits under every tile and depth (the library's own choice may be a kernel
+ * that adds the fp32 products in another order), the weight gradient differs in the order of its fp32
  * partial sums.  Host-only calls, safe from any thread (a small table behind a mutex).
  */
 enum { SOL_PLAN_FWD = 0, SOL_PLAN_DGRAD = 1, SOL_PLAN_WGRAD = 2 };

@@ -58,12 +58,12 @@ inline void clear_stale_error() { (void)hipGetLastError(); }
 enum Knob {
     K_IGEMM_TILE, K_IGEMM_FAST, K_FAST_TILE, K_FAST_SHORTK, K_FAST_MANY, K_FAST_STAGES, K_WGRAD_SPLITS, K_WGRAD_TARGET,
     K_SMALLC, K_FILL_UNTOUCHED, K_WGRAD_FAST, K_PACK_FUSED, K_WGRAD_STAGES, K_PREMASK, K_PANEL, K_PANEL_TILES,
-    K_REDUCE_RIDES, K_WIDE, K_KSPLIT, K_COUNT
+    K_REDUCE_RIDES, K_WIDE, K_KSPLIT, K_HALO, K_COUNT
 };
 const char* const kKnobNames[K_COUNT] = {
     "SOL_IGEMM_TILE", "SOL_IGEMM_FAST", "SOL_FAST_TILE", "SOL_FAST_SHORTK", "SOL_FAST_MANY", "SOL_FAST_STAGES",
     "SOL_WGRAD_SPLITS", "SOL_WGRAD_TARGET", "SOL_SMALLC", "SOL_FILL_UNTOUCHED", "SOL_WGRAD_FAST", "SOL_PACK_FUSED",
-    "SOL_WGRAD_STAGES", "SOL_PREMASK", "SOL_PANEL", "SOL_PANEL_TILES", "SOL_REDUCE_RIDES", "SOL_WIDE", "SOL_KSPLIT"};
+    "SOL_WGRAD_STAGES", "SOL_PREMASK", "SOL_PANEL", "SOL_PANEL_TILES", "SOL_REDUCE_RIDES", "SOL_WIDE", "SOL_KSPLIT", "SOL_HALO"};
 constexpr int kKnobUnset = INT32_MIN;
 std::atomic<int> g_knobs[K_COUNT];
 std::atomic<bool> g_knobs_loaded{false};
@@ -142,7 +142,7 @@ int reduce_rider_blocks(int gemm_wgs, bool small_tile, const ReduceParams* rider
 }
 
 // Which kernel family and tile a pipelined launch takes.
-enum GemmFamily { GEMM_FAST, GEMM_WIDE, GEMM_KSPLIT };
+enum GemmFamily { GEMM_FAST, GEMM_WIDE, GEMM_KSPLIT, GEMM_HALO };
 struct GemmChoice {
     GemmFamily family;
     int tile;
@@ -157,8 +157,8 @@ int tiles_of(const IgemmParams& p, const long long* rows, int bp, int bc) {
     return t < INT_MAX ? (int)t : INT_MAX;
 }
 
-// The choice between the four-wave tiles (`tile`: what the thresholds of run_igemm picked), the eight-wave tiles and
-// the tiles whose waves split the reduction, by expected time.  All of them
+// The choice between the four-wave tiles (`tile`: what the thresholds of run_igemm picked), the eight-wave tiles, the
+// tiles that keep a 3x3 neighbourhood in LDS and the tiles whose waves split the reduction, by expected time.  All of them
 // are bound by what a compute unit copies into LDS and multiplies, plus fixed costs per round of workgroups, so a launch
 // of T workgroups with nk 64-deep slices takes, in ns (fits to launches over the benchmark network's layers at 1 .. 128
 // images, inputs not in L2; 256 compute units):
@@ -166,14 +166,17 @@ int tiles_of(const IgemmParams& p, const long long* rows, int bp, int bc) {
 //   128 x 64, three per compute unit           5000 + nk * max(300, 450 T / 256)
 //   128 x 128, eight waves                     ceil(T / 256) * (5100 + 390 nk)
 //   256 x 128 and 128 x 256, eight waves       ceil(T / 256) * (6500 + 900 nk)
+//   neighbourhood in LDS: 256 x 128            ceil(T / 256) * (8000 + 600 nk)
+//                         128 x 128            ceil(T / 256) * (4200 + 370 nk)
+//                         128 x 64             5000 + nk * max(300, 400 T / 256)
 //   reduction split over the waves             2500 + ceil(T / 256) * (1200 + 1.28 nk (bp + bc))
 // Short reductions (nk < 8) in many tiles are bound by HBM, which the fits do not know: they keep the four-wave tiles
 // (1x1, 401408 pixels, 256 -> 128: 72 us with 128 x 64, 76 us with 256 x 128).  The splitting tiles are for launches that
 // are at most 96 tiles of 64 x 64.
-// Four- and eight-wave tiles add a reduction in the same order, the splitting tiles in an order of their own: which
+// Four- and eight-wave tiles add a reduction in the same order, the other two families in orders of their own: which
 // family a launch takes depends on its sizes only, not on what rides along.  any_order = false (a plan is installed, even
 // one that does not apply to this launch): four- and eight-wave tiles only.
-GemmChoice choose_gemm(const IgemmParams& p, const long long* rows, int tile, const ReduceParams* rider, bool any_order) {
+GemmChoice choose_gemm(IgemmParams& p, const long long* rows, int tile, const ReduceParams* rider, bool any_order) {
     long long all_rows = 0, work = 0;
     for (int c = 0; c < p.ncls; ++c) {
         all_rows += rows[c];
@@ -203,7 +206,7 @@ GemmChoice choose_gemm(const IgemmParams& p, const long long* rows, int tile, co
                 choice = c;
             }
         }
-    } plain, ksplit;
+    } plain, halo, ksplit;
     int bp, bc;
     auto offer_fast = [&](int t) {
         igemm_fast_tile_shape(t, &bp, &bc);
@@ -223,19 +226,29 @@ GemmChoice choose_gemm(const IgemmParams& p, const long long* rows, int tile, co
             plain.offer(GemmChoice{GEMM_WIDE, w}, e, with_rider(e, n, false));
         }
     }
+    if (any_order && knob(K_HALO, 0) >= 0)
+        for (int h = 0; h < HALO_TILES; ++h) {
+            if (!plan_igemm_halo(p, h, &bp, &bc)) continue;
+            const long long n = tiles_of(p, rows, bp, bc);
+            const long long e = h == HALO_256x128 ? rounds(n) * (8000 + 600 * nk)
+                              : h == HALO_128x128 ? rounds(n) * (4200 + 370 * nk)
+                                                  : 5000 + nk * (n < 192 ? 300 : (400 * n) >> 8);
+            halo.offer(GemmChoice{GEMM_HALO, h}, e, with_rider(e, n, h == HALO_128x64));
+        }
     if (any_order && knob(K_KSPLIT, 0) >= 0 && tiles_of(p, rows, 64, 64) <= 96)
         for (int k = 0; k < KSPLIT_TILES; ++k) {
             igemm_ksplit_tile_shape(k, &bp, &bc);
             const long long e = 2500 + rounds(tiles_of(p, rows, bp, bc)) * (1200 + ((nk * (bp + bc) * 328) >> 8));
             ksplit.offer(GemmChoice{GEMM_KSPLIT, k}, e, e);
         }
-    return ksplit.alone < plain.alone ? ksplit.choice : plain.choice;
+    if (ksplit.alone < plain.alone && ksplit.alone < halo.alone) return ksplit.choice;
+    return halo.alone < plain.alone ? halo.choice : plain.choice;
 }
 
 // Fills tile-dependent fields of the launch (tile counts, class offsets) and launches either a pipelined kernel (source
 // channels % 64 == 0, output channels % 8 == 0, no mask on the gathered operand) or the general one.  SOL_IGEMM_FAST=0
 // forces the general kernel; SOL_FAST_TILE / SOL_FAST_STAGES override the pipelined kernel's tile and ring depth,
-// SOL_WIDE, SOL_KSPLIT = n > 0 force tile n - 1 of those families, -1 switches them off (tuning experiments).
+// SOL_WIDE, SOL_HALO, SOL_KSPLIT = n > 0 force tile n - 1 of those families, -1 switches them off (tuning experiments).
 // `rider`: a split reduction the launch may carry along (see above); *rode tells whether it did.
 int run_igemm(IgemmParams& p, const long long* rows, bool mask, const sol_plan& tuned, hipStream_t stream,
               const ReduceParams* rider = nullptr, bool* rode = nullptr) {
@@ -316,7 +329,9 @@ int run_igemm(IgemmParams& p, const long long* rows, bool mask, const sol_plan& 
         if (choice.family == GEMM_FAST && tile == 0 && stages == 4) choice = GemmChoice{GEMM_WIDE, WIDE_128x128};
         if (const int w = knob(K_WIDE, 0); w > 0 && w <= WIDE_TILES) choice = GemmChoice{GEMM_WIDE, w - 1};
         if (const int k = knob(K_KSPLIT, 0); k > 0 && k <= KSPLIT_TILES) choice = GemmChoice{GEMM_KSPLIT, k - 1};
-        if (choice.family == GEMM_WIDE) igemm_wide_tile_shape(choice.tile, &bp, &bc);
+        if (const int h = knob(K_HALO, 0); h > 0 && h <= HALO_TILES && plan_igemm_halo(p, h - 1, &bp, &bc)) choice = GemmChoice{GEMM_HALO, h - 1};
+        if (choice.family == GEMM_HALO) plan_igemm_halo(p, choice.tile, &bp, &bc);
+        else if (choice.family == GEMM_WIDE) igemm_wide_tile_shape(choice.tile, &bp, &bc);
         else if (choice.family == GEMM_KSPLIT) igemm_ksplit_tile_shape(choice.tile, &bp, &bc);
         else igemm_fast_tile_shape(tile, &bp, &bc);
     } else {
@@ -339,10 +354,12 @@ int run_igemm(IgemmParams& p, const long long* rows, bool mask, const sol_plan& 
     }
     p.total_tiles = tiles_p * p.tiles_c;
     hipError_t e;
-    const bool rides = fast_ok && attach(choice.family == GEMM_FAST && (tile == 1 || tile == 2));
+    const bool rides = fast_ok && attach((choice.family == GEMM_FAST && (tile == 1 || tile == 2)) ||
+                                         (choice.family == GEMM_HALO && choice.tile == HALO_128x64));
     trace_point(stream, rides ? SOL_TRACE_IGEMM_REDUCE : fast_ok ? SOL_TRACE_IGEMM : SOL_TRACE_IGEMM_GENERAL);
     if (!fast_ok) e = launch_igemm(p, tile, (p.Cs % 8) == 0, mask, stream);
     else if (choice.family == GEMM_WIDE) e = launch_igemm_wide(p, choice.tile, stream);
+    else if (choice.family == GEMM_HALO) e = launch_igemm_halo(p, choice.tile, stream);
     else if (choice.family == GEMM_KSPLIT) e = launch_igemm_ksplit(p, choice.tile, stream);
     else e = launch_igemm_fast(p, tile, stages, stream);
     return e == hipSuccess ? SOL_OK : SOL_ERR_LAUNCH;

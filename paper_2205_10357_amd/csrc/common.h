@@ -188,6 +188,9 @@ struct IgemmParams {
     int total_tiles;
     int panel_groups;           // panel kernel only: workgroups per 128-pixel panel ...
     int panel_tiles;            // ... and 128-channel tiles each of them walks over
+    int halo_first;             // halo kernel only: source pixel of region row 0 relative to the tile's first pixel ...
+    int halo_copies;            // ... copies per thread that fill a region, and how many of them go out per slice
+    int halo_pace;
     RowClass cls[kMaxClasses];
     // pipelined and panel kernels only: red_blocks > 0 appends that many workgroups to the launch, which finish the
     // split weight gradient of the same block (rows red_block, red_block + red_blocks, ...) instead of multiplying

@@ -1,5 +1,5 @@
-"""GPU parity of the implicit-GEMM families that the launch planner chooses by size: eight-wave tiles and tiles whose
-waves split the reduction.  Every tile is forced on shapes around its edges (rows and channels one below, at and above a tile,
+"""GPU parity of the implicit-GEMM families that the launch planner chooses by size: eight-wave tiles, tiles that
+keep a 3x3 neighbourhood in LDS and tiles whose waves split the reduction.  Every tile is forced on shapes around its edges (rows and channels one below, at and above a tile,
 fewer slices than waves or ring stages, strided row classes, a class without taps) and compared with the CPU checker."""
 import numpy as np
 import pytest
@@ -54,5 +54,26 @@ def test_tiles_whose_waves_split_the_reduction(shape, tile, sol_env):
     """Twice: the partial tiles are added in a fixed order, so the bits repeat; the second time with riding reductions."""
     a = run_forced(shape, "SOL_KSPLIT", tile, sol_env)
     b = run_forced(shape, "SOL_KSPLIT", tile, sol_env, rides=True)
+    for key in ("y", "dx", "dW", "dscale", "dshift"):
+        assert np.array_equal(a[key], b[key]), key
+
+
+HALO_SHAPES = {
+    "image_smaller_than_the_filter_reach": dict(N=3, H=1, W=2, C_in=64, C_out=64, K=3, stride=1, pad=1),
+    "rows_one_over_a_tile": dict(N=1, H=3, W=43, C_in=64, C_out=136, K=3, stride=1, pad=1, res=True),
+    "many_images_in_a_tile": dict(N=11, H=5, W=6, C_in=192, C_out=72, K=3, stride=1, pad=1),
+    "two_copies_per_slice": dict(N=1, H=6, W=56, C_in=128, C_out=128, K=3, stride=1, pad=1, res=True),
+    "wide_rows": dict(N=1, H=4, W=61, C_in=128, C_out=64, K=3, stride=1, pad=1),
+    "5x5": dict(N=2, H=9, W=11, C_in=128, C_out=72, K=5, stride=1, pad=2),
+}
+
+
+@pytest.mark.parametrize("tile", [1, 2, 3])
+@pytest.mark.parametrize("shape", list(HALO_SHAPES), ids=list(HALO_SHAPES))
+def test_tiles_that_keep_the_neighbourhood(shape, tile, sol_env):
+    """Forward and data gradient, again with riding reductions; bits repeat."""
+    SHAPES[shape] = HALO_SHAPES[shape]
+    a = run_forced(shape, "SOL_HALO", tile, sol_env)
+    b = run_forced(shape, "SOL_HALO", tile, sol_env, rides=True)
     for key in ("y", "dx", "dW", "dscale", "dshift"):
         assert np.array_equal(a[key], b[key]), key
