@@ -770,9 +770,10 @@ static int bwd_common(const sol_block_desc* desc, const void* dy, const void* x,
             return dgrad_bf16(desc, g, dy, ymask, pk.out, dx, dx_addend, dx_addend_mask, dx_mask, st,
                               reduce_may_ride ? &rp : nullptr, &reduce_rode);
         }
-        DirectParams p = direct_params();
+        DirectParams p = direct_params();        // with the weight gradient, which is one launch with it
+        if (!dW) p.G = nullptr;
         trace_point(st, SOL_TRACE_DIRECT);
-        return launch_direct_dgrad_f32(p, st) == hipSuccess ? SOL_OK : SOL_ERR_LAUNCH;
+        return launch_direct_bwd_f32(p, st) == hipSuccess ? SOL_OK : SOL_ERR_LAUNCH;
     };
 
     // ---- weight branch: split weight-gradient GEMM, then the reduction that also finishes dscale, dshift ----
@@ -818,10 +819,10 @@ static int bwd_common(const sol_block_desc* desc, const void* dy, const void* x,
                 trace_point(st, SOL_TRACE_WGRAD_GENERAL);
                 if (launch_wgrad(wp, vec, relu, st) != hipSuccess) return SOL_ERR_LAUNCH;
             }
-        } else {
+        } else if (!dx) {
             DirectParams p = direct_params();
             trace_point(st, SOL_TRACE_DIRECT);
-            if (launch_direct_wgrad_f32(p, st) != hipSuccess) return SOL_ERR_LAUNCH;
+            if (launch_direct_bwd_f32(p, st) != hipSuccess) return SOL_ERR_LAUNCH;
         }
         if (reduce_may_ride) return SOL_OK;
         trace_point(st, SOL_TRACE_WGRAD_REDUCE);

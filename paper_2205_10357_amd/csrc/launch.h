@@ -54,6 +54,8 @@ struct DirectParams {
     float* G;                 // unscaled weight gradient [C_out][K] (one split)
     float* dshift_partial;    // [C_out]
     int N, H, W_, C_in, C_out, KH, KW, stride, pad, Ho, Wo, relu;
+    FastDiv div_cin, div_cout, div_kw, div_howo, div_wo, div_hw, div_w, div_stride;   // set by the launchers, as
+    int dgrad_blocks;                                                                 // the split of the backward launch
 };
 
 
@@ -108,8 +110,7 @@ hipError_t launch_wgrad(const WgradParams& p, bool vec, bool mask, hipStream_t s
 hipError_t launch_wgrad_fast(const WgradParams& p, int stages, hipStream_t stream);
 hipError_t launch_wgrad_reduce(const ReduceParams& p, hipStream_t stream);
 hipError_t launch_direct_fwd_f32(const DirectParams& p, hipStream_t s);
-hipError_t launch_direct_dgrad_f32(const DirectParams& p, hipStream_t s);
-hipError_t launch_direct_wgrad_f32(const DirectParams& p, hipStream_t s);
+hipError_t launch_direct_bwd_f32(const DirectParams& p, hipStream_t s);
 hipError_t launch_pack_dgrad_weights(const PackParams& p, hipStream_t s);
 hipError_t launch_untouched_pixels(void* dx, const void* addend, const void* addend_mask, const void* out_mask, int N,
                                    int H, int W, int C, int KH, int KW, int stride, int pad, hipStream_t s);

@@ -77,3 +77,21 @@ def test_tiles_that_keep_the_neighbourhood(shape, tile, sol_env):
     b = run_forced(shape, "SOL_HALO", tile, sol_env, rides=True)
     for key in ("y", "dx", "dW", "dscale", "dshift"):
         assert np.array_equal(a[key], b[key]), key
+
+
+@pytest.mark.parametrize("shape", [
+    dict(N=1, H=4, W=4, C_in=16, C_out=16, K=1, stride=1, pad=0),                 # exactly one tile
+    dict(N=3, H=5, W=7, C_in=17, C_out=33, K=3, stride=1, pad=1, res=True),       # one over a tile everywhere
+    dict(N=1, H=1, W=1, C_in=1, C_out=1, K=1, stride=1, pad=0),                   # fewer reduction elements than waves
+    dict(N=2, H=11, W=9, C_in=5, C_out=3, K=5, stride=3, pad=2),
+])
+def test_fp32_matrix_kernels(shape):
+    case = pu.make_case(231, bf16=False, **shape)
+    r = np.random.default_rng(232)
+    ad = r.standard_normal(case["x"].shape).astype(np.float32)
+    am = r.standard_normal(case["x"].shape).astype(np.float32)
+    one = pu.gpu_block(case, addend=ad, addend_mask=am, want_dres=True)
+    pu.check_block(case, one, addend=ad, addend_mask=am)
+    two = pu.gpu_block(case, addend=ad, addend_mask=am, two_calls=True)           # each branch as a launch of its own
+    for key in ("dx", "dW", "dscale", "dshift"):
+        assert np.array_equal(one[key], two[key]), key
