@@ -139,25 +139,40 @@ def lib():
 
 
 def _ptr(a) -> Optional[int]:
-    if a is None:
-        return None
-    if isinstance(a, int):
+    if a is None or isinstance(a, int):
         return a
-    if hasattr(a, "data_ptr"):
-        return int(a.data_ptr())
-    raise TypeError(f"cannot take a device address from {type(a)!r}")
+    try:
+        return a.data_ptr()
+    except AttributeError:
+        raise TypeError(f"cannot take a device address from {type(a)!r}") from None
 
 
 def _nbytes(a) -> int:
     if a is None:
         return 0
-    return int(a.numel() * a.element_size())
+    return a.numel() * a.element_size()
+
+
+_torch = None
+
+
+def _current_stream() -> Optional[int]:
+    """Handle of torch's current stream.  The raw query is 0.3 us where torch.cuda.current_stream() builds a Stream object
+    in 2.9 us, a third of a whole call of this binding."""
+    global _torch
+    if _torch is None:
+        import torch
+        torch.cuda.init()
+        _torch = torch
+    raw = getattr(_torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return int(_torch.cuda.current_stream().cuda_stream) or None
+    return raw(_torch.cuda.current_device()) or None
 
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        return int(torch.cuda.current_stream().cuda_stream) or None
+        return _current_stream()
     if isinstance(stream, int):
         return stream or None
     return int(stream.cuda_stream) or None
