@@ -180,10 +180,11 @@ GemmChoice choose_gemm(IgemmParams& p, const long long* rows, int tile, const Re
     long long all_rows = 0, work = 0;
     for (int c = 0; c < p.ncls; ++c) {
         all_rows += rows[c];
-        work += rows[c] * p.cls[c].Th * p.cls[c].Tw * (p.Cs / 64);
+        work += rows[c] * p.cls[c].Th * p.cls[c].Tw * p.Cs;
     }
-    const long long nk = p.ncls == 1 ? (long long)p.cls[0].Th * p.cls[0].Tw * (p.Cs / 64)          // slices of an average row
-                       : all_rows > 0 ? (work + all_rows - 1) / all_rows : 0;
+    const bool ragged = (p.Cs & 63) != 0;                     // slices of the flattened (tap, channel) index
+    const long long nk = p.ncls == 1 ? ((long long)p.cls[0].Th * p.cls[0].Tw * p.Cs + 63) >> 6          // slices of an average row
+                       : all_rows > 0 ? (work / 64 + all_rows - 1) / all_rows : 0;
     auto rounds = [](long long t) { return (t + 255) >> 8; };
     // A split reduction that rides along: on the compute units that large tiles leave idle it moves about 25 bytes per ns
     // and unit (a launch of its own, 4000 ns, where fewer than 32 are idle); among many small workgroups it fills gaps.
@@ -217,7 +218,8 @@ GemmChoice choose_gemm(IgemmParams& p, const long long* rows, int tile, const Re
         plain.offer(GemmChoice{GEMM_FAST, t}, e, with_rider(e, n, t == 1 || t == 2));
     };
     offer_fast(tile);
-    if (knob(K_WIDE, 0) >= 0 && nk >= 8 && p.Nc > 64) {
+    if (ragged) offer_fast(3 - tile);                         // 128 x 64 and 64 x 64
+    if (!ragged && knob(K_WIDE, 0) >= 0 && nk >= 8 && p.Nc > 64) {
         if (tile != 1) offer_fast(1);
         for (int w = 0; w < WIDE_TILES; ++w) {
             igemm_wide_tile_shape(w, &bp, &bc);
@@ -226,7 +228,7 @@ GemmChoice choose_gemm(IgemmParams& p, const long long* rows, int tile, const Re
             plain.offer(GemmChoice{GEMM_WIDE, w}, e, with_rider(e, n, false));
         }
     }
-    if (any_order && knob(K_HALO, 0) >= 0)
+    if (!ragged && any_order && knob(K_HALO, 0) >= 0)
         for (int h = 0; h < HALO_TILES; ++h) {
             if (!plan_igemm_halo(p, h, &bp, &bc)) continue;
             const long long n = tiles_of(p, rows, bp, bc);
@@ -245,8 +247,8 @@ GemmChoice choose_gemm(IgemmParams& p, const long long* rows, int tile, const Re
     return halo.alone < plain.alone ? halo.choice : plain.choice;
 }
 
-// Fills tile-dependent fields of the launch (tile counts, class offsets) and launches either a pipelined kernel (source
-// channels % 64 == 0, output channels % 8 == 0, no mask on the gathered operand) or the general one.  SOL_IGEMM_FAST=0
+// Fills tile-dependent fields of the launch (tile counts, class offsets) and launches either a pipelined kernel (channel
+// counts multiples of 8, no mask on the gathered operand) or the general one.  SOL_IGEMM_FAST=0
 // forces the general kernel; SOL_FAST_TILE / SOL_FAST_STAGES override the pipelined kernel's tile and ring depth,
 // SOL_WIDE, SOL_HALO, SOL_KSPLIT = n > 0 force tile n - 1 of those families, -1 switches them off (tuning experiments).
 // `rider`: a split reduction the launch may carry along (see above); *rode tells whether it did.
@@ -272,18 +274,20 @@ int run_igemm(IgemmParams& p, const long long* rows, bool mask, const sol_plan& 
         if (m > reach) reach = m;
     }
     const bool addressable = (long long)p.src_bytes + reach <= 0xffffffffLL && reach <= 0x7fffffffLL;
-    const bool fast_ok = !mask && few_taps && addressable && (p.Cs % 64) == 0 && (p.Nc % 8) == 0 &&
-                         knob(K_IGEMM_FAST, 1) != 0;
+    // source channels that are no multiple of 64 take the pipelined tiles with a table of chunk addresses in LDS
+    const bool ragged = (p.Cs % 64) != 0;
+    const bool fast_ok = !mask && few_taps && addressable && (p.Cs % 8) == 0 && (p.Nc % 8) == 0 &&
+                         (!ragged || igemm_chunk_table_bytes(p) <= 16384) && knob(K_IGEMM_FAST, 1) != 0;
     int bp, bc, tile = 0, stages = 0;
     GemmChoice choice{GEMM_FAST, 0};
     bool many_tiles = false;
     // 1x1 / stride 1 with a short reduction and a wide output: a workgroup keeps its pixel panel in LDS and walks over
     // several channel tiles (tile code 4)
-    const bool panel_ok = fast_ok && knob(K_PANEL, 1) != 0 && igemm_panel_eligible(p);
+    const bool panel_ok = fast_ok && !ragged && knob(K_PANEL, 1) != 0 && igemm_panel_eligible(p);
     if (fast_ok) {
         long long slices = 0;
         for (int c = 0; c < p.ncls; ++c) {
-            const long long s = (long long)p.cls[c].Th * p.cls[c].Tw * (p.Cs / 64);
+            const long long s = ((long long)p.cls[c].Th * p.cls[c].Tw * p.Cs + 63) >> 6;
             if (s > slices) slices = s;
         }
         tile = knob(K_FAST_TILE, -1);
@@ -317,6 +321,7 @@ int run_igemm(IgemmParams& p, const long long* rows, bool mask, const sol_plan& 
             trace_point(stream, attach(false) ? SOL_TRACE_IGEMM_PANEL_REDUCE : SOL_TRACE_IGEMM_PANEL);
             return launch_igemm_panel(p, stream) == hipSuccess ? SOL_OK : SOL_ERR_LAUNCH;
         }
+        if (ragged && tile != 2) tile = 1;
         choice = free_choice ? choose_gemm(p, rows, tile, knob(K_REDUCE_RIDES, 1) != 0 ? rider : nullptr, tuned.tile < 0) : GemmChoice{GEMM_FAST, tile};
         if (choice.family == GEMM_FAST && choice.tile != tile) {
             tile = choice.tile;
@@ -327,9 +332,9 @@ int run_igemm(IgemmParams& p, const long long* rows, bool mask, const sol_plan& 
         if (stages < 2 || stages > 4) stages = (slices <= 4 || many_tiles) ? 2 : (slices <= 8 ? 3 : 4);
         if (tile == 3 && stages > 3) stages = 3;
         if (choice.family == GEMM_FAST && tile == 0 && stages == 4) choice = GemmChoice{GEMM_WIDE, WIDE_128x128};
-        if (const int w = knob(K_WIDE, 0); w > 0 && w <= WIDE_TILES) choice = GemmChoice{GEMM_WIDE, w - 1};
+        if (const int w = knob(K_WIDE, 0); w > 0 && w <= WIDE_TILES && !ragged) choice = GemmChoice{GEMM_WIDE, w - 1};
         if (const int k = knob(K_KSPLIT, 0); k > 0 && k <= KSPLIT_TILES) choice = GemmChoice{GEMM_KSPLIT, k - 1};
-        if (const int h = knob(K_HALO, 0); h > 0 && h <= HALO_TILES && plan_igemm_halo(p, h - 1, &bp, &bc)) choice = GemmChoice{GEMM_HALO, h - 1};
+        if (const int h = knob(K_HALO, 0); h > 0 && h <= HALO_TILES && !ragged && plan_igemm_halo(p, h - 1, &bp, &bc)) choice = GemmChoice{GEMM_HALO, h - 1};
         if (choice.family == GEMM_HALO) plan_igemm_halo(p, choice.tile, &bp, &bc);
         else if (choice.family == GEMM_WIDE) igemm_wide_tile_shape(choice.tile, &bp, &bc);
         else if (choice.family == GEMM_KSPLIT) igemm_ksplit_tile_shape(choice.tile, &bp, &bc);
@@ -361,6 +366,7 @@ int run_igemm(IgemmParams& p, const long long* rows, bool mask, const sol_plan& 
     else if (choice.family == GEMM_WIDE) e = launch_igemm_wide(p, choice.tile, stream);
     else if (choice.family == GEMM_HALO) e = launch_igemm_halo(p, choice.tile, stream);
     else if (choice.family == GEMM_KSPLIT) e = launch_igemm_ksplit(p, choice.tile, stream);
+    else if (ragged) e = launch_igemm_fast_ragged(p, tile, stages, stream);
     else e = launch_igemm_fast(p, tile, stages, stream);
     return e == hipSuccess ? SOL_OK : SOL_ERR_LAUNCH;
 }

@@ -28,7 +28,7 @@ __global__ __launch_bounds__(256) void pack_dgrad_weights_kernel(const PackParam
     p.out[off + ((long long)ci * Th * Tw + (jh * Tw + jw)) * p.C_out + co] = f32_to_bf16(p.scale[co] * w);
 }
 
-// Same re-packing for channel counts that are multiples of 64: one workgroup per (tap, 64 co, 64 ci) tile.
+// Same re-packing for channel counts that are multiples of 8: one workgroup per (tap, 64 co, 64 ci) tile.
 __global__ __launch_bounds__(256) void pack_dgrad_weights_tiled_kernel(const PackParams p) {
     __shared__ __align__(16) bf16_t tile[64 * kPackTilePitch];
     pack_dgrad_weights_tile(p, (int)blockIdx.x, tile);
@@ -160,7 +160,7 @@ hipError_t launch_untouched_pixels(void* dx, const void* addend, const void* add
 
 hipError_t launch_pack_dgrad_weights(const PackParams& p, hipStream_t s) {
     const long long total = (long long)p.C_out * p.KH * p.KW * p.C_in;
-    if ((p.C_in & 63) == 0 && (p.C_out & 63) == 0)
+    if (pack_tiled_ok(p))
         SOL_LAUNCH(pack_dgrad_weights_tiled_kernel, dim3((unsigned)pack_tile_count(p)), dim3(256), 0, s, p);
     else
         SOL_LAUNCH(pack_dgrad_weights_kernel, dim3(blocks_for(total)), dim3(256), 0, s, p);

@@ -33,7 +33,9 @@ __device__ __forceinline__ void ksplit_pin() {
     }
 }
 
-template <int MF, int TP, int TC, int KW, int NS>
+// RAGGED: source channels a multiple of 8 only; slices of the flattened (tap, channel) index and a chunk table, see
+// igemm_fast.hip.
+template <int MF, int TP, int TC, int KW, int NS, bool RAGGED>
 __global__ __launch_bounds__(64 * KW) void igemm_ksplit_kernel(const IgemmParams p) {
     constexpr int BP = MF * TP, BC = MF * TC, NT = 64 * KW;
     constexpr int STEPS = MF == 32 ? 4 : 2;                     // MFMA steps per 64-deep slice: 32x32x16 or 16x16x32
@@ -74,8 +76,8 @@ __global__ __launch_bounds__(64 * KW) void igemm_ksplit_kernel(const IgemmParams
     const int row0 = tp * BP, ch0 = tc * BC;
     const int cpt = p.Cs >> 6;
     const int ntaps = rc.Th * rc.Tw;
-    const int nk = ntaps * cpt;
     const int K = ntaps * p.Cs;
+    const int nk = RAGGED ? (K + 63) >> 6 : ntaps * cpt;
     const GatherBase gb = gather_base(rc, p.Ws, p.Cs);
     const buffer_rsrc_t src_rs = make_buffer_rsrc(reinterpret_cast<const char*>(p.src) - gb.margin, p.src_bytes + gb.margin);
     const buffer_rsrc_t w_rs = make_buffer_rsrc(p.wmat + rc.b_off, (unsigned)((long long)K * p.Nc * 2));
@@ -92,26 +94,55 @@ __global__ __launch_bounds__(64 * KW) void igemm_ksplit_kernel(const IgemmParams
     // slice of this wave that is requested next: tap and channel slice
     int q_sl = wave, q_cs = wave, q_th = 0, q_tw = 0, q_tap = 0;
     auto settle = [&]() {
-        while (q_cs >= cpt) {
-            q_cs -= cpt;
-            ++q_tap;
-            if (++q_tw == rc.Tw) {
-                q_tw = 0;
-                ++q_th;
+        if constexpr (!RAGGED)
+            while (q_cs >= cpt) {
+                q_cs -= cpt;
+                ++q_tap;
+                if (++q_tw == rc.Tw) {
+                    q_tw = 0;
+                    ++q_th;
+                }
             }
-        }
     };
     settle();
+    uintx2* const table = reinterpret_cast<uintx2*>(ldsb + KW * RINGB);
+    uintx2 chunk[2];                         // entries of this lane's two logical chunks of the slice that is requested
+    if constexpr (RAGGED) {
+        const int per_tap = p.Cs >> 3;
+        for (int e = tid; e < nk * 8; e += NT) {
+            const int tap = e / per_tap, c = e - tap * per_tap;
+            const int th = tap / rc.Tw, tw = tap - th * rc.Tw;
+            table[e] = e < (K >> 3) ? uintx2{(unsigned)((((th * p.Ws + tw) * rc.tap_step) * p.Cs + c * 8) * 2 - gb.delta_min), (unsigned)tap}
+                                    : uintx2{0u, 0x80000000u};
+        }
+        __syncthreads();
+    }
     auto request_weights = [&](int stage) {
+        if constexpr (RAGGED) {
+            const int mine = pc ^ ksplit_swizzle(j8);
+            chunk[0] = table[q_sl * 8 + mine];
+            chunk[1] = table[q_sl * 8 + (mine ^ 4)];
+        }
 #pragma unroll
-        for (int i = 0; i < LC; ++i) dma16_buf_to_lds(w_rs, wrowb[i], (unsigned)(q_sl * 128), ring + stage * STAGEB + (BP + 8 * i) * 128);
+        for (int i = 0; i < LC; ++i)
+            dma16_buf_to_lds(w_rs, RAGGED ? wrowb[i] | (unsigned)((int)chunk[i & 1][1] >> 31) : wrowb[i], (unsigned)(q_sl * 128),
+                             ring + stage * STAGEB + (BP + 8 * i) * 128);
     };
     auto request_pixels = [&](int stage) {
-        const unsigned s_pix = (unsigned)((((q_th * p.Ws + q_tw) * rc.tap_step) * p.Cs + q_cs * 64) * 2 - gb.delta_min);
+        if constexpr (RAGGED) {
 #pragma unroll
-        for (int i = 0; i < LP; ++i)
-            dma16_buf_to_lds(src_rs, (rowb[i] + gb.margin + (unsigned)gb.delta_min) | (unsigned)__builtin_amdgcn_sbfe((int)badtap[i], q_tap & 31, 1),
-                             s_pix, ring + stage * STAGEB + 8 * i * 128);
+            for (int i = 0; i < LP; ++i) {
+                const uintx2 e = chunk[i & 1];
+                const unsigned bad = (unsigned)__builtin_amdgcn_sbfe((int)badtap[i], e[1] & 31u, 1) | (unsigned)((int)e[1] >> 31);
+                dma16_buf_to_lds(src_rs, (rowb[i] + gb.margin + (unsigned)gb.delta_min + e[0]) | bad, 0u, ring + stage * STAGEB + 8 * i * 128);
+            }
+        } else {
+            const unsigned s_pix = (unsigned)((((q_th * p.Ws + q_tw) * rc.tap_step) * p.Cs + q_cs * 64) * 2 - gb.delta_min);
+#pragma unroll
+            for (int i = 0; i < LP; ++i)
+                dma16_buf_to_lds(src_rs, (rowb[i] + gb.margin + (unsigned)gb.delta_min) | (unsigned)__builtin_amdgcn_sbfe((int)badtap[i], q_tap & 31, 1),
+                                 s_pix, ring + stage * STAGEB + 8 * i * 128);
+        }
         q_sl += KW;
         q_cs += KW;
         settle();
@@ -121,7 +152,7 @@ __global__ __launch_bounds__(64 * KW) void igemm_ksplit_kernel(const IgemmParams
     const unsigned tap_rows = tap_row_bits(rc);
 #pragma unroll
     for (int i = 0; i < LP; ++i)
-        gather_row(rc, row0 + 8 * i + j8, pc ^ ksplit_swizzle(8 * i + j8), p.Hs, p.Ws, p.Cs, tap_rows, rowb[i], badtap[i]);
+        gather_row(rc, row0 + 8 * i + j8, RAGGED ? 0 : pc ^ ksplit_swizzle(8 * i + j8), p.Hs, p.Ws, p.Cs, tap_rows, rowb[i], badtap[i]);
     if (mine > 0) request_pixels(0);
 #pragma unroll
     for (int s = 1; s < NS; ++s)
@@ -275,25 +306,30 @@ __global__ __launch_bounds__(64 * KW) void igemm_ksplit_kernel(const IgemmParams
     }
 }
 
-template <int MF, int TP, int TC, int KW, int NS>
+template <int MF, int TP, int TC, int KW, int NS, bool RAGGED>
 static hipError_t launch_ksplit_tile(const IgemmParams& p, hipStream_t stream) {
-    const size_t smem = (size_t)KW * NS * (TP + TC) * MF * 128;
-    auto kern = igemm_ksplit_kernel<MF, TP, TC, KW, NS>;
+    const size_t smem = (size_t)KW * NS * (TP + TC) * MF * 128 + (RAGGED ? igemm_chunk_table_bytes(p) : 0);
+    auto kern = igemm_ksplit_kernel<MF, TP, TC, KW, NS, RAGGED>;
     static std::atomic<size_t> granted{0};
     if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), smem, granted); e != hipSuccess) return e;
     SOL_LAUNCH(kern, dim3(p.total_tiles + p.red_blocks), dim3(64 * KW), smem, stream, p);
     return hipGetLastError();
 }
 
-hipError_t launch_igemm_ksplit(const IgemmParams& p, int tile, hipStream_t stream) {
-    if (p.total_tiles <= 0) return hipSuccess;
+template <bool RAGGED>
+static hipError_t launch_ksplit(const IgemmParams& p, int tile, hipStream_t stream) {
     switch (tile) {
-        case KSPLIT_16x16: return launch_ksplit_tile<16, 1, 1, 8, 4>(p, stream);
-        case KSPLIT_16x32: return launch_ksplit_tile<16, 1, 2, 8, 3>(p, stream);
-        case KSPLIT_32x32: return launch_ksplit_tile<32, 1, 1, 8, 2>(p, stream);
-        case KSPLIT_32x64: return launch_ksplit_tile<32, 1, 2, 6, 2>(p, stream);
+        case KSPLIT_16x16: return launch_ksplit_tile<16, 1, 1, 8, 4, RAGGED>(p, stream);
+        case KSPLIT_16x32: return launch_ksplit_tile<16, 1, 2, 8, 3, RAGGED>(p, stream);
+        case KSPLIT_32x32: return launch_ksplit_tile<32, 1, 1, 8, 2, RAGGED>(p, stream);
+        case KSPLIT_32x64: return launch_ksplit_tile<32, 1, 2, 6, 2, RAGGED>(p, stream);
         default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_igemm_ksplit(const IgemmParams& p, int tile, hipStream_t stream) {
+    if (p.total_tiles <= 0) return hipSuccess;
+    return (p.Cs & 63) == 0 ? launch_ksplit<false>(p, tile, stream) : launch_ksplit<true>(p, tile, stream);
 }
 
 void igemm_ksplit_tile_shape(int tile, int* bp, int* bc) {

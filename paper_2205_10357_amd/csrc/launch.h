@@ -93,6 +93,8 @@ hipError_t launch_smallc_fwd(const SmallCParams& p, hipStream_t stream);
 hipError_t launch_igemm(const IgemmParams& p, int tile, bool vec, bool mask, hipStream_t stream);
 void igemm_tile_shape(int tile, int* bp, int* bc);
 hipError_t launch_igemm_fast(const IgemmParams& p, int tile, int stages, hipStream_t stream);
+hipError_t launch_igemm_fast_ragged(const IgemmParams& p, int tile, int stages, hipStream_t stream);
+size_t igemm_chunk_table_bytes(const IgemmParams& p);
 void igemm_fast_tile_shape(int tile, int* bp, int* bc);
 enum WideTile { WIDE_128x128 = 0, WIDE_256x128, WIDE_128x256, WIDE_TILES };
 hipError_t launch_igemm_wide(const IgemmParams& p, int tile, hipStream_t stream);

@@ -8,9 +8,9 @@ namespace sol {
 
 constexpr int kPackTilePitch = 72;     // bf16 elements per LDS row (144 bytes, 16-byte aligned)
 
-// tiles of a weight tensor whose channel counts are multiples of 64
-inline bool pack_tiled_ok(const PackParams& p) { return (p.C_in & 63) == 0 && (p.C_out & 63) == 0; }
-inline int pack_tile_count(const PackParams& p) { return (int)(((long long)p.C_out * p.KH * p.KW * p.C_in) >> 12); }
+// tiles of a weight tensor whose channel counts are multiples of 8 (16-byte pieces); the last tiles may be partial
+inline bool pack_tiled_ok(const PackParams& p) { return (p.C_in & 7) == 0 && (p.C_out & 7) == 0; }
+inline int pack_tile_count(const PackParams& p) { return p.KH * p.KW * ((p.C_in + 63) >> 6) * ((p.C_out + 63) >> 6); }
 
 // out[class][ci][(jh*Tw + jw)*C_out + co] = bf16(scale[co] * W[co][kh][kw][ci]) for tile b = (tap, 64 co, 64 ci),
 // transposed through LDS (tile: 64 * kPackTilePitch elements) so that both the reads (ci contiguous) and the
@@ -18,7 +18,7 @@ inline int pack_tile_count(const PackParams& p) { return (int)(((long long)p.C_o
 __device__ __forceinline__ void pack_dgrad_weights_tile(const PackParams& p, int b, bf16_t* tile) {
     constexpr int PITCH = kPackTilePitch;
     const int tid = threadIdx.x;
-    const int tiles_ci = p.C_in >> 6, tiles_co = p.C_out >> 6;
+    const int tiles_ci = (p.C_in + 63) >> 6, tiles_co = (p.C_out + 63) >> 6;
     const int tci = b % tiles_ci;
     b /= tiles_ci;
     const int tco = b % tiles_co;
@@ -29,6 +29,7 @@ __device__ __forceinline__ void pack_dgrad_weights_tile(const PackParams& p, int
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int co = co0 + r0 + 32 * i;
+        if (co >= p.C_out || ci0 + c8 * 8 >= p.C_in) continue;
         const float sc = p.scale[co];
         const uintx4 v = *reinterpret_cast<const uintx4*>(p.W + (((long long)co * p.KH + kh) * p.KW + kw) * p.C_in +
                                                            ci0 + c8 * 8);
@@ -49,6 +50,7 @@ __device__ __forceinline__ void pack_dgrad_weights_tile(const PackParams& p, int
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int cil = r0 + 32 * i;
+        if (ci0 + cil >= p.C_in || co0 + c8 * 8 >= p.C_out) continue;
         const uintx4 v = *reinterpret_cast<const uintx4*>(&tile[cil * PITCH + c8 * 8]);
         *reinterpret_cast<uintx4*>(p.out + off + ((long long)(ci0 + cil) * Th * Tw + (jh * Tw + jw)) * p.C_out + co0 +
                                    c8 * 8) = v;

@@ -95,3 +95,27 @@ def test_fp32_matrix_kernels(shape):
     two = pu.gpu_block(case, addend=ad, addend_mask=am, two_calls=True)           # each branch as a launch of its own
     for key in ("dx", "dW", "dscale", "dshift"):
         assert np.array_equal(one[key], two[key]), key
+
+
+RAGGED_SHAPES = {
+    "8_channels_many_taps_per_slice": dict(N=2, H=9, W=7, C_in=8, C_out=16, K=5, stride=1, pad=2),
+    "56_channels_one_short_slice": dict(N=1, H=6, W=11, C_in=56, C_out=8, K=1, stride=1, pad=0, res=True),
+    "72_to_104_stride_2": dict(N=1, H=13, W=11, C_in=72, C_out=104, K=3, stride=2, pad=1),
+    "slices_19_and_a_fraction": dict(N=1, H=8, W=9, C_in=136, C_out=72, K=3, stride=1, pad=1),
+    "strided_1x1": dict(N=2, H=9, W=11, C_in=200, C_out=24, K=1, stride=2, pad=0, relu=False),
+    "rows_one_over_a_tile": dict(N=1, H=3, W=43, C_in=24, C_out=136, K=3, stride=1, pad=1),
+}
+
+
+@pytest.mark.parametrize("force", ["SOL_FAST_TILE=1,SOL_FAST_STAGES=2", "SOL_FAST_TILE=1,SOL_FAST_STAGES=4",
+                                   "SOL_FAST_TILE=2,SOL_FAST_STAGES=2", "SOL_FAST_TILE=2,SOL_FAST_STAGES=4",
+                                   "SOL_KSPLIT=1", "SOL_KSPLIT=2", "SOL_KSPLIT=3", "SOL_KSPLIT=4", "SOL_REDUCE_RIDES=1"])
+@pytest.mark.parametrize("shape", list(RAGGED_SHAPES), ids=list(RAGGED_SHAPES))
+def test_channels_that_are_no_multiple_of_64(shape, force, sol_env):
+    """Forward, data gradient and re-packed weights (riding with the weight gradient) of channel counts that are multiples
+    of 8 on every pipelined tile that serves them, and on the library's own choice."""
+    SHAPES[shape] = RAGGED_SHAPES[shape]
+    for setting in force.split(","):
+        name, value = setting.split("=")
+        sol_env(name, value)
+    run_forced(shape, name, value, sol_env)
