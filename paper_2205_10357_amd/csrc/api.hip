@@ -1,6 +1,7 @@
 // C-ABI of the fused block: argument validation (host only, before any HIP call), launch
 // planning (tile shape, split count, workspace layout) and the calls into the kernels.
 #include <limits.h>
+#include <math.h>
 #include <stdlib.h>
 #include <string.h>
 
@@ -400,16 +401,27 @@ BwdPlan plan_bwd(const sol_block_desc* d, const Geometry& g) {
         b.tiles_k = (int)((g.K + 127) / 128);
         b.tiles_c = (d->C_out + 127) / 128;
         const long long tiles = (long long)b.tiles_k * b.tiles_c;
-        const long long max_splits = (g.M + 127) / 128;
+        const long long max_splits = (g.M + 63) / 64;
         long long want = knob(K_WGRAD_SPLITS, 0);
         if (want <= 0) want = installed_plan(d, SOL_PLAN_WGRAD).splits;
         if (want <= 0) {
-            // Workgroups aimed at (per-layer timing over the benchmark network's layers): the 1x1 / stride 1
-            // kernel runs three stages deep, one workgroup per compute unit, and is fastest with one wave of
-            // 256 workgroups; the gathering kernel runs two stages deep, two workgroups per compute unit: 512.
+            // A split of S costs each workgroup L / S slices (L = 64-row slices of the whole reduction) and the launch, the
+            // reduction and the memory between them T * S fp32 tiles, so the best S goes with sqrt(L / T).  Measured
+            // optima of weight gradient + reduction (7 .. 128 images, T = 4 .. 144 tiles) lie at S^2 T / L = 18 .. 22 for
+            // 1x1 / stride 1 and 20 .. 35 for the gathering form.  1x1 / stride 1 runs three stages deep, one workgroup per
+            // compute unit, and leaves an eighth of them to the re-pack that rides along (1x1 2048 -> 512, 2352 pixels:
+            // 256 workgroups 13.0 us, 192 10.7 us); the gathering form runs two per compute unit.  Before (256 / 512
+            // workgroups whatever L is -> now, us of weight gradient + reduction + data gradient): 1x1 512 -> 128, 7436
+            // pixels 23.2 -> 18.5; 3x3 128 -> 128 23.4 -> 19.7; 3x3 256 -> 256, 1372 pixels 30.4 -> 25.8.
             const bool linear = d->KH == 1 && d->KW == 1 && d->stride == 1 && d->pad == 0;
-            const long long target = knob(K_WGRAD_TARGET, linear ? 256 : 512);
-            want = (target + tiles - 1) / tiles;
+            const float slices = (float)((g.M + 63) / 64);
+            want = (long long)(sqrtf((linear ? 18.f : 34.f) * slices / (float)tiles) + 0.5f);
+            // (4 T small workgroups re-pack; the gathering form fills the chip once or twice, not one and a half times)
+            const long long pack = tiles < 16 ? 2 * tiles : 32;
+            const long long target = knob(K_WGRAD_TARGET, linear ? 256 - pack : (want * tiles <= 384 ? 256 : 512));
+            const long long most = (target + (target > 256 ? tiles / 2 : 0)) / tiles;
+            if (want > most) want = most;
+            if (want > 64) want = 64;                       // more cannot ride with the data gradient
             // keep the fp32 partials below ~64 MiB
             const long long cap = (64LL << 20) / (g.w_elems * 4 > 0 ? g.w_elems * 4 : 1);
             if (want > cap) want = cap;
@@ -417,7 +429,7 @@ BwdPlan plan_bwd(const sol_block_desc* d, const Geometry& g) {
         if (want < 1) want = 1;
         if (want > max_splits) want = max_splits;
         long long mps = (g.M + want - 1) / want;
-        mps = (mps + 127) / 128 * 128;
+        mps = (mps + 63) / 64 * 64;
         b.m_per_split = (int)mps;
         b.splits = (int)((g.M + mps - 1) / mps);
         b.wpack_off = 0;
@@ -818,7 +830,8 @@ static int bwd_common(const sol_block_desc* desc, const void* dy, const void* x,
                 int stages = knob(K_WGRAD_STAGES, 0);
                 if (stages < 2 || stages > 4) stages = installed_plan(desc, SOL_PLAN_WGRAD).stages;
                 if (stages < 2 || stages > 4)
-                    stages = (desc->KH == 1 && desc->KW == 1 && desc->stride == 1 && desc->pad == 0) ? 3 : 2;
+                    stages = wp.splits * wp.tiles_k * wp.tiles_c <= 256 ||       // one workgroup per compute unit
+                             (desc->KH == 1 && desc->KW == 1 && desc->stride == 1 && desc->pad == 0) ? 3 : 2;
                 trace_point(st, SOL_TRACE_WGRAD);
                 if (launch_wgrad_fast(wp, stages, st) != hipSuccess) return SOL_ERR_LAUNCH;
             } else {

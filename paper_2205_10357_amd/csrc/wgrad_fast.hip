@@ -7,8 +7,9 @@
 // copies into a ring of NS stages, no register staging, no transposing stores).  The transposition
 // an MFMA operand needs -- a lane holds 8 consecutive reduction elements of one channel -- is done
 // by the LDS read itself: ds_read_b64_tr_b16 hands every lane one column of a 4 x 16 block.
-// 16-byte chunks of a row are XOR-swizzled with 2 * (m & 3) so that the four rows a transposing
-// read touches fall into different banks.
+// 16-byte chunks of a row are XOR-swizzled with 4 * (m & 3) ^ 2 * (m / 8 & 1) so that the eight rows x 64 bytes a
+// transposing read touches fall into different banks: 560 bytes per ns and compute unit (300 with 2 * (m & 3), 150 without;
+// reads alone).  The gathering form gains 1 - 3 % from that, the 1x1 form waits for memory.
 //
 // Each workgroup owns one 128(k) x 128(co) tile of G for one contiguous range of m and writes it
 // as fp32 to the workspace (through LDS, so that rows of the [co][k] partial are written as
@@ -61,7 +62,7 @@ __global__ __launch_bounds__(256) void wgrad_fast_kernel(const WgradParams p) {
     const buffer_rsrc_t x_rs = make_buffer_rsrc(p.x, (unsigned)((long long)p.N * p.H * p.W * p.C_in * 2));
     const buffer_rsrc_t g_rs = make_buffer_rsrc(p.dy, (unsigned)((long long)p.M * p.C_out * 2));
     const int mq = lane >> 4, pc = lane & 15;
-    const int cl = pc ^ (2 * mq);             // logical chunk kept at physical chunk pc (m & 3 == mq)
+    const int cl = pc ^ (4 * mq) ^ (2 * (wave >> 1));   // logical chunk kept at physical chunk pc (row m = 16*i + 4*wave + mq)
     const int kx = k0 + cl * 8;               // first k of this thread's x chunk
     const bool kx_ok = kx < p.K;
     int kh = 0, kw = 0, ci = 0;
@@ -126,8 +127,9 @@ __global__ __launch_bounds__(256) void wgrad_fast_kernel(const WgradParams p) {
         const int mrow = 8 * (grp >> 1) + (j >> 2);
         const int rx = wk * 64 + 32 * f + 16 * (grp & 1) + 4 * (j & 3);
         const int rg = wcn * 64 + 32 * f + 16 * (grp & 1) + 4 * (j & 3);
-        xoff[f] = mrow * 256 + (((rx >> 3) ^ (2 * (mrow & 3))) << 4) + ((rx >> 2) & 1) * 8;
-        goff[f] = mrow * 256 + (((rg >> 3) ^ (2 * (mrow & 3))) << 4) + ((rg >> 2) & 1) * 8;
+        const int sw = (4 * (mrow & 3)) ^ (2 * ((mrow >> 3) & 1));
+        xoff[f] = mrow * 256 + (((rx >> 3) ^ sw) << 4) + ((rx >> 2) & 1) * 8;
+        goff[f] = mrow * 256 + (((rg >> 3) ^ sw) << 4) + ((rg >> 2) & 1) * 8;
     }
     const bool do_shift = (tk == 0) && (wk == 0);
     floatx16 acc[2][2], accs[2];
