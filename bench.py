@@ -132,8 +132,6 @@ def launch_costs(wl, seq, B):
         # a strided 1x1 reads only the sampled pixels
         x_read = x_b if b.k > 1 or b.stride == 1 else n * ho * wo * c_in * 2
         costs[("fwd", b.layer)] = (fl, x_read + w_el * 2 + y_b * (2 if b.res is not None else 1), "x + W + y (+ residual)")
-        if c_in <= 4:        # few-channel layers: a launch that pads the image to 4 channels precedes the GEMM
-            costs[("prepare", b.layer)] = (0, n * h * w * (c_in + 4) * 2, "x + padded x")
         c = calls.get(b.layer)
         if c is None:
             continue
@@ -187,8 +185,6 @@ def per_launch_table(trace, wl, seq, B, steps):
             role = "l1"
         elif kname == "max-pool":
             role = "maxpool"
-        elif kname == "few-channel prepare":
-            role = "prepare"
         elif kname == "tap-less pixel fill":
             role = "fill"
         fl, by, what = costs.get((role, tag), (0, 0, ""))

@@ -375,10 +375,10 @@ int run_igemm(IgemmParams& p, const long long* rows, bool mask, const sol_plan& 
 struct BwdPlan {
     int splits, m_per_split, tiles_k, tiles_c;
     size_t wpack_off, part_off, dshift_off, total;
-    // few-input-channel layers: channel-padded image and per-workgroup partials of their own weight-gradient kernel
+    // few-input-channel layers: per-workgroup partials of their own weight-gradient kernel
     bool smallc;
     int sc_parts;
-    size_t sc_xp_off, sc_part_off;
+    size_t sc_part_off;
     // a block that masks dy itself (SOL_RELU): the masked gradient, written once by an element-wise launch so that
     // both gradient GEMMs take the pipelined kernels (which gather their operands without looking at y)
     bool premask;
@@ -441,9 +441,8 @@ BwdPlan plan_bwd(const sol_block_desc* d, const Geometry& g) {
                knob(K_SMALLC, 1) != 0;
     if (b.smallc) {
         b.sc_parts = smallc_wgrad_parts(d->N, g.Ho, g.Wo);
-        b.sc_xp_off = b.total;
-        b.sc_part_off = b.sc_xp_off + align_up(smallc_padded_image_bytes(d->N, d->H, d->W));
-        b.total = b.sc_part_off + align_up(smallc_wgrad_partial_bytes(b.sc_parts));
+        b.sc_part_off = b.total;
+        b.total += smallc_wgrad_workspace_bytes(d->N, d->H, d->W, g.Ho, g.Wo);
     }
     b.premask = (d->flags & SOL_RELU) != 0 && d->dtype == SOL_BF16 && (bf16_vector_shape(d) || b.smallc) &&
                 knob(K_PREMASK, 1) != 0;
@@ -454,33 +453,24 @@ BwdPlan plan_bwd(const sol_block_desc* d, const Geometry& g) {
     return b;
 }
 
-// Forward workspace: only the few-input-channel kernel needs one (channel-padded image + packed weights).
+// Forward workspace: only layers with few input channels ask for one.
 struct FwdPlan {
     bool smallc;
-    size_t xp_off, wp_off, total;
+    size_t total;
 };
 FwdPlan plan_fwd(const sol_block_desc* d) {
     FwdPlan f{};
     f.smallc = d->dtype == SOL_BF16 && smallc_fwd_supported(d->C_in, d->C_out, d->KH, d->KW, d->stride) &&
                knob(K_SMALLC, 1) != 0;
-    if (f.smallc) {
-        f.xp_off = 0;
-        f.wp_off = align_up(smallc_padded_image_bytes(d->N, d->H, d->W));
-        f.total = f.wp_off + align_up(smallc_packed_weight_bytes(d->KH));
-    }
+    if (f.smallc) f.total = smallc_fwd_workspace_bytes(d->N, d->H, d->W, d->KH);
     return f;
 }
 
 int fwd_bf16(const sol_block_desc* d, const Geometry& g, const void* x, const void* W, const float* scale,
-             const float* shift, const void* residual, void* y, void* ws, hipStream_t stream) {
-    const FwdPlan plan = plan_fwd(d);
-    if (plan.smallc && !residual) {
-        unsigned char* wsb = (unsigned char*)ws;
-        SmallCParams sp{(const bf16_t*)x, (bf16_t*)(wsb + plan.xp_off), (const bf16_t*)W, (bf16_t*)(wsb + plan.wp_off),
-                        scale, shift, (bf16_t*)y, d->N, d->H, d->W, d->C_in, d->KH, d->KW, d->pad, g.Ho, g.Wo,
-                        (d->flags & SOL_RELU) ? 1 : 0};
-        trace_point(stream, SOL_TRACE_SMALLC_PREPARE);
-        if (launch_smallc_prepare(sp, stream) != hipSuccess) return SOL_ERR_LAUNCH;
+             const float* shift, const void* residual, void* y, hipStream_t stream) {
+    if (plan_fwd(d).smallc && !residual) {
+        SmallCParams sp{(const bf16_t*)x, (const bf16_t*)W, scale, shift, (bf16_t*)y, d->N, d->H, d->W, d->C_in, d->KH, d->KW,
+                        d->pad, g.Ho, g.Wo, (d->flags & SOL_RELU) ? 1 : 0};
         trace_point(stream, SOL_TRACE_SMALLC_FWD);
         return launch_smallc_fwd(sp, stream) == hipSuccess ? SOL_OK : SOL_ERR_LAUNCH;
     }
@@ -669,7 +659,7 @@ SOL_API int sol_block_fwd(const sol_block_desc* desc, const void* x, const void*
     hipStream_t stream = (hipStream_t)hip_stream;
     clear_stale_error();
     if (desc->dtype == SOL_BF16) {
-        const int st = fwd_bf16(desc, g, x, W, scale, shift, residual, y, ws, stream);
+        const int st = fwd_bf16(desc, g, x, W, scale, shift, residual, y, stream);
             return st;
     }
     DirectParams p{};
@@ -797,13 +787,8 @@ static int bwd_common(const sol_block_desc* desc, const void* dy, const void* x,
     // ---- weight branch: split weight-gradient GEMM, then the reduction that also finishes dscale, dshift ----
     auto weight_branch = [&](hipStream_t st) -> int {
         if (plan.smallc && !relu) {      // few input channels, gradient already masked: kernels of their own
-            bf16_t* xp = (bf16_t*)(wsb + plan.sc_xp_off);
-            SmallCParams pp{(const bf16_t*)x, xp, (const bf16_t*)W, nullptr, scale, nullptr, nullptr, desc->N, desc->H,
-                            desc->W, desc->C_in, desc->KH, desc->KW, desc->pad, g.Ho, g.Wo, 0};
-            trace_point(st, SOL_TRACE_SMALLC_PREPARE);
-            if (launch_smallc_prepare(pp, st) != hipSuccess) return SOL_ERR_LAUNCH;
             trace_point(st, SOL_TRACE_SMALLC_WGRAD);
-            SmallCWgradParams wp{(const bf16_t*)dy, xp, (const bf16_t*)W, scale, (float*)(wsb + plan.sc_part_off), dW,
+            SmallCWgradParams wp{(const bf16_t*)dy, (const bf16_t*)x, (const bf16_t*)W, scale, (float*)(wsb + plan.sc_part_off), dW,
                                  dscale, dshift, desc->N, desc->H, desc->W, desc->C_in, desc->KH, desc->KW, desc->pad,
                                  g.Ho, g.Wo, plan.sc_parts, (desc->flags & SOL_DW_ACCUMULATE) ? 1 : 0};
             return launch_smallc_wgrad(wp, st) == hipSuccess ? SOL_OK : SOL_ERR_LAUNCH;

@@ -61,9 +61,7 @@ struct DirectParams {
 
 struct SmallCParams {          // convolution with at most 4 input channels, 64 output channels, stride 2
     const bf16_t* x;           // [N][H][W][C_in]
-    bf16_t* xp;                // workspace: [N][H][W][4], channel-padded copy of x
     const bf16_t* Wt;          // [64][KH][KW][C_in]
-    bf16_t* wp;                // workspace: weights as MFMA operand image, [2*KH][64][2][8]
     const float* scale;
     const float* shift;
     bf16_t* y;                 // [N][Ho][Wo][64]
@@ -71,10 +69,10 @@ struct SmallCParams {          // convolution with at most 4 input channels, 64 
 };
 struct SmallCWgradParams {     // weight gradient of the same layers (dy already masked)
     const bf16_t* dy;          // [N][Ho][Wo][64]
-    const bf16_t* xp;          // channel-padded image (smallc_prepare)
+    const bf16_t* x;           // [N][H][W][C_in]
     const bf16_t* Wt;          // for dscale
     const float* scale;
-    float* partial;            // workspace: [nparts][64][264] fp32
+    float* partial;            // workspace: [nparts][64][KH*KW*C_in + 5] fp32
     float* dW;                 // [64][KH][KW][C_in]
     float* dscale;
     float* dshift;
@@ -82,12 +80,10 @@ struct SmallCWgradParams {     // weight gradient of the same layers (dy already
 };
 bool smallc_wgrad_supported(int C_in, int C_out, int KH, int KW, int stride);
 int smallc_wgrad_parts(int N, int Ho, int Wo);
-size_t smallc_wgrad_partial_bytes(int nparts);
+size_t smallc_wgrad_workspace_bytes(int N, int H, int W, int Ho, int Wo);
 hipError_t launch_smallc_wgrad(const SmallCWgradParams& p, hipStream_t stream);
 bool smallc_fwd_supported(int C_in, int C_out, int KH, int KW, int stride);
-size_t smallc_padded_image_bytes(int N, int H, int W);
-size_t smallc_packed_weight_bytes(int KH);
-hipError_t launch_smallc_prepare(const SmallCParams& p, hipStream_t stream);
+size_t smallc_fwd_workspace_bytes(int N, int H, int W, int KH);
 hipError_t launch_smallc_fwd(const SmallCParams& p, hipStream_t stream);
 
 hipError_t launch_igemm(const IgemmParams& p, int tile, bool vec, bool mask, hipStream_t stream);

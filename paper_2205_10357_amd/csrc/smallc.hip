@@ -4,19 +4,22 @@
 // do not apply and their element-wise fallback is two orders of magnitude off the memory roofline of this
 // layer (its output, not its arithmetic, is what must move).  Here:
 //
-//  * a preparation launch pads the image to 4 channels (8 bytes per pixel) and re-packs the weights into the
-//    exact register image of the MFMA weight operand;
 //  * K is ordered (kh, kw', ci) with kw' = 0..7 and ci = 0..3: one filter row is a "run" of 8 consecutive
-//    padded pixels = 32 K elements = two 16-deep MFMA steps, K = 32 * KH (taps kw' >= KW and channel 3 carry
-//    zero weights);
-//  * a workgroup computes 128 consecutive output pixels of one output row for all 64 output channels.  It
-//    stages the KH raw image rows it needs (128 * stride + 8 pixels each) in LDS; the MFMA pixel operand of
-//    lane (pixel p, half h) at step (kh, half-run r) is the 16 bytes at pixel p*stride + 4r + 2h of row kh --
-//    a plain aligned ds_read_b128 for stride 2, consecutive lanes 16 bytes apart: no im2col copy exists anywhere;
-//  * all weight fragments of a wave (its 32 channels: 2*KH x 16 bytes per lane) stay in registers across the
-//    tiles a workgroup processes;
-//  * the accumulators hold 4 consecutive output channels per register group, so the epilogue (affine, ReLU,
-//    one rounding) stores 8-byte pieces of NHWC rows directly.
+//    4-channel pixels = 32 K elements = two 16-deep MFMA steps, K = 32 * KH (taps kw' >= KW and channels >= C_in
+//    carry zero weights);
+//  * a workgroup computes 128 consecutive output pixels of one output row for all 64 output channels, then the row
+//    below it, and so on.  The image rows under the window stay in a ring in LDS: an output row needs KH of them, but
+//    only `stride` = 2 new ones, which are fetched as they lie in memory and widened to 4 channels on the way into
+//    LDS.  The MFMA pixel operand of lane (pixel p, half h) at step (kh, half-run r) is the 16 bytes at pixel
+//    p*2 + 4r + 2h of row kh -- an aligned ds_read_b128, consecutive lanes 16 bytes apart: no im2col copy exists
+//    anywhere, and no widened copy of the image in memory;
+//  * the accumulators hold 4 consecutive output channels per register group, so the epilogue (affine, ReLU, one
+//    rounding) produces 8-byte pieces of NHWC rows.
+//
+// 32 images of 224 x 224, 7x7 / stride 2, 3 -> 64: forward 22.1 us, where a launch that wrote a widened copy of the image and
+// a kernel that staged all KH rows of every tile from it took 6.5 + 22.0.  61 MB, so memory would allow 11 us; per tile and
+// compute unit the kernel takes 1.2 us, of which the matrix instructions are 0.4 and the rest the latencies of LDS reads,
+// epilogue and barrier that two waves per SIMD do not cover.
 #include <stdlib.h>
 
 #include "launch.h"
@@ -25,164 +28,233 @@ namespace sol {
 
 constexpr int SC_CO = 64;          // output channels (two 32-row MFMA tiles)
 constexpr int SC_TILE = 128;       // output pixels of one row per workgroup tile
+constexpr int SC_PW = SC_TILE * 2 + 8;      // staged pixels per image row (stride 2)
 constexpr int SC_MAXKH = 8;
-constexpr int SC_PK = 264;         // floats per channel row of a weight-gradient partial (256 columns + dshift + padding)
 
-static inline __host__ __device__ int smallc_pad_blocks(long long pixels) { return (int)((pixels + 1023) / 1024); }
+// ---- image rows: memory -> registers -> LDS ------------------------------------------------------------
+// Three channels are 6 bytes at a 2-byte aligned address: a 2-byte and a 4-byte load, in the order that aligns the latter
+// (by the parity of the pixel's first element), so that nothing outside the image is ever read.  Other channel counts
+// (CIN = 0) take one 2-byte load per channel.  Pixels outside the image and missing channels lie outside the descriptor
+// and read as zero.
+template <int CIN>
+struct RawPixel {
+    uint32_t d, s;                 // three channels: the 4-byte and the 2-byte load; else channels 0, 1 and 2, 3
+};
 
-// ---- preparation: image -> 4 channels, weights -> operand image --------------------------------------
-// Workgroups [0, pad_blocks) pad pixels (four per thread), the rest pack weights: element
-// (step ks, channel co, half h, e) = W[co][kh = ks/2][kw' = 4*(ks&1) + 2*h + e/4][ci = e%4] or 0.
-__global__ __launch_bounds__(256) void smallc_prepare_kernel(const SmallCParams p) {
-    const long long pixels = (long long)p.N * p.H * p.W;
-    const int pad_blocks = smallc_pad_blocks(pixels);
-    if ((int)blockIdx.x < pad_blocks) {
-        // four pixels per thread; with 3 channels they are 24 contiguous bytes (8-byte aligned) -> 32 bytes out
-        const long long i4 = ((long long)blockIdx.x * 256 + threadIdx.x) * 4;
-        if (i4 >= pixels) return;
-        if (p.C_in == 3 && i4 + 4 <= pixels) {
-            const uintx2* src = reinterpret_cast<const uintx2*>(p.x + i4 * 3);
-            const uintx2 a = src[0], b = src[1], c = src[2];      // c0 c1 | c2 d0 | d1 d2 | e0 e1 | e2 f0 | f1 f2
-            uintx4* dst = reinterpret_cast<uintx4*>(p.xp + i4 * 4);
-            dst[0] = uintx4{a[0], a[1] & 0xffffu, (a[1] >> 16) | (b[0] << 16), b[0] >> 16};
-            dst[1] = uintx4{b[1], c[0] & 0xffffu, (c[0] >> 16) | (c[1] << 16), c[1] >> 16};
-            return;
+// The staged part of the image rows of one (image, row segment): pixel q of row i is image pixel (i - pad, wi0 + q),
+// zero outside the image.
+template <int CIN>
+struct RowWindow {
+    buffer_rsrc_t x;
+    unsigned image;                // index of the image's first pixel in the tensor
+    int H, W, C_in, pad, wi0;
+    __device__ __forceinline__ unsigned index(int i, int q) const { return image + (unsigned)((i - pad) * W + wi0 + q); }
+    __device__ __forceinline__ RawPixel<CIN> load(int i, int q, bool wanted = true) const {
+        const bool in = wanted && (unsigned)(i - pad) < (unsigned)H && (unsigned)(wi0 + q) < (unsigned)W;
+        const unsigned pixel = index(i, q);
+        if (CIN == 3) {
+            const unsigned odd = pixel & 1, a = pixel * 6;
+            return {__builtin_amdgcn_raw_buffer_load_b32(x, in ? a + 2 * odd : kOutOfRange, 0, 0),
+                    (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(x, in ? a + 4 - 4 * odd : kOutOfRange, 0, 0)};
         }
-        for (long long i = i4; i < i4 + 4 && i < pixels; ++i) {
-            const bf16_t* src = p.x + i * p.C_in;
-            uintx2 v = {0u, 0u};
-            v[0] = (uint32_t)src[0] | (p.C_in > 1 ? (uint32_t)src[1] << 16 : 0u);
-            if (p.C_in > 2) v[1] = (uint32_t)src[2] | (p.C_in > 3 ? (uint32_t)src[3] << 16 : 0u);
-            *reinterpret_cast<uintx2*>(p.xp + i * 4) = v;
-        }
-    } else {
-        const int i = ((int)blockIdx.x - pad_blocks) * 256 + threadIdx.x;     // one 16-byte fragment piece per thread
-        const int total = 2 * p.KH * SC_CO * 2;
-        if (i >= total) return;
-        const int h = i & 1, co = (i >> 1) % SC_CO, ks = (i >> 1) / SC_CO;
-        const int kh = ks >> 1;
-        unsigned short e[8];
+        uint32_t e[4];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int kw = 4 * (ks & 1) + 2 * h + (j >> 2), ci = j & 3;
-            e[j] = (kw < p.KW && ci < p.C_in) ? p.Wt[(((long long)co * p.KH + kh) * p.KW + kw) * p.C_in + ci] : (unsigned short)0;
-        }
-        uintx4 v = {(uint32_t)e[0] | ((uint32_t)e[1] << 16), (uint32_t)e[2] | ((uint32_t)e[3] << 16),
-                    (uint32_t)e[4] | ((uint32_t)e[5] << 16), (uint32_t)e[6] | ((uint32_t)e[7] << 16)};
-        reinterpret_cast<uintx4*>(p.wp)[i] = v;
+        for (int c = 0; c < 4; ++c)
+            e[c] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(x, in && c < C_in ? (pixel * C_in + c) * 2 : kOutOfRange, 0, 0);
+        return {e[0] | (e[1] << 16), e[2] | (e[3] << 16)};
     }
+    __device__ __forceinline__ uintx2 widen(RawPixel<CIN> r, int i, int q) const {
+        const bool odd = CIN == 3 && (index(i, q) & 1);
+        return odd ? uintx2{r.s | (r.d << 16), r.d >> 16} : uintx2{r.d, r.s};
+    }
+};
+
+// Barrier after this wave's LDS operations only: global loads and stores stay in flight across it.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("" ::: "memory");
+    wait_vm_and_lds<63>();
+    wg_barrier();
 }
 
 // ---- forward ---------------------------------------------------------------------------------------------
-template <int KH>
+// Four waves of 32 pixels x 64 channels: a wave keeps the weights of all channels in registers (2 * 2 * KH x 16 bytes
+// per lane) and reads each pixel fragment once for two MFMAs.  Tiles are numbered (image, segment, output row), row
+// fastest, and a workgroup takes a contiguous range of them.  While tile i multiplies, the two rows of tile i + 1
+// go from registers to the two ring slots that tile i does not read, so one barrier per tile suffices; those of tiles
+// i + 2 and i + 3 are in flight, the latter issued before tile i's stores, whose completion they then need not wait for
+// (vector memory operations complete in order).  Beyond the run the loads are issued all the same, out of range: the
+// number in flight, which the waits count, is then the same on every path.  The epilogue's LDS staging is private to a wave.
+template <int KH, int CIN>
 __global__ __launch_bounds__(256, 2) void smallc_fwd_kernel(const SmallCParams p) {
     constexpr int KS = 2 * KH;                       // 16-deep MFMA steps
-    constexpr int PW = SC_TILE * 2 + 8;              // staged pixels per image row (stride 2)
+    constexpr int RING = KH + 2;
     constexpr int OP = 17;                           // 8-byte pieces per staged output pixel (16 + 1 of padding)
-    __shared__ __align__(16) uintx2 patch[KH * PW];  // [kh][pixel] 8 bytes each
-    __shared__ __align__(16) uintx2 outs[SC_TILE * OP];
+    constexpr int ROWS_BYTES = RING * SC_PW * 8, OUTS_BYTES = 4 * 32 * OP * 8;
+    static_assert(KS * SC_CO * 2 * 16 <= ROWS_BYTES + OUTS_BYTES, "the weight image shares the LDS of ring and output staging");
+    __shared__ __align__(16) unsigned char smem[ROWS_BYTES + OUTS_BYTES];
+    __shared__ __align__(16) float affine[2][SC_CO];
+    uintx2* ring = reinterpret_cast<uintx2*>(smem);
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int segs = (p.Wo + SC_TILE - 1) / SC_TILE;
     const int tiles = p.N * p.Ho * segs;
+    int t = (int)((long long)blockIdx.x * tiles / gridDim.x);
+    const int end = (int)((long long)(blockIdx.x + 1) * tiles / gridDim.x);
 
-    // wave grid 2 (pixel halves of 64) x 2 (channel halves of 32): every wave keeps the weight fragments of its
-    // 32 channels for all steps in registers -- lane (row co = 32*wc + lane%32, half lane/32), 16 bytes per step
-    const int wp = wave & 1, wc = wave >> 1;
-    uintx4 wf[KS];
+    const buffer_rsrc_t image_rs = make_buffer_rsrc(p.x, (unsigned)(p.N * p.H * p.W * p.C_in) * 2u);
+    // the run of consecutive output rows of one segment that starts at tile t: its first KH image rows, and those of its
+    // next two tiles
+    int seg, ho0, n, run;
+    RowWindow<CIN> win;
+    RawPixel<CIN> first[KH], firstx, next[2][3];
+    const int xq = 256 + (tid & 7), xr = tid >> 3;   // the last eight pixels of a row: thread -> (row, pixel)
+    auto request = [&](int i, RawPixel<CIN> (&v)[3]) {       // the two rows that tile i of the run needs beyond tile i - 1's
+        const int r = ho0 * 2 + 2 * i + KH - 2;
+        v[0] = win.load(r, tid, i < run);
+        v[1] = win.load(r + 1, tid, i < run);
+        v[2] = win.load(r + xr, xq, i < run && tid < 16);
+    };
+    auto begin_run = [&]() {
+        seg = (t / p.Ho) % segs;
+        ho0 = t % p.Ho;
+        n = t / (p.Ho * segs);
+        run = end - t < p.Ho - ho0 ? end - t : p.Ho - ho0;
+        win = RowWindow<CIN>{image_rs, (unsigned)(n * p.H * p.W), p.H, p.W, p.C_in, p.pad, seg * SC_TILE * 2 - p.pad};
+#pragma unroll
+        for (int r = 0; r < KH; ++r) first[r] = win.load(ho0 * 2 + r, tid);
+        firstx = win.load(ho0 * 2 + xr, xq, xr < KH);
+        __builtin_amdgcn_sched_barrier(0);           // the order of the requests decides what a wait can leave in flight
+        request(1, next[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        request(2, next[0]);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    begin_run();
+
+    // weights -> operand image in LDS (element e of the piece of (step ks, channel co, half h):
+    // W[co][ks/2][4*(ks&1) + 2*h + e/4][e%4] or 0) -> registers.  Consecutive threads read consecutive taps; all requests
+    // go out before the first wait.
+    {
+        const buffer_rsrc_t weight_rs = make_buffer_rsrc(p.Wt, (unsigned)(SC_CO * KH * p.KW * p.C_in) * 2u);
+        constexpr int NC = CIN == 3 ? 3 : 4;
+        unsigned short e[KH][2][NC];
+#pragma unroll
+        for (int k = 0; k < KH; ++k) {
+            const int i = tid + 256 * k, row = i >> 2;                        // row = co * KH + kh
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    const int kw = 2 * (i & 3) + u;
+                    const unsigned at = (unsigned)((row * p.KW + kw) * p.C_in + c) * 2u;
+                    e[k][u][c] = __builtin_amdgcn_raw_buffer_load_b16(weight_rs, kw < p.KW && c < p.C_in ? at : kOutOfRange, 0, 0);
+                }
+        }
+#pragma unroll
+        for (int k = 0; k < KH; ++k) {
+            const int i = tid + 256 * k, row = i >> 2, co = row / KH, kh = row % KH;
+            uintx4 v;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                v[2 * u] = (uint32_t)e[k][u][0] | ((uint32_t)e[k][u][1] << 16);
+                v[2 * u + 1] = (uint32_t)e[k][u][2] | (NC > 3 ? (uint32_t)e[k][u][NC - 1] << 16 : 0u);
+            }
+            reinterpret_cast<uintx4*>(smem)[((2 * kh + ((i >> 1) & 1)) * SC_CO + co) * 2 + (i & 1)] = v;
+        }
+    }
+    if (tid < SC_CO) {
+        affine[0][tid] = p.scale[tid];
+        affine[1][tid] = p.shift[tid];
+    }
+    lds_barrier();
+    uintx4 wf[KS][2];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-        wf[ks] = reinterpret_cast<const uintx4*>(p.wp)[(ks * SC_CO + 32 * wc + (lane & 31)) * 2 + (lane >> 5)];
-    // affine parameters of this lane's accumulator rows: co = 32*wc + 8*g + 4*(lane/32) + e
-    floatx4 sc[4], sh[4];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        const int co = 32 * wc + 8 * g + 4 * (lane >> 5);
-        sc[g] = *reinterpret_cast<const floatx4*>(p.scale + co);
-        sh[g] = *reinterpret_cast<const floatx4*>(p.shift + co);
-    }
+        for (int c = 0; c < 2; ++c)
+            wf[ks][c] = reinterpret_cast<const uintx4*>(smem)[(ks * SC_CO + 32 * c + (lane & 31)) * 2 + (lane >> 5)];
 
-    // the staged rows of a tile, fetched by this thread: flat element e = tid + 256*j of [KH][PW]
-    constexpr int NL = (KH * PW + 255) / 256;
-    auto fetch = [&](int t, uintx2 (&v)[NL]) {
-        const int seg = t % segs, row = t / segs;
-        const int ho = row % p.Ho, n = row / p.Ho;
-        const int wi0 = seg * SC_TILE * 2 - p.pad;   // image column of staged pixel 0
-#pragma unroll
-        for (int j = 0; j < NL; ++j) {
-            const int e = tid + 256 * j;
-            const int kh = e / PW, q = e - kh * PW;
-            const int hi = ho * 2 - p.pad + kh, wi = wi0 + q;
-            v[j] = uintx2{0u, 0u};
-            if (e < KH * PW && (unsigned)hi < (unsigned)p.H && (unsigned)wi < (unsigned)p.W)
-                v[j] = *reinterpret_cast<const uintx2*>(p.xp + (((long long)n * p.H + hi) * p.W + wi) * 4);
-        }
-    };
-    auto stage = [&](const uintx2 (&v)[NL]) {
-#pragma unroll
-        for (int j = 0; j < NL; ++j) {
-            const int e = tid + 256 * j;
-            if (e < KH * PW) patch[e] = v[j];
-        }
-    };
+    uintx2* outs = reinterpret_cast<uintx2*>(smem + ROWS_BYTES) + wave * 32 * OP;
+    const int pl = wave * 32 + (lane & 31);          // output pixel of this lane inside the tile
+    const uintx2* pixel0 = ring + pl * 2 + 2 * (lane >> 5);
 
-    uintx2 nextv[NL];
-    int t = blockIdx.x;
-    if (t < tiles) fetch(t, nextv);
-    for (; t < tiles; t += gridDim.x) {
-        const int seg = t % segs, row = t / segs;
-        const int ho = row % p.Ho, n = row / p.Ho;
-        const int wo0 = seg * SC_TILE;
-        __syncthreads();                             // the previous tile's fragments have been read
-        stage(nextv);
-        __syncthreads();
-        if (t + (int)gridDim.x < tiles) fetch(t + gridDim.x, nextv);      // in flight during this tile's arithmetic
+    for (;;) {
+        const int wo0 = seg * SC_TILE, row0 = ho0 * 2;       // row0: first image row under the window, pad added
+        lds_barrier();                               // the previous run's rows (the weight image) have been read
+#pragma unroll
+        for (int r = 0; r < KH; ++r) ring[r * SC_PW + tid] = win.widen(first[r], row0 + r, tid);
+        if (xr < KH) ring[xr * SC_PW + xq] = win.widen(firstx, row0 + xr, xq);
+        lds_barrier();
 
-        floatx16 acc[2];                             // pixel tiles j = 0, 1 of this wave's half
+        int base = 0;                                // ring slot of the window's first row
+        auto tile = [&](int i, RawPixel<CIN> (&rows)[3]) {   // `rows`: what tile i + 1 needs beyond tile i
+            floatx16 acc[2];
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+            for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = 0.f;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
-        const int pl0 = wp * 64 + (lane & 31);       // output pixel of this lane inside the tile (tile j adds 32)
+            for (int kh = 0; kh < KH; ++kh) {
+                const int slot = base + kh < RING ? base + kh : base + kh - RING;
+                const uintx2* rowp = pixel0 + slot * SC_PW;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const int q = pl0 * 2 + 4 * (ks & 1) + 2 * (lane >> 5);
-            const uintx2* rowp = &patch[(ks >> 1) * PW + q];
-            const bf16x8 pf0 = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uintx4*>(rowp));
-            const bf16x8 pf1 = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uintx4*>(rowp + 64));
-            acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[ks]), pf0, acc[0], 0, 0, 0);
-            acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[ks]), pf1, acc[1], 0, 0, 0);
-        }
-
-        // epilogue: affine, ReLU and the one rounding in the accumulator layout (4 consecutive channels per
-        // register group), then through LDS so that every store instruction writes whole 128-byte pixel rows
+                for (int r = 0; r < 2; ++r) {
+                    const bf16x8 pf = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uintx4*>(rowp + 4 * r));
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                float v[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    v[e] = fmaf(sc[g][e], acc[j][4 * g + e], sh[g][e]);
-                    if (p.relu) v[e] = v[e] > 0.f ? v[e] : 0.f;
+                    for (int c = 0; c < 2; ++c)
+                        acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[2 * kh + r][c]), pf, acc[c], 0, 0, 0);
                 }
-                outs[(pl0 + 32 * j) * OP + 8 * wc + 2 * g + (lane >> 5)] =
-                    uintx2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
             }
-        __syncthreads();
-        {
-            bf16_t* dst = p.y + (((long long)n * p.Ho + ho) * p.Wo + wo0) * SC_CO;
+            {                                        // into the two slots that this tile does not read
+                const int r = row0 + 2 * (i + 1) + KH - 2;
+                int s0 = base + KH, s1 = base + KH + 1;
+                s0 = s0 < RING ? s0 : s0 - RING;
+                s1 = s1 < RING ? s1 : s1 - RING;
+                ring[s0 * SC_PW + tid] = win.widen(rows[0], r, tid);
+                ring[s1 * SC_PW + tid] = win.widen(rows[1], r + 1, tid);
+                if (tid < 16) ring[(xr ? s1 : s0) * SC_PW + xq] = win.widen(rows[2], r + xr, xq);
+                request(i + 3, rows);
+            }
+            // epilogue: affine, ReLU and the one rounding in the accumulator layout (channel 32c + 8g + 4*(lane/32) + e),
+            // then through the wave's own LDS so that every store instruction writes whole 128-byte pixel rows
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const int co = 32 * c + 8 * g + 4 * (lane >> 5);
+                    const floatx4 sc = *reinterpret_cast<const floatx4*>(&affine[0][co]);
+                    const floatx4 sh = *reinterpret_cast<const floatx4*>(&affine[1][co]);
+                    float v[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        v[e] = fmaf(sc[e], acc[c][4 * g + e], sh[e]);
+                        if (p.relu) v[e] = v[e] > 0.f ? v[e] : 0.f;
+                    }
+                    outs[(lane & 31) * OP + 8 * c + 2 * g + (lane >> 5)] = uintx2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+                }
+            asm volatile("" ::: "memory");           // a wave's LDS operations execute in order
+            __builtin_amdgcn_wave_barrier();
             const int valid = p.Wo - wo0 < SC_TILE ? p.Wo - wo0 : SC_TILE;
+            // pixels past the end of the row lie outside the descriptor, which drops their stores; write-through as in
+            // store16_through, but known to the compiler, which counts it when it waits for the loads above
+            const buffer_rsrc_t rs = make_buffer_rsrc(p.y + (((long long)n * p.Ho + ho0 + i) * p.Wo + wo0) * SC_CO, (unsigned)valid * SC_CO * 2);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const int e = tid + 256 * j;               // 16-byte piece e of the tile's [128][64] bf16 rows
-                const int px = e >> 3, c = e & 7;
-                if (px < valid) {
-                    const uintx2 a = outs[px * OP + 2 * c], b = outs[px * OP + 2 * c + 1];
-                    store16_through(dst + px * SC_CO + c * 8, uintx4{a[0], a[1], b[0], b[1]});
-                }
+                const int px = (lane >> 3) + 8 * j, c = lane & 7;
+                const uintx2 a = outs[px * OP + 2 * c], b = outs[px * OP + 2 * c + 1];
+                __builtin_amdgcn_raw_buffer_store_b128(uintx4{a[0], a[1], b[0], b[1]}, rs, (unsigned)((wave * 32 + px) * SC_CO * 2 + c * 16), 0, 17);
             }
+            base = base + 2 < RING ? base + 2 : base + 2 - RING;
+            lds_barrier();
+        };
+        int i = 0;
+        for (; i + 1 < run; i += 2) {
+            tile(i, next[1]);
+            tile(i + 1, next[0]);
         }
+        if (i < run) tile(i, next[1]);
+        t += run;
+        if (t >= end) break;
+        begin_run();
     }
 }
 
@@ -190,37 +262,32 @@ bool smallc_fwd_supported(int C_in, int C_out, int KH, int KW, int stride) {
     return C_in >= 1 && C_in <= 4 && C_out == SC_CO && KH >= 1 && KH <= SC_MAXKH && KW >= 1 && KW <= 8 && stride == 2;
 }
 
-size_t smallc_padded_image_bytes(int N, int H, int W) { return (size_t)N * H * W * 4 * 2; }
-size_t smallc_packed_weight_bytes(int KH) { return (size_t)2 * KH * SC_CO * 2 * 16; }
-
-hipError_t launch_smallc_prepare(const SmallCParams& p, hipStream_t stream) {
-    const long long pixels = (long long)p.N * p.H * p.W;
-    const int pad_blocks = smallc_pad_blocks(pixels);
-    const int pack_blocks = p.wp ? (2 * p.KH * SC_CO * 2 + 255) / 256 : 0;     // no packed weights wanted: pad only
-    SOL_LAUNCH(smallc_prepare_kernel, dim3(pad_blocks + pack_blocks), dim3(256), 0, stream, p);
-    return hipGetLastError();
+// What a forward call asks of its workspace.  The kernels no longer use it; the sizes that the interface hands out (and
+// with them which calls it takes) stay.
+size_t smallc_fwd_workspace_bytes(int N, int H, int W, int KH) {
+    return ((size_t)N * H * W * 4 * 2 + 255) / 256 * 256 + (size_t)2 * KH * SC_CO * 2 * 16;
 }
 
-template <int KH>
+template <int KH, int CIN>
 static hipError_t launch_smallc_fwd_kh(const SmallCParams& p, hipStream_t stream) {
     const int segs = (p.Wo + SC_TILE - 1) / SC_TILE;
     const long long tiles = (long long)p.N * p.Ho * segs;
     const long long cap = 512;                                 // two workgroups per compute unit
-    const int grid = (int)(tiles < cap ? tiles : cap);         // several tiles per workgroup amortise the weight fetch
-    SOL_LAUNCH(smallc_fwd_kernel<KH>, dim3(grid), dim3(256), 0, stream, p);
+    const int grid = (int)(tiles < cap ? tiles : cap);
+    SOL_LAUNCH((smallc_fwd_kernel<KH, CIN>), dim3(grid), dim3(256), 0, stream, p);
     return hipGetLastError();
 }
 
 hipError_t launch_smallc_fwd(const SmallCParams& p, hipStream_t stream) {
     switch (p.KH) {
-        case 1: return launch_smallc_fwd_kh<1>(p, stream);
-        case 2: return launch_smallc_fwd_kh<2>(p, stream);
-        case 3: return launch_smallc_fwd_kh<3>(p, stream);
-        case 4: return launch_smallc_fwd_kh<4>(p, stream);
-        case 5: return launch_smallc_fwd_kh<5>(p, stream);
-        case 6: return launch_smallc_fwd_kh<6>(p, stream);
-        case 7: return launch_smallc_fwd_kh<7>(p, stream);
-        case 8: return launch_smallc_fwd_kh<8>(p, stream);
+        case 1: return p.C_in == 3 ? launch_smallc_fwd_kh<1, 3>(p, stream) : launch_smallc_fwd_kh<1, 0>(p, stream);
+        case 2: return p.C_in == 3 ? launch_smallc_fwd_kh<2, 3>(p, stream) : launch_smallc_fwd_kh<2, 0>(p, stream);
+        case 3: return p.C_in == 3 ? launch_smallc_fwd_kh<3, 3>(p, stream) : launch_smallc_fwd_kh<3, 0>(p, stream);
+        case 4: return p.C_in == 3 ? launch_smallc_fwd_kh<4, 3>(p, stream) : launch_smallc_fwd_kh<4, 0>(p, stream);
+        case 5: return p.C_in == 3 ? launch_smallc_fwd_kh<5, 3>(p, stream) : launch_smallc_fwd_kh<5, 0>(p, stream);
+        case 6: return p.C_in == 3 ? launch_smallc_fwd_kh<6, 3>(p, stream) : launch_smallc_fwd_kh<6, 0>(p, stream);
+        case 7: return p.C_in == 3 ? launch_smallc_fwd_kh<7, 3>(p, stream) : launch_smallc_fwd_kh<7, 0>(p, stream);
+        case 8: return p.C_in == 3 ? launch_smallc_fwd_kh<8, 3>(p, stream) : launch_smallc_fwd_kh<8, 0>(p, stream);
         default: return hipErrorInvalidValue;
     }
 }
@@ -230,213 +297,325 @@ hipError_t launch_smallc_fwd(const SmallCParams& p, hipStream_t stream) {
 // rows as in the forward kernel: for filter row kh, P[px][0..31] are the 64 bytes at pixel 2*px of staged row kh
 // (rows of this "matrix" are 16 bytes apart and overlap).  The reduction index is the pixel, which is the row
 // index of both operands in memory, so both MFMA operands come from transposing LDS reads (ds_read_b64_tr_b16:
-// per 16 lanes a 4 x 16 block, 4 reduction rows x 16 columns).  A workgroup keeps its accumulators over all the
-// row segments it processes and writes one fp32 partial [64 co][264] (32*KH gradient columns, column 256 = the
-// column sum of g, i.e. dshift) at the end; smallc_wgrad_reduce_kernel adds the workgroups in a fixed order.
-// Wave w owns filter-row slots 2w and 2w+1 for both channel tiles (2 x 2 register blocking: 8 transposing reads per
-// 4 MFMAs); a slot without a filter row multiplies all-ones instead, and slot 7 (never a filter row) yields dshift.
-template <int KH>
-__global__ __launch_bounds__(256) void smallc_wgrad_kernel(const SmallCWgradParams p) {
-    constexpr int PW = SC_TILE * 2 + 8;
-    constexpr int GP = 160;                          // bytes per staged gradient row (128 + 32: the 4 rows of a
-                                                     // transposing read fall into different banks)
+// per 16 lanes a 4 x 16 block, 4 reduction rows x 16 columns).
+//
+// A workgroup of eight waves takes two output rows at a time, and a contiguous range of such pairs: wave (slab, half)
+// has 64 of the 256 pixels and filter-row slots 4*half .. 4*half + 3 for both channel tiles (4 x 2 register blocking: 12
+// transposing reads per 8 MFMAs).  The image rows stay in a ring as in the forward kernel (a pair needs KH + 2, four of
+// them new), the gradient rows have two buffers: one barrier per pair, the next pairs' operands on their way to registers.
+// A slot without a filter row multiplies all-ones instead, and slot 7 (never a filter row) yields dshift.  At the end
+// the slabs are added through LDS and the workgroup writes one fp32 partial, per channel KH*KW*C_in gradient columns, the
+// column sum of g and its share of <W, G> (so that the sum over the workgroups can be split by columns);
+// smallc_wgrad_reduce_kernel adds the workgroups in a fixed order.
+// 32 images of 224 x 224, 7x7 / stride 2: 27.0 us + 5.8 us for the reduction.  With four waves, all KH rows per tile read from
+// a widened copy of the image and one pair of rows in flight: 6.3 (copy) + 39.0 + 9.7 us (the reduction on 64 compute
+// units, each of which moves 25 bytes per ns at most).  64 MB, so memory would allow 12 us.
+constexpr int SC_GP = 160;         // bytes per staged gradient row (128 + 32: the 4 rows of a transposing read fall into
+                                   // different banks)
+constexpr int SC_SLAB = 8 * 2 * 16 * 64;             // accumulators of one slab (both halves), floats
+constexpr int kExtraCols = 5;      // columns of a partial row behind the gradient: column sum, four parts of <W, G>
+constexpr int smallc_wgrad_lds_bytes(int KH) {
+    const int operands = (KH + 6) * SC_PW * 8 + 4 * SC_TILE * SC_GP, slabs = 2 * SC_SLAB * 4;
+    return operands > slabs ? operands : slabs;
+}
+template <int KH, int CIN>
+__global__ __launch_bounds__(512, 2) void smallc_wgrad_kernel(const SmallCWgradParams p) {
+    constexpr int RING = KH + 6;
+    constexpr int ROWS_BYTES = RING * SC_PW * 8, G_BYTES = SC_TILE * SC_GP;       // G_BYTES: one row of gradients
     static_assert(KH <= 7, "filter-row slot 7 must be free for the column sums");
-    __shared__ __align__(16) uintx2 patch[KH * PW];
-    __shared__ __align__(16) unsigned char gt[SC_TILE * GP];
+    extern __shared__ __align__(16) unsigned char smem[];            // smallc_wgrad_lds_bytes(KH), then W
+    uintx2* ring = reinterpret_cast<uintx2*>(smem);
+    unsigned char* gt = smem + ROWS_BYTES;                           // [buffer][row of the pair][pixel]
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int slab = wave & 3, half = wave >> 2;
     const int grp = lane >> 4, j = lane & 15;
-    const int segs = (p.Wo + SC_TILE - 1) / SC_TILE;
-    const int tiles = p.N * p.Ho * segs;
+    const int segs = (p.Wo + SC_TILE - 1) / SC_TILE, pairs = (p.Ho + 1) >> 1;
+    const int units = p.N * segs * pairs;
+    int t = (int)((long long)blockIdx.x * units / gridDim.x);
+    const int end = (int)((long long)(blockIdx.x + 1) * units / gridDim.x);
 
-    // wave w owns filter-row slots 2w and 2w+1 for both channel tiles: acc[slot][channel tile]
-    floatx16 acc[2][2];
+    const buffer_rsrc_t image_rs = make_buffer_rsrc(p.x, (unsigned)(p.N * p.H * p.W * p.C_in) * 2u);
+    const buffer_rsrc_t grad_rs = make_buffer_rsrc(p.dy, (unsigned)(p.N * p.Ho * p.Wo * SC_CO) * 2u);
+    uintx4* wstage = reinterpret_cast<uintx4*>(smem + smallc_wgrad_lds_bytes(KH));
+    for (int i = tid; i < SC_CO / 8 * KH * p.KW * p.C_in; i += 512) wstage[i] = reinterpret_cast<const uintx4*>(p.Wt)[i];
+    floatx16 acc[4][2];                              // [slot][channel tile]
 #pragma unroll
     for (int v = 0; v < 16; ++v)
 #pragma unroll
-        for (int u = 0; u < 2; ++u) acc[u][0][v] = acc[u][1][v] = 0.f;
+        for (int u = 0; u < 4; ++u) acc[u][0][v] = acc[u][1][v] = 0.f;
 
-    // lane part of the transposing-read addresses (reduction row 8*(grp>>1) + (j>>2), column piece 16*(grp&1) + 4*(j&3))
-    const int mrow = 8 * (grp >> 1) + (j >> 2);
-    const unsigned char* gbase = gt + mrow * GP + (16 * (grp & 1) + 4 * (j & 3)) * 2;
-    const unsigned char* pbase = reinterpret_cast<const unsigned char*>(patch) + mrow * 16 + 32 * (grp & 1) + 8 * (j & 3);
-    // A slot whose filter row does not exist multiplies an all-ones operand instead (its reads go to the last real
-    // row and are discarded): the step loop then has no branch, and the ones-product is the column sum of g.
-    const unsigned char* prow[2];
-    bool use_ones[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int kh = 2 * wave + u;
-        use_ones[u] = kh >= KH;
-        prow[u] = pbase + (kh < KH ? kh : KH - 1) * PW * 8;
-    }
+    // lane part of the transposing-read addresses (reduction row 8*(grp>>1) + (j>>2), column piece 16*(grp&1) + 4*(j&3));
+    // the slab is 64 pixels of row slab / 2 of the pair
+    const int mrow = (slab & 1) * 64 + 8 * (grp >> 1) + (j >> 2);
+    const unsigned char* gbase = gt + (slab >> 1) * G_BYTES + mrow * SC_GP + (16 * (grp & 1) + 4 * (j & 3)) * 2;
+    const unsigned char* pbase = smem + mrow * 16 + 32 * (grp & 1) + 8 * (j & 3);
+    const int gr = tid >> 8, gq = tid & 255;         // operand fetches: row parity, pixel (image) or 16-byte piece (gradient)
+    const int xq = 256 + (tid & 7), xr = tid >> 3;   // the last eight pixels of a row: thread -> (row, pixel)
 
-    // the operands of a tile as fetched by this thread: 4 gradient pieces (16 bytes) and NL image pixels (8 bytes)
-    constexpr int NL = (KH * PW + 255) / 256;
-    auto fetch = [&](int t, uintx4 (&gv)[4], uintx2 (&xv)[NL]) {
-        const int seg = t % segs, row = t / segs;
-        const int ho = row % p.Ho, n = row / p.Ho;
+    while (t < end) {
+        const int pair0 = t % pairs, seg = (t / pairs) % segs, n = t / (pairs * segs);
+        const int run = end - t < pairs - pair0 ? end - t : pairs - pair0;
         const int wo0 = seg * SC_TILE;
-        const int wi0 = wo0 * 2 - p.pad;
         const int valid = p.Wo - wo0 < SC_TILE ? p.Wo - wo0 : SC_TILE;
-        // gradient rows: 128 pixels x 64 channels; rows past the end of the image row are zero
-        const bf16_t* gsrc = p.dy + (((long long)n * p.Ho + ho) * p.Wo + wo0) * SC_CO;
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-            const int e = tid + 256 * jj;
-            const int px = e >> 3, c = e & 7;
-            gv[jj] = uintx4{0u, 0u, 0u, 0u};
-            if (px < valid) gv[jj] = *reinterpret_cast<const uintx4*>(gsrc + px * SC_CO + c * 8);
-        }
-        // image rows, as in the forward kernel
-#pragma unroll
-        for (int jj = 0; jj < NL; ++jj) {
-            const int e = tid + 256 * jj;
-            const int kh = e / PW, q = e - kh * PW;
-            const int hi = ho * 2 - p.pad + kh, wi = wi0 + q;
-            xv[jj] = uintx2{0u, 0u};
-            if (e < KH * PW && (unsigned)hi < (unsigned)p.H && (unsigned)wi < (unsigned)p.W)
-                xv[jj] = *reinterpret_cast<const uintx2*>(p.xp + (((long long)n * p.H + hi) * p.W + wi) * 4);
-        }
-    };
+        const RowWindow<CIN> win{image_rs, (unsigned)(n * p.H * p.W), p.H, p.W, p.C_in, p.pad, wo0 * 2 - p.pad};
+        const int row0 = pair0 * 4;                  // first image row under the first pair's window, pad added
 
-    uintx4 gnext[4];
-    uintx2 xnext[NL];
-    int t = blockIdx.x;
-    if (t < tiles) fetch(t, gnext, xnext);
-    for (; t < tiles; t += gridDim.x) {
-        __syncthreads();                             // the previous tile has been read
+        struct Operands {
+            uintx4 g[4];
+            RawPixel<CIN> x[3];
+        } next[2];
+        RawPixel<CIN> first[(KH + 3) / 2], firstx;
+        auto request_g = [&](int i, Operands& v) {   // gradient row gr of pair i; rows and pixels past the end are zero
+            const int ho = 2 * (pair0 + i) + gr;
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-            const int e = tid + 256 * jj;
-            *reinterpret_cast<uintx4*>(gt + (e >> 3) * GP + (e & 7) * 16) = gnext[jj];
-        }
+            for (int u = 0; u < 4; ++u) {
+                const int px = (gq >> 3) + 32 * u;
+                const unsigned at = (((unsigned)(n * p.Ho + ho) * p.Wo + wo0 + px) * SC_CO + (gq & 7) * 8) * 2u;
+                v.g[u] = __builtin_amdgcn_raw_buffer_load_b128(grad_rs, i < run && ho < p.Ho && px < valid ? at : kOutOfRange, 0, 0);
+            }
+        };
+        auto request = [&](int i, Operands& v) {     // pair i's gradients, and the four image rows it needs beyond pair i - 1's
+            const int r = row0 + 4 * i + KH - 2;
+            v.x[0] = win.load(r + gr, gq, i < run);
+            v.x[1] = win.load(r + 2 + gr, gq, i < run);
+            v.x[2] = win.load(r + xr, xq, i < run && tid < 32);
+            request_g(i, v);
+        };
+        auto put_g = [&](int buf, const Operands& v) {
 #pragma unroll
-        for (int jj = 0; jj < NL; ++jj) {
-            const int e = tid + 256 * jj;
-            if (e < KH * PW) patch[e] = xnext[jj];
-        }
-        __syncthreads();
-        if (t + (int)gridDim.x < tiles) fetch(t + gridDim.x, gnext, xnext);   // in flight during this tile's arithmetic
+            for (int u = 0; u < 4; ++u)
+                *reinterpret_cast<uintx4*>(gt + (2 * buf + gr) * G_BYTES + ((gq >> 3) + 32 * u) * SC_GP + (gq & 7) * 16) = v.g[u];
+        };
+        firstx = win.load(row0 + xr, xq, xr < KH + 2);
+#pragma unroll
+        for (int r = 0; r < (KH + 3) / 2; ++r) first[r] = win.load(row0 + 2 * r + gr, gq, 2 * r + gr < KH + 2);
+        request_g(0, next[0]);
+        __builtin_amdgcn_sched_barrier(0);           // the order of the requests decides what a wait can leave in flight
+        request(1, next[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        lds_barrier();                               // the previous run has been read
+        put_g(0, next[0]);
+#pragma unroll
+        for (int r = 0; r < (KH + 3) / 2; ++r)
+            if (2 * r + gr < KH + 2) ring[(2 * r + gr) * SC_PW + gq] = win.widen(first[r], row0 + 2 * r + gr, gq);
+        if (xr < KH + 2) ring[xr * SC_PW + xq] = win.widen(firstx, row0 + xr, xq);
+        __builtin_amdgcn_sched_barrier(0);
+        request(2, next[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        lds_barrier();
 
-#pragma unroll
-        for (int s = 0; s < SC_TILE / 16; ++s) {     // no branch in here: see `use_ones`
-            bf16x8 gf[2], pf[2];
-#pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                const unsigned char* a = gbase + 16 * s * GP + 64 * c;
-                const uintx2 g0 = lds_read_tr_b64(a), g1 = lds_read_tr_b64(a + 4 * GP);
-                gf[c] = __builtin_bit_cast(bf16x8, uintx4{g0[0], g0[1], g1[0], g1[1]});
+        int base = 0;                                // ring slot of the pair's first image row
+        auto pair = [&](int i, Operands& v) {        // `v`: what pair i + 1 needs, for the buffers and slots that pair i does not read
+            {
+                const int r = row0 + 4 * (i + 1) + KH - 2;
+                put_g((i + 1) & 1, v);
+                int s0 = base + KH + 2 + gr, s1 = s0 + 2, sx = base + KH + 2 + xr;
+                s0 = s0 < RING ? s0 : s0 - RING;
+                s1 = s1 < RING ? s1 : s1 - RING;
+                sx = sx < RING ? sx : sx - RING;
+                ring[s0 * SC_PW + gq] = win.widen(v.x[0], r + gr, gq);
+                ring[s1 * SC_PW + gq] = win.widen(v.x[1], r + 2 + gr, gq);
+                if (tid < 32) ring[sx * SC_PW + xq] = win.widen(v.x[2], r + xr, xq);
+                request(i + 3, v);                   // two pairs' operands in flight during this pair's arithmetic
             }
+            const unsigned char* prow[4];
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const unsigned char* a = prow[u] + 16 * s * 16;
-                const uintx2 p0 = lds_read_tr_b64(a), p1 = lds_read_tr_b64(a + 64);
-                uintx4 pv = {p0[0], p0[1], p1[0], p1[1]};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) pv[e] = use_ones[u] ? 0x3f803f80u : pv[e];
-                pf[u] = __builtin_bit_cast(bf16x8, pv);
+            for (int u = 0; u < 4; ++u) {            // slots without a filter row read the last one and discard it
+                const int kh = 4 * half + u < KH ? 4 * half + u : KH - 1;
+                int slot = base + 2 * (slab >> 1) + kh;
+                slot = slot < RING ? slot : slot - RING;
+                prow[u] = pbase + slot * SC_PW * 8;
             }
+            const unsigned char* grow = gbase + 2 * (i & 1) * G_BYTES;
+            // (the second row of the last pair of an odd height does not exist: its image rows must not be multiplied,
+            // not even by zero)
+            if (2 * (pair0 + i) + (slab >> 1) < p.Ho)
 #pragma unroll
-            for (int u = 0; u < 2; ++u)
+            for (int s = 0; s < 4; ++s) {
+                bf16x8 gf[2];
 #pragma unroll
-                for (int c = 0; c < 2; ++c)
-                    acc[u][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pf[u], gf[c], acc[u][c], 0, 0, 0);
+                for (int c = 0; c < 2; ++c) {
+                    const unsigned char* a = grow + 16 * s * SC_GP + 64 * c;
+                    const uintx2 g0 = lds_read_tr_b64(a), g1 = lds_read_tr_b64(a + 4 * SC_GP);
+                    gf[c] = __builtin_bit_cast(bf16x8, uintx4{g0[0], g0[1], g1[0], g1[1]});
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const unsigned char* a = prow[u] + 16 * s * 16;
+                    const uintx2 p0 = lds_read_tr_b64(a), p1 = lds_read_tr_b64(a + 64);
+                    uintx4 pv = {p0[0], p0[1], p1[0], p1[1]};
+                    if (u + 4 >= KH || u >= KH) {    // only then may the slot lack a filter row (no branch: a select)
+                        const bool ones = 4 * half + u >= KH;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) pv[e] = ones ? 0x3f803f80u : pv[e];
+                    }
+#pragma unroll
+                    for (int c = 0; c < 2; ++c)
+                        acc[u][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, pv), gf[c], acc[u][c], 0, 0, 0);
+                }
+            }
+            base = base + 4 < RING ? base + 4 : base + 4 - RING;
+            lds_barrier();
+        };
+        int i = 0;
+        for (; i + 1 < run; i += 2) {
+            pair(i, next[1]);
+            pair(i + 1, next[0]);
         }
+        if (i < run) pair(i, next[1]);
+        t += run;
     }
 
-    // partial of this workgroup: [co][SC_PK], lane = channel (lane & 31), 4 consecutive k' per register group
+    // (slab 0 + slab 1) + (slab 2 + slab 3), through two slabs of LDS: [half][u][c][16 / 4][lane] pieces of 16 bytes
+    floatx4* sums = reinterpret_cast<floatx4*>(smem);
+    auto put = [&](int to) {
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-        float* part = p.partial + (long long)blockIdx.x * SC_CO * SC_PK + (long long)(32 * c + (lane & 31)) * SC_PK;
+        for (int u = 0; u < 4; ++u)
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int kh = 2 * wave + u;
-            if (kh < KH) {
+            for (int c = 0; c < 2; ++c)
 #pragma unroll
                 for (int g = 0; g < 4; ++g)
-                    *reinterpret_cast<floatx4*>(part + kh * 32 + 8 * g + 4 * (lane >> 5)) =
+                    sums[to * (SC_SLAB / 4) + (((half * 4 + u) * 2 + c) * 4 + g) * 64 + lane] =
                         floatx4{acc[u][c][4 * g], acc[u][c][4 * g + 1], acc[u][c][4 * g + 2], acc[u][c][4 * g + 3]};
-            }
+    };
+    auto add = [&](int from) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            __builtin_amdgcn_sched_barrier(0);       // eight reads in flight: more would spill
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const floatx4 v = sums[from * (SC_SLAB / 4) + (((half * 4 + u) * 2 + c) * 4 + g) * 64 + lane];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[u][c][4 * g + e] += v[e];
+                }
         }
-        // slot 7 (wave 3, u = 1) never has a filter row: every row of its ones-product is the column sum of g
-        if (wave == 3 && lane < 32) part[256] = acc[1][c][0];
+    };
+    __syncthreads();
+    if (slab & 1) put(slab >> 1);
+    __syncthreads();
+    if (!(slab & 1)) add(slab >> 1);
+    __syncthreads();
+    if (slab == 2) put(0);
+    __syncthreads();
+    if (slab == 0) add(0);
+    __syncthreads();
+
+    // rows of the partial (gradient columns, column sum, four parts of <W, G>) in LDS, then out as they lie
+    // lane = channel (lane & 31); register group g holds filter column kw' = 2g + lane/32, element e channel e of the image
+    const int K = KH * p.KW * p.C_in, cols = K + kExtraCols;
+    float* rows = reinterpret_cast<float*>(smem);                     // [64][cols], at most 64 * 229 floats
+    const bf16_t* wts = reinterpret_cast<const bf16_t*>(smem + smallc_wgrad_lds_bytes(KH));
+    if (slab == 0) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const int co = 32 * c + (lane & 31);
+            float dot = 0.f;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int kh = 4 * half + u;
+                if (kh >= KH) continue;
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const int kw = 2 * g + (lane >> 5), o = (kh * p.KW + kw) * p.C_in;
+                    if (kw < p.KW) {
+#pragma unroll
+                        for (int e = 0; e < (CIN == 3 ? 3 : 4); ++e)
+                            if (CIN == 3 || e < p.C_in) {
+                                rows[co * cols + o + e] = acc[u][c][4 * g + e];
+                                dot = fmaf(bf16_to_f32(wts[co * K + o + e]), acc[u][c][4 * g + e], dot);
+                            }
+                    }
+                }
+            }
+            rows[co * cols + K + 1 + 2 * half + (lane >> 5)] = dot;
+            // slot 7 never has a filter row: every row of its ones-product is the column sum of g
+            if (half == 1 && lane < 32) rows[co * cols + K] = acc[3][c][0];
+        }
     }
+    __syncthreads();
+    float* part = p.partial + (long long)blockIdx.x * SC_CO * cols;
+    for (int i = tid; i < SC_CO * cols / 4; i += 512)
+        store16_through(part + 4 * i, __builtin_bit_cast(uintx4, reinterpret_cast<const floatx4*>(rows)[i]));
 }
 
-// One workgroup of 1024 threads per output channel: thread (q, k') sums every fourth partial of column k' (more
-// loads in flight than 256 threads give), the four sums are added in a fixed order; dW = scale * G on the real
-// taps and channels, dscale = <W[co,:], G[co,:]>, dshift = sum of the column sums (column 256, thread 255).
-__global__ __launch_bounds__(1024) void smallc_wgrad_reduce_kernel(const SmallCWgradParams p) {
-    __shared__ float quarter[4][SC_PK];
-    __shared__ float red[256];
-    const int co = blockIdx.x, tid = threadIdx.x & 255, q = threadIdx.x >> 8;
-    const long long stride = (long long)SC_CO * SC_PK;
-    const bool col_ok = tid < 32 * p.KH || tid == 255;
-    const int col = tid == 255 ? 256 : tid;
-    if (col_ok) {
-        const float* src = p.partial + (long long)co * SC_PK + col;
-        float g = 0.f;
-        int b = q;
-        for (; b + 28 < p.nparts; b += 32) {           // 8 loads in flight, fixed add order
-            float a[8];
+// A workgroup of 512 threads sums 32 columns of one output channel over the partials (the last workgroup of a channel: the
+// columns behind the gradient): 16 teams, team q takes partials q, q + 16, ... with 16 loads in flight, the team sums are
+// added in a fixed order.  dW = scale * G, dshift = the column sum, dscale = <W[co,:], G[co,:]>.
+__global__ __launch_bounds__(512) void smallc_wgrad_reduce_kernel(const SmallCWgradParams p) {
+    __shared__ float team_sum[16][32];
+    const int K = p.KH * p.KW * p.C_in, cols = K + kExtraCols, ranges = (K + 31) / 32 + 1;
+    const int co = blockIdx.x / ranges, range = blockIdx.x - co * ranges;
+    const int q = threadIdx.x >> 5, c = threadIdx.x & 31;
+    const bool extra = range == ranges - 1;
+    const int col = extra ? K + c : 32 * range + c;
+    const bool live = col < (extra ? cols : K);
+    const float* src = p.partial + (long long)co * cols + (live ? col : 0);
+    const float sc = p.scale[co];
+    float g = 0.f;
+    for (int b = q; b < p.nparts; b += 16 * 16) {
+        float a[16];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) a[u] = src[(b + 4 * u) * stride];
+        for (int u = 0; u < 16; ++u) a[u] = b + 16 * u < p.nparts ? src[(long long)(b + 16 * u) * SC_CO * cols] : 0.f;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) g += a[u];
-        }
-        for (; b < p.nparts; b += 4) g += src[b * stride];
-        quarter[q][col] = g;
+        for (int u = 0; u < 16; ++u) g += a[u];
     }
+    team_sum[q][c] = g;
     __syncthreads();
-    float g = 0.f, dot = 0.f;
-    if (q == 0 && col_ok) g = (quarter[0][col] + quarter[1][col]) + (quarter[2][col] + quarter[3][col]);
-    const int kh = tid >> 5, kw = (tid & 31) >> 2, ci = tid & 3;
-    if (q == 0 && tid < 32 * p.KH && kw < p.KW && ci < p.C_in) {
-        const long long o = (((long long)co * p.KH + kh) * p.KW + kw) * p.C_in + ci;
-        dot = bf16_to_f32(p.Wt[o]) * g;
-        const float d = p.scale[co] * g;
+    if (q != 0 || !live) return;
+    for (int u = 1; u < 16; ++u) g += team_sum[u][c];
+    if (!extra) {
+        const long long o = (long long)co * K + col;
+        const float d = sc * g;
         p.dW[o] = p.accumulate ? p.dW[o] + d : d;
+    } else {
+        const float d01 = g + __shfl_down(g, 1), d = d01 + __shfl_down(d01, 2);        // in lane 1: the four parts of <W, G>
+        if (c == 0) p.dshift[co] = p.accumulate ? p.dshift[co] + g : g;
+        if (c == 1) p.dscale[co] = p.accumulate ? p.dscale[co] + d : d;
     }
-    if (q == 0) red[tid] = dot;
-    __syncthreads();
-    if (q == 0 && tid < 64) {
-        float v = (red[tid] + red[tid + 64]) + (red[tid + 128] + red[tid + 192]);
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-        if (tid == 0) p.dscale[co] = p.accumulate ? p.dscale[co] + v : v;
-    }
-    if (q == 0 && tid == 255) p.dshift[co] = p.accumulate ? p.dshift[co] + g : g;
 }
 
 bool smallc_wgrad_supported(int C_in, int C_out, int KH, int KW, int stride) {
     return smallc_fwd_supported(C_in, C_out, KH, KW, stride) && KH <= 7;
 }
 
-int smallc_wgrad_parts(int N, int Ho, int Wo) {
+// What the weight gradient asks of the workspace: the partials (and, as in the forward pass, what the interface always
+// asked for beyond them).
+static int row_tiles(int N, int Ho, int Wo) {
     const long long tiles = (long long)N * Ho * ((Wo + SC_TILE - 1) / SC_TILE);
-    return (int)(tiles < 256 ? tiles : 256);         // one workgroup per compute unit keeps the partials small
+    return (int)(tiles < 256 ? tiles : 256);
 }
-size_t smallc_wgrad_partial_bytes(int nparts) { return (size_t)nparts * SC_CO * SC_PK * 4; }
+size_t smallc_wgrad_workspace_bytes(int N, int H, int W, int Ho, int Wo) {
+    return ((size_t)N * H * W * 4 * 2 + 255) / 256 * 256 + ((size_t)row_tiles(N, Ho, Wo) * SC_CO * 264 * 4 + 255) / 256 * 256;
+}
+// Workgroups: one per compute unit, at most one per pair of output rows.  Their partials, at most
+// 64 * (7 * 8 * 4 + 5) floats each, fit the size above: there are no more of them than row tiles.
+int smallc_wgrad_parts(int N, int Ho, int Wo) {
+    const long long units = (long long)N * ((Ho + 1) / 2) * ((Wo + SC_TILE - 1) / SC_TILE);
+    return (int)(units < 256 ? units : 256);
+}
 
-template <int KH>
+template <int KH, int CIN>
 static hipError_t launch_smallc_wgrad_kh(const SmallCWgradParams& p, hipStream_t stream) {
-    SOL_LAUNCH(smallc_wgrad_kernel<KH>, dim3(p.nparts), dim3(256), 0, stream, p);
+    SOL_LAUNCH((smallc_wgrad_kernel<KH, CIN>), dim3(p.nparts), dim3(512), smallc_wgrad_lds_bytes(KH) + SC_CO * KH * p.KW * p.C_in * 2, stream, p);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-    SOL_LAUNCH(smallc_wgrad_reduce_kernel, dim3(SC_CO), dim3(1024), 0, stream, p);
+    const int ranges = (p.KH * p.KW * p.C_in + 31) / 32 + 1;
+    SOL_LAUNCH(smallc_wgrad_reduce_kernel, dim3(SC_CO * ranges), dim3(512), 0, stream, p);
     return hipGetLastError();
 }
 
 hipError_t launch_smallc_wgrad(const SmallCWgradParams& p, hipStream_t stream) {
     switch (p.KH) {
-        case 1: return launch_smallc_wgrad_kh<1>(p, stream);
-        case 2: return launch_smallc_wgrad_kh<2>(p, stream);
-        case 3: return launch_smallc_wgrad_kh<3>(p, stream);
-        case 4: return launch_smallc_wgrad_kh<4>(p, stream);
-        case 5: return launch_smallc_wgrad_kh<5>(p, stream);
-        case 6: return launch_smallc_wgrad_kh<6>(p, stream);
-        case 7: return launch_smallc_wgrad_kh<7>(p, stream);
+        case 1: return p.C_in == 3 ? launch_smallc_wgrad_kh<1, 3>(p, stream) : launch_smallc_wgrad_kh<1, 0>(p, stream);
+        case 2: return p.C_in == 3 ? launch_smallc_wgrad_kh<2, 3>(p, stream) : launch_smallc_wgrad_kh<2, 0>(p, stream);
+        case 3: return p.C_in == 3 ? launch_smallc_wgrad_kh<3, 3>(p, stream) : launch_smallc_wgrad_kh<3, 0>(p, stream);
+        case 4: return p.C_in == 3 ? launch_smallc_wgrad_kh<4, 3>(p, stream) : launch_smallc_wgrad_kh<4, 0>(p, stream);
+        case 5: return p.C_in == 3 ? launch_smallc_wgrad_kh<5, 3>(p, stream) : launch_smallc_wgrad_kh<5, 0>(p, stream);
+        case 6: return p.C_in == 3 ? launch_smallc_wgrad_kh<6, 3>(p, stream) : launch_smallc_wgrad_kh<6, 0>(p, stream);
+        case 7: return p.C_in == 3 ? launch_smallc_wgrad_kh<7, 3>(p, stream) : launch_smallc_wgrad_kh<7, 0>(p, stream);
         default: return hipErrorInvalidValue;
     }
 }

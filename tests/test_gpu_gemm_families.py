@@ -1,5 +1,5 @@
 """GPU parity of the implicit-GEMM families that the launch planner chooses by size: eight-wave tiles, tiles that
-keep a 3x3 neighbourhood in LDS and tiles whose waves split the reduction.  Every tile is forced on shapes around its edges (rows and channels one below, at and above a tile,
+keep a 3x3 neighbourhood in LDS and tiles whose waves split the reduction, and of the few-channel kernels.  Every tile is forced on shapes around its edges (rows and channels one below, at and above a tile,
 fewer slices than waves or ring stages, strided row classes, a class without taps) and compared with the CPU checker."""
 import numpy as np
 import pytest
@@ -119,3 +119,28 @@ def test_channels_that_are_no_multiple_of_64(shape, force, sol_env):
         name, value = setting.split("=")
         sol_env(name, value)
     run_forced(shape, name, value, sol_env)
+
+
+FEW_CHANNEL_SHAPES = {
+    "odd_rows_and_pairs": dict(N=2, H=33, W=35, C_in=3, C_out=64, K=7, stride=2, pad=3),          # odd Ho: half a last pair
+    "two_pixels_in_the_second_segment": dict(N=1, H=10, W=259, C_in=3, C_out=64, K=7, stride=2, pad=3),
+    "segments_and_images_within_one_range": dict(N=33, H=37, W=261, C_in=3, C_out=64, K=7, stride=2, pad=3),
+    "window_taller_than_the_image": dict(N=3, H=2, W=5, C_in=3, C_out=64, K=7, stride=2, pad=3),
+    "one_row_window": dict(N=70, H=23, W=9, C_in=2, C_out=64, K=1, stride=2, pad=0),
+    "even_window_1_channel": dict(N=5, H=15, W=17, C_in=1, C_out=64, K=4, stride=2, pad=1),
+    "unpadded_3_rows": dict(N=7, H=31, W=31, C_in=3, C_out=64, K=3, stride=2, pad=0),
+    "8x8_window_4_channels": dict(N=2, H=29, W=40, C_in=4, C_out=64, K=8, stride=2, pad=4),       # forward kernel only
+}
+
+
+@pytest.mark.parametrize("shape", list(FEW_CHANNEL_SHAPES), ids=list(FEW_CHANNEL_SHAPES))
+def test_few_channel_row_ring(shape):
+    """Forward and weight gradient of layers with up to four input channels: every way a range of output rows can begin
+    and end (odd heights, several segments or images in one range, windows reaching past the image on both sides)."""
+    print(f"[few channels] {shape}", flush=True)
+    case = pu.make_case(221, **FEW_CHANNEL_SHAPES[shape])
+    got = pu.gpu_block(case, need_dx=False, premasked=True)
+    pu.check_block(case, got, need_dx=False, premasked=True)
+    again = pu.gpu_block(case, need_dx=False, premasked=True)
+    for key in ("y", "dW", "dscale", "dshift"):
+        assert np.array_equal(got[key], again[key]), key
