@@ -72,7 +72,7 @@ struct SmallCWgradParams {     // weight gradient of the same layers (dy already
     const bf16_t* x;           // [N][H][W][C_in]
     const bf16_t* Wt;          // for dscale
     const float* scale;
-    float* partial;            // workspace: [nparts][64][KH*KW*C_in + 5] fp32
+    float* partial;            // workspace: [nparts][64][KH*KW*C_in + 9] fp32
     float* dW;                 // [64][KH][KW][C_in]
     float* dscale;
     float* dshift;

@@ -16,11 +16,13 @@
 //  * the accumulators hold 4 consecutive output channels per register group, so the epilogue (affine, ReLU, one
 //    rounding) produces 8-byte pieces of NHWC rows.
 //
-// 32 images of 224 x 224, 7x7 / stride 2, 3 -> 64: forward 22.1 us, where a launch that wrote a widened copy of the image and
-// a kernel that staged all KH rows of every tile from it took 6.5 + 22.0.  61 MB, so memory would allow 11 us; per tile and
-// compute unit the kernel takes 1.2 us, of which the matrix instructions are 0.4 and the rest the latencies of LDS reads,
-// epilogue and barrier that two waves per SIMD do not cover.
+// 32 images of 224 x 224, 7x7 / stride 2, 3 -> 64: forward 21.0 us, where a launch that wrote a widened copy of the image and
+// a kernel that staged all KH rows of every tile from it took 6.5 + 22.0.  61 MB, so memory would allow 11 us; a launch
+// costs 5 us before its first tile and a tile 0.8 us per compute unit, of which the matrix instructions are 0.4 and the LDS
+// reads 0.5.
 #include <stdlib.h>
+
+#include <type_traits>
 
 #include "launch.h"
 
@@ -84,14 +86,18 @@ __device__ __forceinline__ void lds_barrier() {
 // i + 2 and i + 3 are in flight, the latter issued before tile i's stores, whose completion they then need not wait for
 // (vector memory operations complete in order).  Beyond the run the loads are issued all the same, out of range: the
 // number in flight, which the waits count, is then the same on every path.  The epilogue's LDS staging is private to a wave.
+constexpr int smallc_fwd_lds_bytes(int KH) {
+    const int tile = (KH + 2) * SC_PW * 8 + 4 * 32 * 17 * 8, weights = 2 * KH * 4096;
+    return tile > weights ? tile : weights;
+}
 template <int KH, int CIN>
 __global__ __launch_bounds__(256, 2) void smallc_fwd_kernel(const SmallCParams p) {
     constexpr int KS = 2 * KH;                       // 16-deep MFMA steps
     constexpr int RING = KH + 2;
     constexpr int OP = 17;                           // 8-byte pieces per staged output pixel (16 + 1 of padding)
-    constexpr int ROWS_BYTES = RING * SC_PW * 8, OUTS_BYTES = 4 * 32 * OP * 8;
-    static_assert(KS * SC_CO * 2 * 16 <= ROWS_BYTES + OUTS_BYTES, "the weight image shares the LDS of ring and output staging");
-    __shared__ __align__(16) unsigned char smem[ROWS_BYTES + OUTS_BYTES];
+    constexpr int ROWS_BYTES = RING * SC_PW * 8;
+    // the weights, as they lie and as operand image, share the LDS of ring and output staging
+    extern __shared__ __align__(16) unsigned char smem[];            // smallc_fwd_lds_bytes(KH)
     __shared__ __align__(16) float affine[2][SC_CO];
     uintx2* ring = reinterpret_cast<uintx2*>(smem);
 
@@ -130,43 +136,39 @@ __global__ __launch_bounds__(256, 2) void smallc_fwd_kernel(const SmallCParams p
         request(2, next[0]);
         __builtin_amdgcn_sched_barrier(0);
     };
-    begin_run();
 
-    // weights -> operand image in LDS (element e of the piece of (step ks, channel co, half h):
-    // W[co][ks/2][4*(ks&1) + 2*h + e/4][e%4] or 0) -> registers.  Consecutive threads read consecutive taps; all requests
-    // go out before the first wait.
-    {
-        const buffer_rsrc_t weight_rs = make_buffer_rsrc(p.Wt, (unsigned)(SC_CO * KH * p.KW * p.C_in) * 2u);
-        constexpr int NC = CIN == 3 ? 3 : 4;
-        unsigned short e[KH][2][NC];
+    // weights -> LDS as they lie -> operand image in LDS (element e of the piece of (step ks, channel co, half h):
+    // W[co][ks/2][4*(ks&1) + 2*h + e/4][e%4] or 0) -> registers.  (Gathered from memory two bytes at a time the pieces kept the
+    // address units of two workgroups busy for 3 us.)
+    const int wpieces = SC_CO / 8 * KH * p.KW * p.C_in;
+    uintx4 raw[KH];
 #pragma unroll
-        for (int k = 0; k < KH; ++k) {
-            const int i = tid + 256 * k, row = i >> 2;                        // row = co * KH + kh
+    for (int k = 0; k < KH; ++k)
+        if (tid + 256 * k < wpieces) raw[k] = reinterpret_cast<const uintx4*>(p.Wt)[tid + 256 * k];
+    float affine_in = 0.f;
+    if (tid < 2 * SC_CO) affine_in = tid < SC_CO ? p.scale[tid] : p.shift[tid - SC_CO];
+    __builtin_amdgcn_sched_barrier(0);
+    begin_run();                                     // arrives while the weights are sorted
+    const uint16_t* wraw = reinterpret_cast<const uint16_t*>(smem + KH * 4096);
 #pragma unroll
-            for (int u = 0; u < 2; ++u)
+    for (int k = 0; k < KH; ++k)
+        if (tid + 256 * k < wpieces) reinterpret_cast<uintx4*>(smem + KH * 4096)[tid + 256 * k] = raw[k];
+    lds_barrier();
 #pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    const int kw = 2 * (i & 3) + u;
-                    const unsigned at = (unsigned)((row * p.KW + kw) * p.C_in + c) * 2u;
-                    e[k][u][c] = __builtin_amdgcn_raw_buffer_load_b16(weight_rs, kw < p.KW && c < p.C_in ? at : kOutOfRange, 0, 0);
-                }
+    for (int k = 0; k < KH; ++k) {
+        const int i = tid + 256 * k, row = i >> 2, co = row / KH, kh = row % KH;        // row = co * KH + kh
+        uint32_t e[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int kw = 2 * (i & 3) + (j >> 2), c = j & 3;
+            const bool in = kw < p.KW && (CIN == 3 ? c < 3 : c < p.C_in);
+            e[j] = CIN == 3 && c == 3 ? 0u : (uint32_t)wraw[in ? (row * p.KW + kw) * p.C_in + c : 0];
+            e[j] = in ? e[j] : 0u;
         }
-#pragma unroll
-        for (int k = 0; k < KH; ++k) {
-            const int i = tid + 256 * k, row = i >> 2, co = row / KH, kh = row % KH;
-            uintx4 v;
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                v[2 * u] = (uint32_t)e[k][u][0] | ((uint32_t)e[k][u][1] << 16);
-                v[2 * u + 1] = (uint32_t)e[k][u][2] | (NC > 3 ? (uint32_t)e[k][u][NC - 1] << 16 : 0u);
-            }
-            reinterpret_cast<uintx4*>(smem)[((2 * kh + ((i >> 1) & 1)) * SC_CO + co) * 2 + (i & 1)] = v;
-        }
+        reinterpret_cast<uintx4*>(smem)[((2 * kh + ((i >> 1) & 1)) * SC_CO + co) * 2 + (i & 1)] =
+            uintx4{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
     }
-    if (tid < SC_CO) {
-        affine[0][tid] = p.scale[tid];
-        affine[1][tid] = p.shift[tid];
-    }
+    if (tid < 2 * SC_CO) affine[tid >> 6][tid & 63] = affine_in;
     lds_barrier();
     uintx4 wf[KS][2];
 #pragma unroll
@@ -274,7 +276,7 @@ static hipError_t launch_smallc_fwd_kh(const SmallCParams& p, hipStream_t stream
     const long long tiles = (long long)p.N * p.Ho * segs;
     const long long cap = 512;                                 // two workgroups per compute unit
     const int grid = (int)(tiles < cap ? tiles : cap);
-    SOL_LAUNCH((smallc_fwd_kernel<KH, CIN>), dim3(grid), dim3(256), 0, stream, p);
+    SOL_LAUNCH((smallc_fwd_kernel<KH, CIN>), dim3(grid), dim3(256), smallc_fwd_lds_bytes(KH), stream, p);
     return hipGetLastError();
 }
 
@@ -307,13 +309,14 @@ hipError_t launch_smallc_fwd(const SmallCParams& p, hipStream_t stream) {
 // the slabs are added through LDS and the workgroup writes one fp32 partial, per channel KH*KW*C_in gradient columns, the
 // column sum of g and its share of <W, G> (so that the sum over the workgroups can be split by columns);
 // smallc_wgrad_reduce_kernel adds the workgroups in a fixed order.
-// 32 images of 224 x 224, 7x7 / stride 2: 27.0 us + 5.8 us for the reduction.  With four waves, all KH rows per tile read from
-// a widened copy of the image and one pair of rows in flight: 6.3 (copy) + 39.0 + 9.7 us (the reduction on 64 compute
-// units, each of which moves 25 bytes per ns at most).  64 MB, so memory would allow 12 us.
+// 32 images of 224 x 224, 7x7 / stride 2: 23.5 us + 5.4 us for the reduction.  With four waves, all KH rows per tile read from
+// a widened copy of the image and one tile in flight: 6.3 (copy) + 39.0 + 9.7 us (the reduction on 64 compute units, each of
+// which moves 25 bytes per ns at most).  64 MB, so memory would allow 12 us; a launch costs 8 us besides its pairs of rows,
+// and a pair 1.9 us, of which the matrix instructions are 0.9.
 constexpr int SC_GP = 160;         // bytes per staged gradient row (128 + 32: the 4 rows of a transposing read fall into
                                    // different banks)
 constexpr int SC_SLAB = 8 * 2 * 16 * 64;             // accumulators of one slab (both halves), floats
-constexpr int kExtraCols = 5;      // columns of a partial row behind the gradient: column sum, four parts of <W, G>
+constexpr int kExtraCols = 9;      // columns of a partial row behind the gradient: column sum, eight parts of <W, G>
 constexpr int smallc_wgrad_lds_bytes(int KH) {
     const int operands = (KH + 6) * SC_PW * 8 + 4 * SC_TILE * SC_GP, slabs = 2 * SC_SLAB * 4;
     return operands > slabs ? operands : slabs;
@@ -339,7 +342,14 @@ __global__ __launch_bounds__(512, 2) void smallc_wgrad_kernel(const SmallCWgradP
     const buffer_rsrc_t image_rs = make_buffer_rsrc(p.x, (unsigned)(p.N * p.H * p.W * p.C_in) * 2u);
     const buffer_rsrc_t grad_rs = make_buffer_rsrc(p.dy, (unsigned)(p.N * p.Ho * p.Wo * SC_CO) * 2u);
     uintx4* wstage = reinterpret_cast<uintx4*>(smem + smallc_wgrad_lds_bytes(KH));
-    for (int i = tid; i < SC_CO / 8 * KH * p.KW * p.C_in; i += 512) wstage[i] = reinterpret_cast<const uintx4*>(p.Wt)[i];
+    const int wpieces = SC_CO / 8 * KH * p.KW * p.C_in;
+    uintx4 raw[(KH + 1) / 2];
+#pragma unroll
+    for (int k = 0; k < (KH + 1) / 2; ++k)
+        if (tid + 512 * k < wpieces) raw[k] = reinterpret_cast<const uintx4*>(p.Wt)[tid + 512 * k];
+#pragma unroll
+    for (int k = 0; k < (KH + 1) / 2; ++k)
+        if (tid + 512 * k < wpieces) wstage[tid + 512 * k] = raw[k];
     floatx16 acc[4][2];                              // [slot][channel tile]
 #pragma unroll
     for (int v = 0; v < 16; ++v)
@@ -468,73 +478,85 @@ __global__ __launch_bounds__(512, 2) void smallc_wgrad_kernel(const SmallCWgradP
         t += run;
     }
 
-    // (slab 0 + slab 1) + (slab 2 + slab 3), through two slabs of LDS: [half][u][c][16 / 4][lane] pieces of 16 bytes
-    floatx4* sums = reinterpret_cast<floatx4*>(smem);
-    auto put = [&](int to) {
+    // The four slabs are added through LDS: first a wave and its partner (slab ^ 1) exchange halves, the even slab keeps channel
+    // tile 0, then with slab ^ 2 half of what is left, slabs 0 and 1 keep slots 0 and 1.  A wave's mail lies at its own place.
+    floatx4* mail = reinterpret_cast<floatx4*>(smem);                 // [wave][piece][lane] of 16 bytes, 16 KiB per wave
+    auto post = [&](int to, auto c_tag, auto u_tag) {                 // slots u .. u + 3 (or 1) of channel tile c
+        constexpr int C = decltype(c_tag)::value, U = decltype(u_tag)::value;
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < (U < 0 ? 4 : 2); ++u)
 #pragma unroll
-            for (int c = 0; c < 2; ++c)
-#pragma unroll
-                for (int g = 0; g < 4; ++g)
-                    sums[to * (SC_SLAB / 4) + (((half * 4 + u) * 2 + c) * 4 + g) * 64 + lane] =
-                        floatx4{acc[u][c][4 * g], acc[u][c][4 * g + 1], acc[u][c][4 * g + 2], acc[u][c][4 * g + 3]};
+            for (int g = 0; g < 4; ++g) {
+                const floatx16& a = acc[(U < 0 ? 0 : U) + u][C];
+                mail[to * 1024 + (u * 4 + g) * 64 + lane] = floatx4{a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]};
+            }
     };
-    auto add = [&](int from) {
+    auto open = [&](auto c_tag, auto u_tag) {
+        constexpr int C = decltype(c_tag)::value, U = decltype(u_tag)::value;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            __builtin_amdgcn_sched_barrier(0);       // eight reads in flight: more would spill
+        for (int u = 0; u < (U < 0 ? 4 : 2); ++u)
 #pragma unroll
-            for (int c = 0; c < 2; ++c)
+            for (int g = 0; g < 4; ++g) {
+                const floatx4 v = mail[wave * 1024 + (u * 4 + g) * 64 + lane];
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const floatx4 v = sums[from * (SC_SLAB / 4) + (((half * 4 + u) * 2 + c) * 4 + g) * 64 + lane];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[u][c][4 * g + e] += v[e];
-                }
-        }
+                for (int e = 0; e < 4; ++e) acc[(U < 0 ? 0 : U) + u][C][4 * g + e] += v[e];
+            }
     };
+    using std::integral_constant;
     __syncthreads();
-    if (slab & 1) put(slab >> 1);
+    if (slab & 1) post(wave ^ 1, integral_constant<int, 0>{}, integral_constant<int, -1>{});
+    else post(wave ^ 1, integral_constant<int, 1>{}, integral_constant<int, -1>{});
     __syncthreads();
-    if (!(slab & 1)) add(slab >> 1);
+    if (slab & 1) {
+        open(integral_constant<int, 1>{}, integral_constant<int, -1>{});
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc[u][0] = acc[u][1];
+    } else {
+        open(integral_constant<int, 0>{}, integral_constant<int, -1>{});
+    }
     __syncthreads();
-    if (slab == 2) put(0);
+    if (slab & 2) post(wave ^ 2, integral_constant<int, 0>{}, integral_constant<int, 0>{});
+    else post(wave ^ 2, integral_constant<int, 0>{}, integral_constant<int, 2>{});
     __syncthreads();
-    if (slab == 0) add(0);
+    if (slab & 2) {
+        open(integral_constant<int, 0>{}, integral_constant<int, 2>{});
+        acc[0][0] = acc[2][0];
+        acc[1][0] = acc[3][0];
+    } else {
+        open(integral_constant<int, 0>{}, integral_constant<int, 0>{});
+    }
     __syncthreads();
 
-    // rows of the partial (gradient columns, column sum, four parts of <W, G>) in LDS, then out as they lie
+    // rows of the partial (gradient columns, column sum, eight parts of <W, G>) in LDS, then out as they lie
     // lane = channel (lane & 31); register group g holds filter column kw' = 2g + lane/32, element e channel e of the image
     const int K = KH * p.KW * p.C_in, cols = K + kExtraCols;
-    float* rows = reinterpret_cast<float*>(smem);                     // [64][cols], at most 64 * 229 floats
+    float* rows = reinterpret_cast<float*>(smem);                     // [64][cols], at most 64 * 233 floats
     const bf16_t* wts = reinterpret_cast<const bf16_t*>(smem + smallc_wgrad_lds_bytes(KH));
-    if (slab == 0) {
+    {
+        const int co = 32 * (slab & 1) + (lane & 31);
+        float dot = 0.f;
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            const int co = 32 * c + (lane & 31);
-            float dot = 0.f;
+        for (int u = 0; u < 2; ++u) {
+            const int kh = 4 * half + (slab & 2) + u;
+            if (kh >= KH) {
+                // slot 7 never has a filter row: every row of its ones-product is the column sum of g
+                if (kh == 7 && lane < 32) rows[co * cols + K] = acc[u][0][0];
+                continue;
+            }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int kh = 4 * half + u;
-                if (kh >= KH) continue;
+            for (int g = 0; g < 4; ++g) {
+                const int kw = 2 * g + (lane >> 5), o = (kh * p.KW + kw) * p.C_in;
+                if (kw < p.KW) {
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int kw = 2 * g + (lane >> 5), o = (kh * p.KW + kw) * p.C_in;
-                    if (kw < p.KW) {
-#pragma unroll
-                        for (int e = 0; e < (CIN == 3 ? 3 : 4); ++e)
-                            if (CIN == 3 || e < p.C_in) {
-                                rows[co * cols + o + e] = acc[u][c][4 * g + e];
-                                dot = fmaf(bf16_to_f32(wts[co * K + o + e]), acc[u][c][4 * g + e], dot);
-                            }
-                    }
+                    for (int e = 0; e < (CIN == 3 ? 3 : 4); ++e)
+                        if (CIN == 3 || e < p.C_in) {
+                            rows[co * cols + o + e] = acc[u][0][4 * g + e];
+                            dot = fmaf(bf16_to_f32(wts[co * K + o + e]), acc[u][0][4 * g + e], dot);
+                        }
                 }
             }
-            rows[co * cols + K + 1 + 2 * half + (lane >> 5)] = dot;
-            // slot 7 never has a filter row: every row of its ones-product is the column sum of g
-            if (half == 1 && lane < 32) rows[co * cols + K] = acc[3][c][0];
         }
+        rows[co * cols + K + 1 + 4 * half + (slab & 2) + (lane >> 5)] = dot;
     }
     __syncthreads();
     float* part = p.partial + (long long)blockIdx.x * SC_CO * cols;
@@ -572,7 +594,9 @@ __global__ __launch_bounds__(512) void smallc_wgrad_reduce_kernel(const SmallCWg
         const float d = sc * g;
         p.dW[o] = p.accumulate ? p.dW[o] + d : d;
     } else {
-        const float d01 = g + __shfl_down(g, 1), d = d01 + __shfl_down(d01, 2);        // in lane 1: the four parts of <W, G>
+        float d = g + __shfl_down(g, 1);                       // in lane 1: the eight parts of <W, G>
+        d += __shfl_down(d, 2);
+        d += __shfl_down(d, 4);
         if (c == 0) p.dshift[co] = p.accumulate ? p.dshift[co] + g : g;
         if (c == 1) p.dscale[co] = p.accumulate ? p.dscale[co] + d : d;
     }
@@ -592,7 +616,7 @@ size_t smallc_wgrad_workspace_bytes(int N, int H, int W, int Ho, int Wo) {
     return ((size_t)N * H * W * 4 * 2 + 255) / 256 * 256 + ((size_t)row_tiles(N, Ho, Wo) * SC_CO * 264 * 4 + 255) / 256 * 256;
 }
 // Workgroups: one per compute unit, at most one per pair of output rows.  Their partials, at most
-// 64 * (7 * 8 * 4 + 5) floats each, fit the size above: there are no more of them than row tiles.
+// 64 * (7 * 8 * 4 + 9) floats each, fit the size above: there are no more of them than row tiles.
 int smallc_wgrad_parts(int N, int Ho, int Wo) {
     const long long units = (long long)N * ((Ho + 1) / 2) * ((Wo + SC_TILE - 1) / SC_TILE);
     return (int)(units < 256 ? units : 256);
