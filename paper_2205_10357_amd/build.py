@@ -7,7 +7,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsol_block.so")
 PROBE = os.path.join(HERE, "loop_model.bin")
-SOURCES = ["api.hip", "igemm.hip", "igemm_fast.hip", "igemm_panel.hip", "igemm_wide.hip", "igemm_halo.hip", "igemm_ksplit.hip", "wgrad.hip", "wgrad_fast.hip", "smallc.hip", "direct_f32.hip", "glue.hip", "runtime.hip"]
+SOURCES = ["api.hip", "igemm.hip", "igemm_fast.hip", "igemm_panel.hip", "igemm_wide.hip", "igemm_halo.hip", "igemm_ksplit.hip", "wgrad.hip", "wgrad_fast.hip", "wgrad_wide.hip", "smallc.hip", "direct_f32.hip", "glue.hip", "runtime.hip"]
 HEADERS = ["common.h", "launch.h", "classes.h", "igemm_gather.h", "pack_tile.h", "reduce_rows.h", "sol_lds_tr.h", os.path.join("..", "..", "include", "sol_block.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

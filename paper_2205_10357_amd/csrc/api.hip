@@ -59,12 +59,12 @@ inline void clear_stale_error() { (void)hipGetLastError(); }
 enum Knob {
     K_IGEMM_TILE, K_IGEMM_FAST, K_FAST_TILE, K_FAST_SHORTK, K_FAST_MANY, K_FAST_STAGES, K_WGRAD_SPLITS, K_WGRAD_TARGET,
     K_SMALLC, K_FILL_UNTOUCHED, K_WGRAD_FAST, K_PACK_FUSED, K_WGRAD_STAGES, K_PREMASK, K_PANEL, K_PANEL_TILES,
-    K_REDUCE_RIDES, K_WIDE, K_KSPLIT, K_HALO, K_COUNT
+    K_REDUCE_RIDES, K_WIDE, K_KSPLIT, K_HALO, K_WGRAD_WIDE, K_COUNT
 };
 const char* const kKnobNames[K_COUNT] = {
     "SOL_IGEMM_TILE", "SOL_IGEMM_FAST", "SOL_FAST_TILE", "SOL_FAST_SHORTK", "SOL_FAST_MANY", "SOL_FAST_STAGES",
     "SOL_WGRAD_SPLITS", "SOL_WGRAD_TARGET", "SOL_SMALLC", "SOL_FILL_UNTOUCHED", "SOL_WGRAD_FAST", "SOL_PACK_FUSED",
-    "SOL_WGRAD_STAGES", "SOL_PREMASK", "SOL_PANEL", "SOL_PANEL_TILES", "SOL_REDUCE_RIDES", "SOL_WIDE", "SOL_KSPLIT", "SOL_HALO"};
+    "SOL_WGRAD_STAGES", "SOL_PREMASK", "SOL_PANEL", "SOL_PANEL_TILES", "SOL_REDUCE_RIDES", "SOL_WIDE", "SOL_KSPLIT", "SOL_HALO", "SOL_WGRAD_WIDE"};
 constexpr int kKnobUnset = INT32_MIN;
 std::atomic<int> g_knobs[K_COUNT];
 std::atomic<bool> g_knobs_loaded{false};
@@ -374,6 +374,7 @@ int run_igemm(IgemmParams& p, const long long* rows, bool mask, const sol_plan& 
 
 struct BwdPlan {
     int splits, m_per_split, tiles_k, tiles_c;
+    bool wide;                    // the weight gradient takes the eight-wave kernel (where it takes a pipelined one at all)
     size_t wpack_off, part_off, dshift_off, total;
     // few-input-channel layers: per-workgroup partials of their own weight-gradient kernel
     bool smallc;
@@ -392,6 +393,7 @@ inline bool bf16_vector_shape(const sol_block_desc* d) {
 
 BwdPlan plan_bwd(const sol_block_desc* d, const Geometry& g) {
     BwdPlan b{};
+    int room = 1;                 // splits that the workspace has room for
     if (d->dtype == SOL_F32) {
         b.splits = 1;
         b.m_per_split = (int)g.M;
@@ -404,7 +406,13 @@ BwdPlan plan_bwd(const sol_block_desc* d, const Geometry& g) {
         const long long max_splits = (g.M + 63) / 64;
         long long want = knob(K_WGRAD_SPLITS, 0);
         if (want <= 0) want = installed_plan(d, SOL_PLAN_WGRAD).splits;
-        if (want <= 0) {
+        // (an installed plan or an override of the four-wave kernel's ring depth keeps that kernel)
+        const bool staged = installed_plan(d, SOL_PLAN_WGRAD).stages >= 2 || knob(K_WGRAD_STAGES, 0) >= 2;
+        const int force_wide = staged ? -1 : knob(K_WGRAD_WIDE, 0);
+        if (want > 0) {
+            room = (int)(want < max_splits ? want : max_splits);
+            b.wide = force_wide > 0;
+        } else {
             // A split of S costs each workgroup L / S slices (L = 64-row slices of the whole reduction) and the launch, the
             // reduction and the memory between them T * S fp32 tiles, so the best S goes with sqrt(L / T).  Measured
             // optima of weight gradient + reduction (7 .. 128 images, T = 4 .. 144 tiles) lie at S^2 T / L = 18 .. 22 for
@@ -415,16 +423,36 @@ BwdPlan plan_bwd(const sol_block_desc* d, const Geometry& g) {
             // pixels 23.2 -> 18.5; 3x3 128 -> 128 23.4 -> 19.7; 3x3 256 -> 256, 1372 pixels 30.4 -> 25.8.
             const bool linear = d->KH == 1 && d->KW == 1 && d->stride == 1 && d->pad == 0;
             const float slices = (float)((g.M + 63) / 64);
+            // Gathering form with a long reduction: one eight-wave workgroup per compute unit instead of two of four waves, i.e.
+            // half the partial tiles, beside the 2 T workgroups that re-pack (32 of them at most wait for their turn).  Weight
+            // gradient + reduction + data gradient, us, four -> eight waves: 3x3 256 -> 256, 12544 pixels (T = 36, L = 196)
+            // 44.2 -> 41.6; 3x3 128 -> 128 (T = 9) L = 392 33.0 -> 30.3, L = 1568 72.5 -> 71.0; 1x1 / stride 2 256 -> 512 (T = 8),
+            // L = 1568 149 -> 141.  With few slices the two are equal or four waves ahead (T = 9, L = 117: 19.4 and 19.8; T = 6,
+            // L = 130 20.7 and 21.0; T = 36, L = 22 26.5 and 27.2): the line is between.  Where one workgroup per compute unit
+            // leaves more than 96 idle (T = 144), two splits finer balance better.
+            const long long riders = tiles < 16 ? 2 * tiles : 32;
+            const long long wide_splits = (256 - riders) / tiles;
+            b.wide = force_wide > 0 ? wide_splits > 0 : !linear && force_wide == 0 && knob(K_WGRAD_TARGET, 0) <= 0 && wide_splits * tiles >= 160 && slices * (float)tiles >= 2048.f;
             want = (long long)(sqrtf((linear ? 18.f : 34.f) * slices / (float)tiles) + 0.5f);
             // (4 T small workgroups re-pack; the gathering form fills the chip once or twice, not one and a half times)
             const long long pack = tiles < 16 ? 2 * tiles : 32;
             const long long target = knob(K_WGRAD_TARGET, linear ? 256 - pack : (want * tiles <= 384 ? 256 : 512));
             const long long most = (target + (target > 256 ? tiles / 2 : 0)) / tiles;
             if (want > most) want = most;
+            if (b.wide) want = wide_splits;
             if (want > 64) want = 64;                       // more cannot ride with the data gradient
             // keep the fp32 partials below ~64 MiB
             const long long cap = (64LL << 20) / (g.w_elems * 4 > 0 ? g.w_elems * 4 : 1);
             if (want > cap) want = cap;
+            // The workspace keeps the room of the finest split that was ever asked for (256 workgroups for 1x1 / stride 1, 512
+            // for the gathering form, ranges of 128 rows), so that which calls the no-allocation entry takes does not move
+            // with the split.
+            long long most_room = ((linear ? 256 : 512) + tiles - 1) / tiles;
+            if (most_room > cap) most_room = cap;
+            if (most_room > (g.M + 127) / 128) most_room = (g.M + 127) / 128;
+            if (most_room < 1) most_room = 1;
+            const long long rows = ((g.M + most_room - 1) / most_room + 127) / 128 * 128;
+            room = (int)((g.M + rows - 1) / rows);
         }
         if (want < 1) want = 1;
         if (want > max_splits) want = max_splits;
@@ -435,8 +463,9 @@ BwdPlan plan_bwd(const sol_block_desc* d, const Geometry& g) {
         b.wpack_off = 0;
         b.part_off = align_up((size_t)g.w_elems * 2);
     }
-    b.dshift_off = b.part_off + align_up((size_t)b.splits * g.w_elems * 4);
-    b.total = b.dshift_off + align_up((size_t)b.splits * d->C_out * 4);
+    if (room < b.splits) room = b.splits;
+    b.dshift_off = b.part_off + align_up((size_t)room * g.w_elems * 4);
+    b.total = b.dshift_off + align_up((size_t)room * d->C_out * 4);
     b.smallc = d->dtype == SOL_BF16 && smallc_wgrad_supported(d->C_in, d->C_out, d->KH, d->KW, d->stride) &&
                knob(K_SMALLC, 1) != 0;
     if (b.smallc) {
@@ -808,7 +837,8 @@ static int bwd_common(const sol_block_desc* desc, const void* dy, const void* x,
             wp.div_howo = make_fast_div((uint32_t)(g.Ho * g.Wo));
             wp.div_wo = make_fast_div((uint32_t)g.Wo);
             wp.pack = pk;
-            wp.pack_blocks = pack_rides ? pack_tile_count(pk) : 0;
+            wp.pack_tiles = pack_rides ? pack_tile_count(pk) : 0;
+            wp.pack_blocks = wp.pack_tiles;
             const bool vec = bf16_vec;
             // pipelined kernel when dy needs no mask; SOL_WGRAD_FAST=0 forces the general kernel
             if (wgrad_pipelined) {
@@ -818,7 +848,13 @@ static int bwd_common(const sol_block_desc* desc, const void* dy, const void* x,
                     stages = wp.splits * wp.tiles_k * wp.tiles_c <= 256 ||       // one workgroup per compute unit
                              (desc->KH == 1 && desc->KW == 1 && desc->stride == 1 && desc->pad == 0) ? 3 : 2;
                 trace_point(st, SOL_TRACE_WGRAD);
-                if (launch_wgrad_fast(wp, stages, st) != hipSuccess) return SOL_ERR_LAUNCH;
+                if (plan.wide) {
+                    // two tiles of the re-pack at a time per workgroup, on the compute units that the products leave idle
+                    const int idle = (256 - (wp.splits * wp.tiles_k * wp.tiles_c) % 256) % 256, pairs = (wp.pack_tiles + 1) / 2;
+                    const int blocks = idle > 32 ? idle : 32;
+                    wp.pack_blocks = pairs < blocks ? pairs : blocks;
+                    if (launch_wgrad_wide(wp, st) != hipSuccess) return SOL_ERR_LAUNCH;
+                } else if (launch_wgrad_fast(wp, stages, st) != hipSuccess) return SOL_ERR_LAUNCH;
             } else {
                 trace_point(st, SOL_TRACE_WGRAD_GENERAL);
                 if (launch_wgrad(wp, vec, relu, st) != hipSuccess) return SOL_ERR_LAUNCH;

@@ -229,10 +229,10 @@ struct WgradParams {
     int m_per_split;            // multiple of the reduction tile
     int tiles_k, tiles_c;
     FastDiv div_howo, div_wo;   // divisors Ho*Wo and Wo
-    // pipelined kernel only: pack_blocks > 0 appends that many workgroups to the launch, which re-pack the
-    // weights for the data gradient of the same block (one 64 x 64 tile each) instead of multiplying
+    // pipelined kernels only: pack_blocks > 0 appends that many workgroups to the launch, which re-pack the
+    // weights for the data gradient of the same block (pack_tiles tiles of 64 x 64) instead of multiplying
     PackParams pack;
-    int pack_blocks;
+    int pack_blocks, pack_tiles;
 };
 
 

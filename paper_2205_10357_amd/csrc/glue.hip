@@ -31,7 +31,7 @@ __global__ __launch_bounds__(256) void pack_dgrad_weights_kernel(const PackParam
 // Same re-packing for channel counts that are multiples of 8: one workgroup per (tap, 64 co, 64 ci) tile.
 __global__ __launch_bounds__(256) void pack_dgrad_weights_tiled_kernel(const PackParams p) {
     __shared__ __align__(16) bf16_t tile[64 * kPackTilePitch];
-    pack_dgrad_weights_tile(p, (int)blockIdx.x, tile);
+    pack_dgrad_weights_tile(p, (int)blockIdx.x, (int)gridDim.x, tile);
 }
 
 template <typename T>

@@ -106,6 +106,7 @@ int plan_igemm_panel(IgemmParams& p, int tiles_per_workgroup);
 hipError_t launch_igemm_panel(const IgemmParams& p, hipStream_t stream);
 hipError_t launch_wgrad(const WgradParams& p, bool vec, bool mask, hipStream_t stream);
 hipError_t launch_wgrad_fast(const WgradParams& p, int stages, hipStream_t stream);
+hipError_t launch_wgrad_wide(const WgradParams& p, hipStream_t stream);
 hipError_t launch_wgrad_reduce(const ReduceParams& p, hipStream_t stream);
 hipError_t launch_direct_fwd_f32(const DirectParams& p, hipStream_t s);
 hipError_t launch_direct_bwd_f32(const DirectParams& p, hipStream_t s);

@@ -14,10 +14,12 @@ inline int pack_tile_count(const PackParams& p) { return p.KH * p.KW * ((p.C_in 
 
 // out[class][ci][(jh*Tw + jw)*C_out + co] = bf16(scale[co] * W[co][kh][kw][ci]) for tile b = (tap, 64 co, 64 ci),
 // transposed through LDS (tile: 64 * kPackTilePitch elements) so that both the reads (ci contiguous) and the
-// writes (co contiguous) are 16-byte pieces of 128-byte rows.  All 256 threads of the workgroup take part.
-__device__ __forceinline__ void pack_dgrad_weights_tile(const PackParams& p, int b, bf16_t* tile) {
+// writes (co contiguous) are 16-byte pieces of 128-byte rows.  Groups of 256 threads take a tile each (all threads of the
+// workgroup must call: barrier inside); tiles from `count` on do not exist.
+__device__ __forceinline__ void pack_dgrad_weights_tile(const PackParams& p, int b, int count, bf16_t* tile) {
     constexpr int PITCH = kPackTilePitch;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x & 255;
+    const bool exists = b < count;
     const int tiles_ci = (p.C_in + 63) >> 6, tiles_co = (p.C_out + 63) >> 6;
     const int tci = b % tiles_ci;
     b /= tiles_ci;
@@ -29,7 +31,7 @@ __device__ __forceinline__ void pack_dgrad_weights_tile(const PackParams& p, int
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int co = co0 + r0 + 32 * i;
-        if (co >= p.C_out || ci0 + c8 * 8 >= p.C_in) continue;
+        if (!exists || co >= p.C_out || ci0 + c8 * 8 >= p.C_in) continue;
         const float sc = p.scale[co];
         const uintx4 v = *reinterpret_cast<const uintx4*>(p.W + (((long long)co * p.KH + kh) * p.KW + kw) * p.C_in +
                                                            ci0 + c8 * 8);
@@ -50,7 +52,7 @@ __device__ __forceinline__ void pack_dgrad_weights_tile(const PackParams& p, int
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int cil = r0 + 32 * i;
-        if (ci0 + cil >= p.C_in || co0 + c8 * 8 >= p.C_out) continue;
+        if (!exists || ci0 + cil >= p.C_in || co0 + c8 * 8 >= p.C_out) continue;
         const uintx4 v = *reinterpret_cast<const uintx4*>(&tile[cil * PITCH + c8 * 8]);
         *reinterpret_cast<uintx4*>(p.out + off + ((long long)(ci0 + cil) * Th * Tw + (jh * Tw + jw)) * p.C_out + co0 +
                                    c8 * 8) = v;

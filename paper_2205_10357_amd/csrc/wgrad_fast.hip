@@ -43,7 +43,7 @@ __global__ __launch_bounds__(256) void wgrad_fast_kernel(const WgradParams p) {
     const int tiles = p.tiles_k * p.tiles_c;
     const int nwg = tiles * p.splits;         // workgroups that multiply; the launch may carry re-pack workgroups after them
     if ((int)blockIdx.x >= nwg) {
-        pack_dgrad_weights_tile(p.pack, (int)blockIdx.x - nwg, reinterpret_cast<bf16_t*>(lds));
+        pack_dgrad_weights_tile(p.pack, (int)blockIdx.x - nwg, p.pack_tiles, reinterpret_cast<bf16_t*>(lds));
         return;
     }
     const int bid = xcd_remap(blockIdx.x, nwg);

@@ -1,5 +1,5 @@
 """GPU parity of the implicit-GEMM families that the launch planner chooses by size: eight-wave tiles, tiles that
-keep a 3x3 neighbourhood in LDS and tiles whose waves split the reduction, and of the few-channel kernels.  Every tile is forced on shapes around its edges (rows and channels one below, at and above a tile,
+keep a 3x3 neighbourhood in LDS and tiles whose waves split the reduction, and of the few-channel and eight-wave weight-gradient kernels.  Every tile is forced on shapes around its edges (rows and channels one below, at and above a tile,
 fewer slices than waves or ring stages, strided row classes, a class without taps) and compared with the CPU checker."""
 import numpy as np
 import pytest
@@ -143,4 +143,33 @@ def test_few_channel_row_ring(shape):
     pu.check_block(case, got, need_dx=False, premasked=True)
     again = pu.gpu_block(case, need_dx=False, premasked=True)
     for key in ("y", "dW", "dscale", "dshift"):
+        assert np.array_equal(got[key], again[key]), key
+
+
+WIDE_WGRAD_SHAPES = {
+    "one_slice": dict(N=1, H=5, W=7, C_in=64, C_out=72, K=3, stride=1, pad=1),
+    "images_smaller_than_a_slice": dict(N=41, H=3, W=5, C_in=128, C_out=136, K=3, stride=1, pad=1),
+    "row_advance_carries_into_the_image": dict(N=7, H=13, W=11, C_in=72, C_out=104, K=3, stride=1, pad=1),
+    "stride_2_odd": dict(N=5, H=23, W=17, C_in=64, C_out=128, K=3, stride=2, pad=1),
+    "strided_1x1": dict(N=9, H=15, W=19, C_in=136, C_out=200, K=1, stride=2, pad=0, relu=False),
+    "taps_that_reach_no_pixel": dict(N=30, H=2, W=3, C_in=24, C_out=16, K=5, stride=1, pad=2),
+    "window_at_the_edge_only": dict(N=12, H=9, W=9, C_in=8, C_out=264, K=5, stride=2, pad=0),
+    "1x1": dict(N=3, H=21, W=9, C_in=256, C_out=128, K=1, stride=1, pad=0),
+}
+
+
+@pytest.mark.parametrize("splits", [0, 1, 3])
+@pytest.mark.parametrize("shape", list(WIDE_WGRAD_SHAPES), ids=list(WIDE_WGRAD_SHAPES))
+def test_eight_wave_weight_gradient(shape, splits, sol_env):
+    """The eight-wave weight gradient (fewer slices than ring stages, images below a slice, carries of the walking gather,
+    strides, taps without any pixel, partial tiles) with the riding re-pack, against the checker and twice the same bits."""
+    sol_env("SOL_WGRAD_WIDE", 1)
+    if splits:
+        sol_env("SOL_WGRAD_SPLITS", splits)
+    print(f"[eight-wave wgrad] {shape} splits={splits}", flush=True)
+    case = pu.make_case(231, **WIDE_WGRAD_SHAPES[shape])
+    got = pu.gpu_block(case, premasked=True)
+    pu.check_block(case, got, premasked=True)
+    again = pu.gpu_block(case, premasked=True)
+    for key in ("dx", "dW", "dscale", "dshift"):
         assert np.array_equal(got[key], again[key]), key
