@@ -568,8 +568,10 @@ int dgrad_bf16(const sol_block_desc* d, const Geometry& g, const void* dy, const
     long long rows[kMaxClasses];
     int nc = 0;
     // pixels without a tap (1x1 / stride 2: three quarters of dx) are filled at memory speed by a launch of their
-    // own; as GEMM tiles without a reduction they cost several times that
+    // own; as GEMM tiles without a reduction they cost several times that.  Where dx is added to in place and not masked
+    // they stay as they are (56x56, 128 images, 256 channels: a launch of 43 us).
     const bool fill_untouched = (d->C_in % 8) == 0 && knob(K_FILL_UNTOUCHED, 1) != 0;
+    const bool in_place = addend == dx && !addend_mask && !dx_mask;
     bool any_untouched = false;
     for (int ph = 0; ph < s; ++ph)
         for (int pw = 0; pw < s; ++pw) {
@@ -582,7 +584,7 @@ int dgrad_bf16(const sol_block_desc* d, const Geometry& g, const void* dy, const
             c.Tw = class_taps(d->KW, s, d->pad, pw, &fw);
             if (c.Th == 0 || c.Tw == 0) {   // no tap reaches these pixels: K = 0, output = addend
                 if (fill_untouched) {       // ... written by an element-wise launch instead of GEMM tiles
-                    any_untouched = true;
+                    any_untouched = !in_place;
                     continue;
                 }
                 c.Th = 0;

@@ -177,6 +177,23 @@ class Sequencer:
         return self.dact[last_op.out]
 
     # ----------------------------------------------------------------- backward
+    def _backward_order(self, readers, producer) -> list:
+        """Reverse op order, but a strided block that reaches only some pixels of its input (1x1 / stride 2: a quarter) comes
+        after the other readers of that input.  They have then written every pixel and the block adds to those it reaches;
+        coming first it would fill the others with zeros for the next reader to read and add to (stage-2 step of 128 images:
+        154 MB written and read back).  Where the input's gradient is masked the last writer has to touch every pixel, and the
+        order stays."""
+        order = list(reversed(self.ops))
+        for o in list(order):
+            src = producer.get(o.inp)
+            others = [r for r in readers[o.inp] if r is not o and r.k >= r.stride]
+            if o.k < o.stride and o.res is None and others and (src is None or not src.relu):
+                last = max(order.index(r) for r in others)
+                at = order.index(o)
+                if at < last:
+                    order.insert(last, order.pop(at))
+        return order
+
     def _plan_backward(self) -> None:
         """Resolve, once, the arguments of every backward call (reverse op order)."""
         for o in self.ops:
@@ -192,7 +209,8 @@ class Sequencer:
         shortcut: Dict[int, torch.Tensor] = {}     # shortcut gradient waiting to be added to a tensor
         written: Dict[int, bool] = {}
         calls: List[dict] = []
-        for o in reversed(self.ops):
+        order = self._backward_order(readers, producer)
+        for o in order:
             if o.out not in grad_of:
                 if o.out in shortcut and not readers.get(o.out):
                     if o.relu:
@@ -216,7 +234,7 @@ class Sequencer:
                     call["addend"] = shortcut.pop(o.inp)
                 written[o.inp] = True
                 grad_of[o.inp] = self.dact[o.inp]
-                is_last_writer = readers[o.inp][0] is o
+                is_last_writer = [r for r in order if r.inp == o.inp][-1] is o
                 src = producer.get(o.inp)
                 if is_last_writer and src is not None and src.relu:
                     call["dx_mask"] = self.act[o.inp]

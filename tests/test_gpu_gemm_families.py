@@ -173,3 +173,22 @@ def test_eight_wave_weight_gradient(shape, splits, sol_env):
     again = pu.gpu_block(case, premasked=True)
     for key in ("dx", "dW", "dscale", "dshift"):
         assert np.array_equal(got[key], again[key]), key
+
+
+@pytest.mark.parametrize("masked", [False, True])
+def test_strided_block_adds_to_its_input_gradient_in_place(masked):
+    """1x1 / stride 2 with dx as its own addend: the pixels it reaches get the sum, the others stay (or take the mask)."""
+    d = B.BlockDesc(3, 13, 11, 64, 128, 1, 1, 2, 0, B.SOL_BF16, 0)
+    g = torch.Generator(device="cuda").manual_seed(241)
+    draw = lambda *s: torch.randn(s, generator=g, device="cuda").to(torch.bfloat16)
+    W, dy, dx0 = draw(128, 1, 1, 64), draw(3, d.Ho, d.Wo, 128), draw(3, 13, 11, 64)
+    x, scale, mask = draw(3, 13, 11, 64), torch.rand(128, generator=g, device="cuda"), draw(3, 13, 11, 64) if masked else None
+    ws = torch.empty(B.sol_block_workspace_bytes(d, B.SOL_PASS_BWD), dtype=torch.uint8, device="cuda")
+    out = []
+    for in_place in (True, False):
+        dx = dx0.clone() if in_place else torch.full_like(dx0, 7.0)
+        B.sol_block_bwd(d, dy, x, W, None, dx, None, None, None, scale, None, dx if in_place else dx0, None, mask, ws)
+        out.append(dx)
+    assert torch.equal(out[0], out[1])
+    if not masked:
+        assert torch.equal(out[0][:, 1::2], dx0[:, 1::2]) and torch.equal(out[0][:, :, 1::2], dx0[:, :, 1::2])

@@ -115,3 +115,28 @@ def test_inference_arena_never_overlaps_live_tensors():
     # ResNet-50: the arena reaches the lower bound (stem output + pooled output and the like), a sixth of all-kept
     W = wl.Workload(4, "t", "bf16", 1, 224, 224, 3, wl.resnet50_ops(), np.zeros((1,), np.float32), train=False)
     assert W.plan_inference_arena()[1] == 3612672 and W.memory_plan()["intermediates_all_kept"] == 22428672
+
+
+def test_backward_visits_a_sparse_strided_reader_after_the_dense_one():
+    """A strided 1x1 block comes after the other readers of its input (they write every pixel, it adds to a quarter), every
+    block after those that read its output, and the order stays where the input's gradient is masked."""
+    from paper_2205_10357_amd.runner import Sequencer
+    from paper_2205_10357_amd import workloads as wl
+
+    def order_of(ops):
+        seq = Sequencer.__new__(Sequencer)
+        seq.ops = ops
+        readers = {}
+        for o in ops:
+            readers.setdefault(o.inp, []).append(o)
+        return readers, [o.name for o in seq._backward_order(readers, {o.out: o for o in ops})]
+
+    ops = wl.stage2_ops(True)
+    readers, names = order_of(ops)
+    assert sorted(names) == sorted(o.name for o in ops)
+    assert names[-2:] == [ops[0].name, next(o.name for o in ops if o.name.endswith("proj"))]
+    for o in ops:
+        for r in readers.get(o.out, []):
+            assert names.index(r.name) < names.index(o.name)
+    head = [wl.ConvBlock("head", 256, 256, 1, 1, 0, True, 99, 0, None, 99)]
+    assert order_of(head + ops)[1] == [o.name for o in reversed(head + ops)]
