@@ -219,7 +219,9 @@ GemmChoice choose_gemm(IgemmParams& p, const long long* rows, int tile, const Re
         plain.offer(GemmChoice{GEMM_FAST, t}, e, with_rider(e, n, t == 1 || t == 2));
     };
     offer_fast(tile);
-    if (ragged) offer_fast(3 - tile);                         // 128 x 64 and 64 x 64
+    // 64 x 64 beside 128 x 64 where its workgroups are resident at once (1x1 512 -> 2048, 539 pixels 8.0 -> 6.5 us, 1176 pixels
+    // 10.4 -> 7.9; 512 -> 128, 12544 pixels 8.2 -> 6.0)
+    if (ragged || (tile == 1 && tiles_of(p, rows, 64, 64) <= 640)) offer_fast(3 - tile);
     if (!ragged && knob(K_WIDE, 0) >= 0 && nk >= 8 && p.Nc > 64) {
         if (tile != 1) offer_fast(1);
         for (int w = 0; w < WIDE_TILES; ++w) {
@@ -310,7 +312,19 @@ int run_igemm(IgemmParams& p, const long long* rows, bool mask, const sol_plan& 
             igemm_fast_tile_shape(tile, &bp, &bc);
             if (tiles_of(p, rows, bp, bc) < 160) tile = 2;
             // the panel kernel where its launch is one wave of workgroups that fills most of the chip
-            if (panel_ok) {
+            // Short reductions whose small tiles are all resident at once pay one latency chain instead of a round after the
+            // other.  1x1 with residual, panel kernel or 128 x 64 -> 64 x 64, us: 64 -> 256, 18207 pixels (1140 tiles) 10.4 -> 6.0,
+            // 28611 9.2 -> 7.6, 62424 (3904) 14.3 and 13.9; 128 -> 512, 5488 pixels 6.0 -> 4.7, 8624 (1080) 8.7 -> 7.1; 256 -> 1024,
+            // 1372 6.0 -> 4.9, 2156 (544) 6.5 -> 5.9, 3136 (784) 6.7 and 7.1; 512 -> 2048, 1176 (608) 10.4 -> 7.9.  With four slices
+            // and more tiles than that 128 x 64 (256 -> 1024, 3136 pixels 6.1, 4704 10.2 -> 8.3), until the panel kernel leads.
+            const long long t64 = tiles_of(p, rows, 64, 64);
+            if (t64 <= (slices <= 2 ? 2560 : slices <= 4 ? 704 : slices <= 8 ? 640 : 0)) {
+                tile = 2;
+                many_tiles = false;
+            } else if (slices <= 4 && t64 <= 1280 && p.Nc > 64) {
+                tile = 1;
+                many_tiles = true;
+            } else if (panel_ok) {
                 const long long panels = (rows[0] + 127) / 128;
                 long long groups = 256 / (panels > 0 ? panels : 1);
                 if (groups > p.Nc / 128) groups = p.Nc / 128;
@@ -326,7 +340,7 @@ int run_igemm(IgemmParams& p, const long long* rows, bool mask, const sol_plan& 
         choice = free_choice ? choose_gemm(p, rows, tile, knob(K_REDUCE_RIDES, 1) != 0 ? rider : nullptr, tuned.tile < 0) : GemmChoice{GEMM_FAST, tile};
         if (choice.family == GEMM_FAST && choice.tile != tile) {
             tile = choice.tile;
-            many_tiles = true;
+            many_tiles = tile != 2 || tiles_of(p, rows, 64, 64) > 512;      // deep rings of 64 x 64 tiles: two per compute unit
         }
         stages = knob(K_FAST_STAGES, 0);
         if (stages < 2 || stages > 4) stages = tuned.stages;

@@ -192,3 +192,16 @@ def test_strided_block_adds_to_its_input_gradient_in_place(masked):
     assert torch.equal(out[0], out[1])
     if not masked:
         assert torch.equal(out[0][:, 1::2], dx0[:, 1::2]) and torch.equal(out[0][:, :, 1::2], dx0[:, :, 1::2])
+
+
+@pytest.mark.parametrize("shape", [
+    dict(N=4, H=16, W=44, C_in=256, C_out=1024, K=1, stride=1, pad=0, res=True),      # 704 tiles of 64 x 64: the last resident
+    dict(N=4, H=16, W=45, C_in=256, C_out=1024, K=1, stride=1, pad=0, res=True),      # one column of tiles more: 128 x 64
+    dict(N=1, H=32, W=40, C_in=512, C_out=2048, K=1, stride=1, pad=0, res=True),      # eight slices, 640 tiles
+    dict(N=1, H=32, W=41, C_in=512, C_out=2048, K=1, stride=1, pad=0, res=True),
+])
+def test_pointwise_launches_around_the_resident_tile_lines(shape):
+    """The library's own choice of tile on either side of the lines between small tiles resident at once and the others."""
+    case = pu.make_case(251, **shape)
+    got = pu.gpu_block(case, premasked=True)
+    pu.check_block(case, got, premasked=True)
