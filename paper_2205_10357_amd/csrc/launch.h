@@ -54,8 +54,7 @@ struct DirectParams {
     float* G;                 // unscaled weight gradient [C_out][K] (one split)
     float* dshift_partial;    // [C_out]
     int N, H, W_, C_in, C_out, KH, KW, stride, pad, Ho, Wo, relu;
-    FastDiv div_cin, div_cout, div_kw, div_howo, div_wo, div_hw, div_w, div_stride;   // set by the launchers, as
-    int dgrad_blocks;                                                                 // the split of the backward launch
+    FastDiv div_cin, div_cout, div_kw, div_howo, div_wo, div_hw, div_w, div_stride;   // set by the launchers
 };
 
 

@@ -97,6 +97,47 @@ def test_fp32_matrix_kernels(shape):
         assert np.array_equal(one[key], two[key]), key
 
 
+def _same_class_and_value(name, got, ref, tol):
+    """NaN and the two infinities exactly where the checker has them; finite values to `tol` of their norm."""
+    kind = lambda a: np.isnan(a) * 1 + np.isposinf(a) * 2 + np.isneginf(a) * 3
+    assert np.array_equal(kind(got), kind(ref)), (name, int((kind(got) != kind(ref)).sum()), int((kind(ref) > 0).sum()))
+    fin = np.isfinite(ref)
+    assert pu.rel_l2(got[fin], ref[fin]) <= tol, name
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+@pytest.mark.parametrize("plant", ["w", "dy"])
+@pytest.mark.parametrize("shape", [
+    dict(N=2, H=9, W=11, C_in=3, C_out=20, K=3, stride=1, pad=1),
+    dict(N=1, H=14, W=13, C_in=17, C_out=5, K=3, stride=2, pad=1),
+    dict(N=2, H=7, W=6, C_in=4, C_out=33, K=5, stride=2, pad=2),
+])
+def test_fp32_infinite_operand_spares_what_no_tap_reaches(shape, plant, value):
+    """A weight or gradient that is not finite reaches the results its taps reach and no other: a tap outside the image, or
+    between the strides, is skipped and not multiplied by zero."""
+    case = pu.make_case(233, bf16=False, relu=False, **shape)
+    d = case["d"]
+    r = np.random.default_rng(234)
+    case["dy"] = r.standard_normal((d.N, d.C_out, d.Ho, d.Wo)).astype(np.float32)
+    flat = case[plant].reshape(-1)
+    flat[[0, flat.size // 3, flat.size - 1]] = value
+    x, w, dy = (pu.to_dev(case[k], False) for k in ("x", "w", "dy"))
+    scale, shift = pu.vec_dev(case["scale"]), pu.vec_dev(case["shift"])
+    desc = B.BlockDesc(d.N, d.H, d.W, d.C_in, d.C_out, d.KH, d.KW, d.stride, d.pad, B.SOL_F32, 0)
+    y, dx, dW = torch.empty_like(dy), torch.empty_like(x), torch.empty_like(w)
+    ds, db = torch.empty_like(scale), torch.empty_like(scale)
+    ws = torch.empty(B.sol_block_workspace_bytes(desc, B.SOL_PASS_BWD), dtype=torch.uint8, device="cuda")
+    B.sol_block_fwd(desc, x, w, scale, shift, None, y, None)
+    B.sol_block_bwd(desc, dy, x, w, None, dx, dW, ds, db, scale, None, None, None, None, ws)
+    torch.cuda.synchronize()
+    y_o = pu.orc.block_fwd(d, case["x"], case["w"], case["scale"], case["shift"])
+    g = pu.orc.block_bwd(d, case["dy"], case["x"], case["w"], y_o, case["scale"])
+    _same_class_and_value("y", pu.to_host(y), y_o, pu.TOL["f32"])
+    _same_class_and_value("dx", pu.to_host(dx), g["dx"], pu.TOL["f32"])
+    _same_class_and_value("dW", pu.to_host(dW), g["dW"], pu.TOL["f32"])
+    _same_class_and_value("dshift", pu.to_host(db, None), g["dshift"], pu.TOL["f32"])
+
+
 RAGGED_SHAPES = {
     "8_channels_many_taps_per_slice": dict(N=2, H=9, W=7, C_in=8, C_out=16, K=5, stride=1, pad=2),
     "56_channels_one_short_slice": dict(N=1, H=6, W=11, C_in=56, C_out=8, K=1, stride=1, pad=0, res=True),
