@@ -20,6 +20,12 @@ constexpr int kDirectWaves = 8;
 constexpr int kDirectThreads = 64 * kDirectWaves;
 constexpr int kDirectPitch = 17;
 constexpr int kDirectUnroll = 8;
+// A dimension of a launch may have at most 2^32 - 1 threads, and a tensor of few channels has more tiles than that allows
+// (2^27 pixels of one channel: 2^23 tiles of 512 threads): tiles lie in rows of this many workgroups.  (A loop over tiles in
+// a smaller grid took 77 registers instead of 50 and a tenth of the backward launch's speed.)
+constexpr int kDirectRow = 1 << 20;
+__device__ __forceinline__ int direct_tile_index() { return (int)(blockIdx.y * (unsigned)kDirectRow + blockIdx.x); }
+
 struct DirectLds {
     float part[kDirectWaves * 16 * kDirectPitch];
     float colsum[kDirectWaves][16];
@@ -273,17 +279,18 @@ __device__ __forceinline__ void direct_wgrad_tile(const DirectParams& p, int til
     }
 }
 
-__global__ __launch_bounds__(kDirectThreads) void direct_fwd_f32(const DirectParams p) {
+__global__ __launch_bounds__(kDirectThreads) void direct_fwd_f32(const DirectParams p, int tiles) {
     __shared__ DirectLds lds;
-    direct_fwd_tile(p, blockIdx.x, lds);
+    const int t = direct_tile_index();
+    if (t < tiles) direct_fwd_tile(p, t, lds);
 }
 
 // Tiles [0, dgrad_tiles): data gradient; the rest: tiles of the unscaled weight gradient G.
-__global__ __launch_bounds__(kDirectThreads) void direct_bwd_f32(const DirectParams p, int dgrad_tiles) {
+__global__ __launch_bounds__(kDirectThreads) void direct_bwd_f32(const DirectParams p, int dgrad_tiles, int tiles) {
     __shared__ DirectLds lds;
-    const int t = blockIdx.x;
+    const int t = direct_tile_index();
     if (t < dgrad_tiles) direct_dgrad_tile(p, t, lds);
-    else direct_wgrad_tile(p, t - dgrad_tiles, lds);
+    else if (t < tiles) direct_wgrad_tile(p, t - dgrad_tiles, lds);
 }
 
 static void set_divisors(DirectParams& p) {
@@ -296,13 +303,19 @@ static void set_divisors(DirectParams& p) {
     p.div_w = make_fast_div((uint32_t)p.W_);
     p.div_stride = make_fast_div((uint32_t)p.stride);
 }
+// (a tensor has at most 2^31 - 1 elements: at most 2^27 tiles, as a column of 1 x n elements)
 static inline long long tiles16(long long rows, long long cols) { return ((rows + 15) / 16) * ((cols + 15) / 16); }
+static inline dim3 direct_grid(long long tiles) {
+    if (tiles <= kDirectRow) return dim3((unsigned)tiles);
+    return dim3(kDirectRow, (unsigned)((tiles + kDirectRow - 1) / kDirectRow));
+}
+static_assert((long long)kDirectRow * kDirectThreads < (1LL << 32), "threads of a launch");
 
 hipError_t launch_direct_fwd_f32(const DirectParams& params, hipStream_t s) {
     DirectParams p = params;
     set_divisors(p);
     const long long tiles = tiles16((long long)p.N * p.Ho * p.Wo, p.C_out);
-    SOL_LAUNCH(direct_fwd_f32, dim3((unsigned)tiles), dim3(kDirectThreads), 0, s, p);
+    SOL_LAUNCH(direct_fwd_f32, direct_grid(tiles), dim3(kDirectThreads), 0, s, p, (int)tiles);
     return hipGetLastError();
 }
 
@@ -312,7 +325,7 @@ hipError_t launch_direct_bwd_f32(const DirectParams& params, hipStream_t s) {
     set_divisors(p);
     const long long dgrad = p.dx ? tiles16((long long)p.N * p.H * p.W_, p.C_in) : 0;
     const long long wgrad = p.G ? tiles16((long long)p.KH * p.KW * p.C_in, p.C_out) : 0;
-    SOL_LAUNCH(direct_bwd_f32, dim3((unsigned)(dgrad + wgrad)), dim3(kDirectThreads), 0, s, p, (int)dgrad);
+    SOL_LAUNCH(direct_bwd_f32, direct_grid(dgrad + wgrad), dim3(kDirectThreads), 0, s, p, (int)dgrad, (int)(dgrad + wgrad));
     return hipGetLastError();
 }
 

@@ -138,6 +138,27 @@ def test_fp32_infinite_operand_spares_what_no_tap_reaches(shape, plant, value):
     _same_class_and_value("dshift", pu.to_host(db, None), g["dshift"], pu.TOL["f32"])
 
 
+def test_fp32_tensor_with_more_tiles_than_one_dimension_of_a_launch_holds():
+    """2^27 + 16 pixels of one channel: 2^23 + 1 tiles of 512 threads are more than the 2^32 - 1 threads that a dimension of a
+    launch may have.  All values are small integers and the gradient is zero but for every 4096th pixel, so every result is
+    exact."""
+    n = (1 << 27) + 16
+    desc = B.BlockDesc(1, 16, n // 16, 1, 1, 1, 1, 1, 0, B.SOL_F32, 0)
+    x = (torch.arange(n, device="cuda", dtype=torch.int32) % 7).float().view(1, 16, n // 16, 1)
+    one = lambda v: torch.full((1,), float(v), device="cuda")
+    w, y, dx = one(3).view(1, 1, 1, 1), torch.full_like(x, -1.0), torch.full_like(x, -1.0)
+    B.sol_block_fwd(desc, x, w, one(2), one(5), None, y, None)
+    assert torch.equal(y, 6.0 * x + 5.0)
+    dy = torch.zeros_like(x)
+    dy.view(-1)[::4096] = 1.0
+    dW, ds, db = torch.empty_like(w), one(-1), one(-1)
+    ws = torch.empty(B.sol_block_workspace_bytes(desc, B.SOL_PASS_BWD), dtype=torch.uint8, device="cuda")
+    B.sol_block_bwd(desc, dy, x, w, None, dx, dW, ds, db, one(2), None, None, None, None, ws)
+    assert torch.equal(dx, 6.0 * dy)
+    g = float(x.view(-1)[::4096].double().sum())
+    assert (float(dW), float(ds), float(db)) == (2 * g, 3 * g, float(dy.double().sum()))
+
+
 RAGGED_SHAPES = {
     "8_channels_many_taps_per_slice": dict(N=2, H=9, W=7, C_in=8, C_out=16, K=5, stride=1, pad=2),
     "56_channels_one_short_slice": dict(N=1, H=6, W=11, C_in=56, C_out=8, K=1, stride=1, pad=0, res=True),
