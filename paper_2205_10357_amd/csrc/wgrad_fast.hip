@@ -24,6 +24,12 @@
 
 namespace sol {
 
+// Accumulators per output: consecutive 16-row steps take turns.  The error of a weight gradient is that of its longest chains
+// of fp32 additions, and a launch that splits the reduction less finely has longer ones.  Relative error against 64-bit sums,
+// one chain per output -> two: 3x3 512 -> 512, 2352 pixels (3 splits) 1.42e-7 -> 1.04e-7 (with 4 splits and one chain 1.26e-7);
+// 1x1 1024 -> 256, 1372 pixels 9.9e-8 -> 8.1e-8; 1x1 256 -> 128, 401408 pixels 5.2e-7 -> 3.7e-7; same times.  Two sets take 64
+// registers more; two waves per SIMD (two workgroups per compute unit, gathering form) have 256 each.
+constexpr int WGF_SETS = 2;
 constexpr int WGF_TILE = 128;                 // tile edge along k and along co
 constexpr int WGF_BM = 64;                    // reduction rows per slice
 constexpr int WGF_OPER = WGF_BM * 16;         // 16-byte chunks of one operand tile
@@ -34,7 +40,7 @@ constexpr int WGF_LDW = WGF_TILE + 4;         // fp32 pitch of the output stagin
 // parameter, and the column-sum variant of the loop is chosen once outside it, because every scalar
 // branch inside the slice loop costs a pipeline bubble that a single wave per SIMD cannot hide.
 template <int NS, bool LINEAR>
-__global__ __launch_bounds__(256) void wgrad_fast_kernel(const WgradParams p) {
+__global__ __launch_bounds__(256, 2) void wgrad_fast_kernel(const WgradParams p) {
     HIP_DYNAMIC_SHARED(uintx4, lds)
     constexpr int LPS = 8;                    // async copies per thread and slice (4 x rows + 4 g rows)
 
@@ -132,13 +138,14 @@ __global__ __launch_bounds__(256) void wgrad_fast_kernel(const WgradParams p) {
         goff[f] = mrow * 256 + (((rg >> 3) ^ sw) << 4) + ((rg >> 2) & 1) * 8;
     }
     const bool do_shift = (tk == 0) && (wk == 0);
-    floatx16 acc[2][2], accs[2];
+    // even and odd steps add up in accumulators of their own
+    floatx16 acc[WGF_SETS][2][2], accs[2];
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            acc[a][0][v] = 0.f;
-            acc[a][1][v] = 0.f;
+#pragma unroll
+            for (int s = 0; s < WGF_SETS; ++s) acc[s][a][0][v] = acc[s][a][1][v] = 0.f;
             accs[a][v] = 0.f;
         }
     }
@@ -172,13 +179,14 @@ __global__ __launch_bounds__(256) void wgrad_fast_kernel(const WgradParams p) {
     auto frag = [](const Frags& fr, int i) {
         return __builtin_bit_cast(bf16x8, uintx4{fr.r[2 * i][0], fr.r[2 * i][1], fr.r[2 * i + 1][0], fr.r[2 * i + 1][1]});
     };
-    auto multiply = [&](Frags& fr, auto newer_tag, auto shift_tag) {   // newer_tag: reads issued after fr's that may stay in flight
+    auto multiply = [&](Frags& fr, auto set_tag, auto newer_tag, auto shift_tag) {   // newer_tag: reads issued after fr's that may stay in flight
         lds_tr_wait<decltype(newer_tag)::value>(fr.r[0], fr.r[1], fr.r[2], fr.r[3], fr.r[4], fr.r[5], fr.r[6], fr.r[7]);
+        constexpr int S = decltype(set_tag)::value;
         const bf16x8 x0 = frag(fr, 0), x1 = frag(fr, 1), g0 = frag(fr, 2), g1 = frag(fr, 3);
-        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x0, g0, acc[0][0], 0, 0, 0);
-        acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x0, g1, acc[0][1], 0, 0, 0);
-        acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1, g0, acc[1][0], 0, 0, 0);
-        acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1, g1, acc[1][1], 0, 0, 0);
+        acc[S][0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x0, g0, acc[S][0][0], 0, 0, 0);
+        acc[S][0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x0, g1, acc[S][0][1], 0, 0, 0);
+        acc[S][1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1, g0, acc[S][1][0], 0, 0, 0);
+        acc[S][1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1, g1, acc[S][1][1], 0, 0, 0);
         if constexpr (decltype(shift_tag)::value) {
             accs[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, g0, accs[0], 0, 0, 0);
             accs[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, g1, accs[1], 0, 0, 0);
@@ -195,15 +203,15 @@ __global__ __launch_bounds__(256) void wgrad_fast_kernel(const WgradParams p) {
         issue_frags(fa, xbase, std::integral_constant<int, 0>{});
         issue_frags(fb, xbase, std::integral_constant<int, 1>{});
         if constexpr (MORE) request_part(0);
-        multiply(fa, std::integral_constant<int, 8>{}, shift_tag);
+        multiply(fa, std::integral_constant<int, 0>{}, std::integral_constant<int, 8>{}, shift_tag);
         issue_frags(fa, xbase, std::integral_constant<int, 2>{});
         if constexpr (MORE) request_part(1);
-        multiply(fb, std::integral_constant<int, 8>{}, shift_tag);
+        multiply(fb, std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{}, shift_tag);
         issue_frags(fb, xbase, std::integral_constant<int, 3>{});
         if constexpr (MORE) request_part(2);
-        multiply(fa, std::integral_constant<int, 8>{}, shift_tag);
+        multiply(fa, std::integral_constant<int, 0>{}, std::integral_constant<int, 8>{}, shift_tag);
         if constexpr (MORE) request_part(3);
-        multiply(fb, std::integral_constant<int, 0>{}, shift_tag);
+        multiply(fb, std::integral_constant<int, 1>{}, std::integral_constant<int, 0>{}, shift_tag);
     };
 
     auto run = [&](auto shift_tag) {
@@ -221,6 +229,10 @@ __global__ __launch_bounds__(256) void wgrad_fast_kernel(const WgradParams p) {
     };
     if (do_shift) run(std::true_type{});
     else run(std::false_type{});
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) acc[0][a][b] += acc[1][a][b];
 
     // ---- column sums: row 0 of the ones-product = accumulator element 0 of lanes 0..31 ----------
     if (do_shift && lane < 32) {
@@ -244,7 +256,7 @@ __global__ __launch_bounds__(256) void wgrad_fast_kernel(const WgradParams p) {
             for (int q = 0; q < 4; ++q) {
                 const int kk = wk * 64 + 32 * a + 8 * q + 4 * (lane >> 5);
                 *reinterpret_cast<floatx4*>(stg + col * WGF_LDW + kk) =
-                    floatx4{acc[a][b][4 * q], acc[a][b][4 * q + 1], acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]};
+                    floatx4{acc[0][a][b][4 * q], acc[0][a][b][4 * q + 1], acc[0][a][b][4 * q + 2], acc[0][a][b][4 * q + 3]};
             }
     }
     wait_vm_and_lds<0>();

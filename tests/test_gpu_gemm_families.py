@@ -237,6 +237,29 @@ def test_eight_wave_weight_gradient(shape, splits, sol_env):
         assert np.array_equal(got[key], again[key]), key
 
 
+@pytest.mark.parametrize("wide,chains", [(-1, 2), (1, 4)])
+def test_weight_gradient_adds_in_several_chains(wide, chains, sol_env):
+    """Error of one split of 2048 steps of 16 pixels against 64-bit sums.  A chain of n fp32 additions of random terms has a
+    relative error of c * sqrt(n / 2) with c = 0.62 * 2^-24 (what one chain per output showed here, 0.4 of it the rounding of
+    an addition); the bound lies between the number of chains the kernel has and half of it."""
+    sol_env("SOL_WGRAD_SPLITS", 1)
+    sol_env("SOL_WGRAD_WIDE", wide)
+    n, hw, ci, co = 8, 64, 128, 128
+    g = torch.Generator(device="cuda").manual_seed(242)
+    x = torch.rand(n, hw, hw, ci, generator=g, device="cuda").to(torch.bfloat16)
+    dy = torch.randn(n, hw, hw, co, generator=g, device="cuda").to(torch.bfloat16)
+    W, scale = torch.zeros(co, 1, 1, ci, device="cuda").to(torch.bfloat16), torch.ones(co, device="cuda")
+    d = B.BlockDesc(n, hw, hw, ci, co, 1, 1, 1, 0, B.SOL_BF16, 0)
+    dW, ds, db = torch.empty(co, 1, 1, ci, device="cuda"), torch.empty(co, device="cuda"), torch.empty(co, device="cuda")
+    ws = torch.empty(B.sol_block_workspace_bytes(d, B.SOL_PASS_BWD), dtype=torch.uint8, device="cuda")
+    B.sol_block_bwd(d, dy, x, W, None, None, dW, ds, db, scale, None, None, None, None, ws)
+    ref = dy.view(-1, co).double().t() @ x.view(-1, ci).double()
+    err = float((dW.view(co, ci).double() - ref).norm() / ref.norm())
+    steps = n * hw * hw / 16
+    print(f"error {err:.3g}", flush=True)
+    assert err <= 0.62 * 2.0 ** -24 * np.sqrt(steps / chains / 2) * 2 ** 0.25
+
+
 @pytest.mark.parametrize("masked", [False, True])
 def test_strided_block_adds_to_its_input_gradient_in_place(masked):
     """1x1 / stride 2 with dx as its own addend: the pixels it reaches get the sum, the others stay (or take the mask)."""
