@@ -145,6 +145,11 @@ SOL_API size_t sol_block_bwd_noalloc_limit(void);
  * gradient in the workspace): ask with the descriptor the call will carry. */
 SOL_API size_t sol_block_workspace_bytes(const sol_block_desc* desc, int pass);
 
+/* Bytes of fp32 partial sums (gradient and column sums of every split) that the weight gradient of this
+ * descriptor writes and its reduction reads back; at most what the workspace has room for.  0 if the
+ * descriptor is invalid.  For traffic accounts and for tests of the split.  Host-only. */
+SOL_API size_t sol_block_wgrad_partial_bytes(const sol_block_desc* desc);
+
 /*
  * Launch plans.  The paper tunes every layer on its own when a network is compiled (section "SOL
  * architecture", the auto-tuning of the layer implementations).  Here the library picks tile

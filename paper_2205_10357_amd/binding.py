@@ -17,7 +17,7 @@ SOL_PASS_FWD, SOL_PASS_BWD = 0, 1
 SOL_PLAN_FWD, SOL_PLAN_DGRAD, SOL_PLAN_WGRAD = 0, 1, 2
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libsol_block.so")
-EXPORTS = ("sol_block_fwd", "sol_block_bwd", "sol_block_workspace_bytes", "sol_status_string",
+EXPORTS = ("sol_block_fwd", "sol_block_bwd", "sol_block_workspace_bytes", "sol_block_wgrad_partial_bytes", "sol_status_string",
            "sol_l1_loss_grad", "sol_maxpool_fwd", "sol_block_set_plan", "sol_block_get_plan", "sol_clear_plans",
            "sol_reload_overrides", "sol_block_bwd_noalloc", "sol_block_bwd_noalloc_limit",
            "sol_sequence_create", "sol_sequence_destroy", "sol_sequence_length", "sol_sequence_add_fwd",
@@ -120,6 +120,8 @@ def lib():
         l.sol_trace_kind_name.argtypes = [i32]
         l.sol_block_workspace_bytes.restype = C.c_size_t
         l.sol_block_workspace_bytes.argtypes = [C.POINTER(_CDesc), C.c_int]
+        l.sol_block_wgrad_partial_bytes.restype = C.c_size_t
+        l.sol_block_wgrad_partial_bytes.argtypes = [C.POINTER(_CDesc)]
         l.sol_status_string.restype = C.c_char_p
         l.sol_status_string.argtypes = [C.c_int]
         l.sol_l1_loss_grad.restype = C.c_int
@@ -218,6 +220,11 @@ def sol_reload_overrides() -> None:
 def sol_block_workspace_bytes(desc, pass_: int) -> int:
     d = _cdesc(desc)
     return int(lib().sol_block_workspace_bytes(C.byref(d), int(pass_)))
+
+
+def sol_block_wgrad_partial_bytes(desc) -> int:
+    d = _cdesc(desc)
+    return int(lib().sol_block_wgrad_partial_bytes(C.byref(d)))
 
 
 def sol_block_fwd(desc, x, W, scale, shift, residual, y, ws=None, ws_bytes: Optional[int] = None, stream=None,

@@ -405,6 +405,63 @@ inline bool bf16_vector_shape(const sol_block_desc* d) {
     return d->dtype == SOL_BF16 && (d->C_in % 8) == 0 && (d->C_out % 8) == 0;
 }
 
+// A backward pass of this block masks its gradient in a launch of its own, so that the GEMMs need not.
+inline bool premasks(const sol_block_desc* d, bool smallc) {
+    return (d->flags & SOL_RELU) != 0 && d->dtype == SOL_BF16 && (bf16_vector_shape(d) || smallc) && knob(K_PREMASK, 1) != 0;
+}
+// The weight gradient takes one of the pipelined kernels.
+inline bool pipelined_wgrad(const sol_block_desc* d) {
+    return bf16_vector_shape(d) && ((d->flags & SOL_RELU) == 0 || premasks(d, false)) && knob(K_WGRAD_FAST, 1) != 0;
+}
+
+// Kernel and split of a pipelined weight gradient of `slices` 64-row slices of the reduction and `tiles` 128 x 128 tiles.
+//
+// A split of S costs each workgroup slices / S and the launch, the reduction and the memory between them tiles * S fp32 tiles,
+// so the best S goes with sqrt(slices / tiles).  Measured optima of weight gradient + reduction (7 .. 128 images, 4 .. 144 tiles)
+// lie at S^2 tiles / slices = 18 .. 22 for 1x1 / stride 1 and 20 .. 35 for the gathering form.  1x1 / stride 1 runs three stages
+// deep, one workgroup per compute unit, and leaves an eighth of them to the re-pack that rides along (1x1 2048 -> 512, 2352
+// pixels: 256 workgroups 13.0 us, 192 10.7 us); the gathering form runs two per compute unit.  Before (256 / 512 workgroups
+// whatever the slices are -> now, us of weight gradient + reduction + data gradient): 1x1 512 -> 128, 7436 pixels 23.2 -> 18.5;
+// 3x3 128 -> 128 23.4 -> 19.7; 3x3 256 -> 256, 1372 pixels 30.4 -> 25.8.
+struct WgradChoice {
+    long long splits;
+    bool wide;
+};
+WgradChoice choose_wgrad(long long slices, long long tiles, bool linear, int force_wide) {
+    WgradChoice c{};
+    // 4 T small workgroups re-pack (T = tiles)
+    const long long pack = tiles < 16 ? 2 * tiles : 32;
+    const float ratio = (float)slices / (float)tiles;
+    // Gathering form with a long reduction: one eight-wave workgroup per compute unit instead of two of four waves, i.e. half
+    // the partial tiles, beside the 2 T workgroups that re-pack (32 of them at most wait for their turn).  Weight gradient +
+    // reduction + data gradient, us, four -> eight waves: 3x3 256 -> 256, 12544 pixels (T = 36, L = 196 slices) 44.2 -> 41.6;
+    // 3x3 128 -> 128 (T = 9) L = 392 33.0 -> 30.3, L = 1568 72.5 -> 71.0; 1x1 / stride 2 256 -> 512 (T = 8), L = 1568 149 -> 141.
+    // With few slices the two are equal or four waves ahead (T = 9, L = 117: 19.4 and 19.8; T = 6, L = 130 20.7 and 21.0;
+    // T = 36, L = 22 26.5 and 27.2): the line is between.  Where one workgroup per compute unit leaves more than 96 idle
+    // (T = 144), two splits finer balance better.
+    const long long wide_splits = (256 - pack) / tiles;
+    c.wide = force_wide > 0 ? wide_splits > 0
+                            : !linear && force_wide == 0 && knob(K_WGRAD_TARGET, 0) <= 0 && wide_splits * tiles >= 160 && slices * tiles >= 2048;
+    long long best = (long long)(sqrtf((linear ? 18.f : 34.f) * ratio) + 0.5f);
+    // (the gathering form fills the chip once or twice, not one and a half times)
+    const long long target = knob(K_WGRAD_TARGET, linear ? 256 - pack : (best * tiles <= 384 ? 256 : 512));
+    const long long most = c.wide ? wide_splits : (target + (target > 256 ? tiles / 2 : 0)) / tiles;
+    if (c.wide || best > most) best = most;
+    c.splits = best < 1 ? 1 : best;
+    if (best > 64) {
+        // More than 64 splits cannot ride with the data gradient: a reduction of its own, which takes 4 us and 30 ns per split
+        // more than one that rides along and so wants fewer of them.  It pays where it takes enough slices off each
+        // workgroup, i.e. with few tiles and a long reduction.  Whole call, us, 64 riding -> finer splits: T = 1 (1x1 64 -> 64)
+        // L = 6272 73 -> 47 (254 splits), L = 1568 26.6 -> 25.3 (131), L = 392 14.4 and 16.3 (96); T = 2 (1x1 64 -> 256) L = 6272
+        // 99 -> 92 (126), L = 1568 30.0 and 30.5 (128); 1x1 256 -> 128 L = 6272 167 -> 164, L = 1568 39.0 and 42.8.
+        long long alone = (long long)(sqrtf(11.f * ratio) + 0.5f);
+        if (alone > most) alone = most;
+        const bool pays = alone > 64 && slices / 64 - slices / alone >= 6 + 6 * tiles;
+        c.splits = pays ? alone : 64;
+    }
+    return c;
+}
+
 BwdPlan plan_bwd(const sol_block_desc* d, const Geometry& g) {
     BwdPlan b{};
     int room = 1;                 // splits that the workspace has room for
@@ -417,67 +474,38 @@ BwdPlan plan_bwd(const sol_block_desc* d, const Geometry& g) {
         b.tiles_k = (int)((g.K + 127) / 128);
         b.tiles_c = (d->C_out + 127) / 128;
         const long long tiles = (long long)b.tiles_k * b.tiles_c;
-        const long long max_splits = (g.M + 63) / 64;
-        long long want = knob(K_WGRAD_SPLITS, 0);
-        if (want <= 0) want = installed_plan(d, SOL_PLAN_WGRAD).splits;
-        // (an installed plan or an override of the four-wave kernel's ring depth keeps that kernel)
-        const bool staged = installed_plan(d, SOL_PLAN_WGRAD).stages >= 2 || knob(K_WGRAD_STAGES, 0) >= 2;
-        const int force_wide = staged ? -1 : knob(K_WGRAD_WIDE, 0);
-        if (want > 0) {
-            room = (int)(want < max_splits ? want : max_splits);
-            b.wide = force_wide > 0;
-        } else {
-            // A split of S costs each workgroup L / S slices (L = 64-row slices of the whole reduction) and the launch, the
-            // reduction and the memory between them T * S fp32 tiles, so the best S goes with sqrt(L / T).  Measured
-            // optima of weight gradient + reduction (7 .. 128 images, T = 4 .. 144 tiles) lie at S^2 T / L = 18 .. 22 for
-            // 1x1 / stride 1 and 20 .. 35 for the gathering form.  1x1 / stride 1 runs three stages deep, one workgroup per
-            // compute unit, and leaves an eighth of them to the re-pack that rides along (1x1 2048 -> 512, 2352 pixels:
-            // 256 workgroups 13.0 us, 192 10.7 us); the gathering form runs two per compute unit.  Before (256 / 512
-            // workgroups whatever L is -> now, us of weight gradient + reduction + data gradient): 1x1 512 -> 128, 7436
-            // pixels 23.2 -> 18.5; 3x3 128 -> 128 23.4 -> 19.7; 3x3 256 -> 256, 1372 pixels 30.4 -> 25.8.
-            const bool linear = d->KH == 1 && d->KW == 1 && d->stride == 1 && d->pad == 0;
-            const float slices = (float)((g.M + 63) / 64);
-            // Gathering form with a long reduction: one eight-wave workgroup per compute unit instead of two of four waves, i.e.
-            // half the partial tiles, beside the 2 T workgroups that re-pack (32 of them at most wait for their turn).  Weight
-            // gradient + reduction + data gradient, us, four -> eight waves: 3x3 256 -> 256, 12544 pixels (T = 36, L = 196)
-            // 44.2 -> 41.6; 3x3 128 -> 128 (T = 9) L = 392 33.0 -> 30.3, L = 1568 72.5 -> 71.0; 1x1 / stride 2 256 -> 512 (T = 8),
-            // L = 1568 149 -> 141.  With few slices the two are equal or four waves ahead (T = 9, L = 117: 19.4 and 19.8; T = 6,
-            // L = 130 20.7 and 21.0; T = 36, L = 22 26.5 and 27.2): the line is between.  Where one workgroup per compute unit
-            // leaves more than 96 idle (T = 144), two splits finer balance better.
-            const long long riders = tiles < 16 ? 2 * tiles : 32;
-            const long long wide_splits = (256 - riders) / tiles;
-            b.wide = force_wide > 0 ? wide_splits > 0 : !linear && force_wide == 0 && knob(K_WGRAD_TARGET, 0) <= 0 && wide_splits * tiles >= 160 && slices * (float)tiles >= 2048.f;
-            want = (long long)(sqrtf((linear ? 18.f : 34.f) * slices / (float)tiles) + 0.5f);
-            // (4 T small workgroups re-pack; the gathering form fills the chip once or twice, not one and a half times)
-            const long long pack = tiles < 16 ? 2 * tiles : 32;
-            const long long target = knob(K_WGRAD_TARGET, linear ? 256 - pack : (want * tiles <= 384 ? 256 : 512));
-            const long long most = (target + (target > 256 ? tiles / 2 : 0)) / tiles;
-            if (want > most) want = most;
-            if (b.wide) want = wide_splits;
-            if (want > 64) want = 64;                       // more cannot ride with the data gradient
-            // keep the fp32 partials below ~64 MiB
-            const long long cap = (64LL << 20) / (g.w_elems * 4 > 0 ? g.w_elems * 4 : 1);
-            if (want > cap) want = cap;
-            // The workspace keeps the room of the finest split that was ever asked for (256 workgroups for 1x1 / stride 1, 512
-            // for the gathering form, ranges of 128 rows), so that which calls the no-allocation entry takes does not move
-            // with the split.
-            long long most_room = ((linear ? 256 : 512) + tiles - 1) / tiles;
-            if (most_room > cap) most_room = cap;
-            if (most_room > (g.M + 127) / 128) most_room = (g.M + 127) / 128;
-            if (most_room < 1) most_room = 1;
-            const long long rows = ((g.M + most_room - 1) / most_room + 127) / 128 * 128;
-            room = (int)((g.M + rows - 1) / rows);
+        const sol_plan tuned = installed_plan(d, SOL_PLAN_WGRAD);
+        const bool linear = d->KH == 1 && d->KW == 1 && d->stride == 1 && d->pad == 0;
+        // At most 256 workgroups for 1x1 / stride 1 (one per compute unit) and 512 for the gathering form (two), in ranges of
+        // whole 128 rows, with the fp32 partials below about 64 MiB: what the workspace has room for, whatever the split.  An
+        // installed plan or an override takes the place of the workgroup count.
+        const long long cap = (64LL << 20) / (g.w_elems * 4 > 0 ? g.w_elems * 4 : 1);
+        long long asked = knob(K_WGRAD_SPLITS, 0);
+        if (asked <= 0) asked = tuned.splits;
+        const bool own = asked <= 0;             // the library's choice
+        if (own) {
+            asked = (knob(K_WGRAD_TARGET, linear ? 256 : 512) + tiles - 1) / tiles;
+            if (asked > cap) asked = cap;
         }
-        if (want < 1) want = 1;
-        if (want > max_splits) want = max_splits;
-        long long mps = (g.M + want - 1) / want;
-        mps = (mps + 63) / 64 * 64;
-        b.m_per_split = (int)mps;
-        b.splits = (int)((g.M + mps - 1) / mps);
+        if (asked > (g.M + 127) / 128) asked = (g.M + 127) / 128;
+        if (asked < 1) asked = 1;
+        long long rows = ((g.M + asked - 1) / asked + 127) / 128 * 128;
+        room = (int)((g.M + rows - 1) / rows);
+        // (a ring depth that a plan or an override asks for is the four-wave kernel's)
+        const bool staged = tuned.stages >= 2 || knob(K_WGRAD_STAGES, 0) >= 2;
+        const int force_wide = staged ? -1 : knob(K_WGRAD_WIDE, 0);
+        b.wide = force_wide > 0;
+        if (own && pipelined_wgrad(d)) {
+            const WgradChoice c = choose_wgrad((g.M + 63) / 64, tiles, linear, force_wide);
+            const long long want = c.splits < room ? c.splits : room;
+            b.wide = c.wide;
+            rows = ((g.M + want - 1) / want + 63) / 64 * 64;
+        }
+        b.m_per_split = (int)rows;
+        b.splits = (int)((g.M + rows - 1) / rows);
         b.wpack_off = 0;
         b.part_off = align_up((size_t)g.w_elems * 2);
     }
-    if (room < b.splits) room = b.splits;
     b.dshift_off = b.part_off + align_up((size_t)room * g.w_elems * 4);
     b.total = b.dshift_off + align_up((size_t)room * d->C_out * 4);
     b.smallc = d->dtype == SOL_BF16 && smallc_wgrad_supported(d->C_in, d->C_out, d->KH, d->KW, d->stride) &&
@@ -487,8 +515,7 @@ BwdPlan plan_bwd(const sol_block_desc* d, const Geometry& g) {
         b.sc_part_off = b.total;
         b.total += smallc_wgrad_workspace_bytes(d->N, d->H, d->W, g.Ho, g.Wo);
     }
-    b.premask = (d->flags & SOL_RELU) != 0 && d->dtype == SOL_BF16 && (bf16_vector_shape(d) || b.smallc) &&
-                knob(K_PREMASK, 1) != 0;
+    b.premask = premasks(d, b.smallc);
     if (b.premask) {
         b.gmask_off = b.total;
         b.total += align_up((size_t)g.y_elems * 2);
@@ -689,6 +716,14 @@ SOL_API size_t sol_block_workspace_bytes(const sol_block_desc* desc, int pass) {
     if (pass == SOL_PASS_FWD) return plan_fwd(desc).total;
     if (pass != SOL_PASS_BWD) return 0;
     return plan_bwd(desc, g).total;
+}
+
+SOL_API size_t sol_block_wgrad_partial_bytes(const sol_block_desc* desc) {
+    Geometry g;
+    if (check_desc(desc, &g) != SOL_OK) return 0;
+    const BwdPlan plan = plan_bwd(desc, g);
+    if (plan.smallc && (plan.premask || (desc->flags & SOL_RELU) == 0)) return smallc_wgrad_partial_bytes(plan.sc_parts, (int)g.K);
+    return (size_t)plan.splits * (size_t)(g.w_elems + desc->C_out) * 4;
 }
 
 SOL_API int sol_block_fwd(const sol_block_desc* desc, const void* x, const void* W, const float* scale, const float* shift,

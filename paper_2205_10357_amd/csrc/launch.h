@@ -79,6 +79,7 @@ struct SmallCWgradParams {     // weight gradient of the same layers (dy already
 };
 bool smallc_wgrad_supported(int C_in, int C_out, int KH, int KW, int stride);
 int smallc_wgrad_parts(int N, int Ho, int Wo);
+size_t smallc_wgrad_partial_bytes(int nparts, int K);
 size_t smallc_wgrad_workspace_bytes(int N, int H, int W, int Ho, int Wo);
 hipError_t launch_smallc_wgrad(const SmallCWgradParams& p, hipStream_t stream);
 bool smallc_fwd_supported(int C_in, int C_out, int KH, int KW, int stride);

@@ -622,6 +622,8 @@ int smallc_wgrad_parts(int N, int Ho, int Wo) {
     return (int)(units < 256 ? units : 256);
 }
 
+size_t smallc_wgrad_partial_bytes(int nparts, int K) { return (size_t)nparts * SC_CO * (K + kExtraCols) * 4; }
+
 template <int KH, int CIN>
 static hipError_t launch_smallc_wgrad_kh(const SmallCWgradParams& p, hipStream_t stream) {
     SOL_LAUNCH((smallc_wgrad_kernel<KH, CIN>), dim3(p.nparts), dim3(512), smallc_wgrad_lds_bytes(KH) + SC_CO * KH * p.KW * p.C_in * 2, stream, p);

@@ -168,3 +168,51 @@ def test_trace_kind_names_and_stop_without_start():
     import ctypes as C
     n = C.c_int32(7)
     assert B.lib().sol_trace_stop(None, 0, C.byref(n)) == -4                  # no trace is running
+
+
+def _splits(d):
+    return B.sol_block_wgrad_partial_bytes(d) // (4 * d.C_out * (d.KH * d.KW * d.C_in + 1))
+
+
+@pytest.mark.parametrize("kw,at_least", [
+    (dict(N=128, H=56, W=56, C_in=64, C_out=64, KH=1, KW=1, pad=0), 240),                  # one output tile
+    (dict(N=64, H=56, W=56, C_in=128, C_out=128, KH=1, KW=1, pad=0), 160),
+    (dict(N=128, H=56, W=56, C_in=64, C_out=256, KH=1, KW=1, pad=0), 120),                 # two output tiles
+    (dict(N=64, H=56, W=56, C_in=24, C_out=64), 120),
+    (dict(N=32, H=224, W=224, C_in=3, C_out=32, stride=2), 440),                           # channels no multiple of 8
+    (dict(N=32, H=56, W=56, C_in=20, C_out=20), 196),
+    (dict(N=32, H=56, W=56, C_in=20, C_out=20, flags=0), 196),
+])
+def test_long_reduction_of_a_narrow_layer_fills_the_chip(kw, at_least):
+    """One or two 128 x 128 tiles times the splits are the workgroups of the weight gradient, on 256 compute units."""
+    assert _splits(desc(**kw)) >= at_least
+
+
+def test_weight_gradient_split_stays_within_the_workspace():
+    """The room for partial sums follows from the shape alone (256 workgroups for 1x1 / stride 1, else 512, in ranges of 128
+    rows, at most 64 MiB), and the split never exceeds it; an installed plan's splits are ranges of 128 rows too."""
+    import random
+    rng = random.Random(7)
+    up = lambda v: (v + 255) // 256 * 256
+    for _ in range(3000):
+        ch = lambda: rng.choice([rng.randint(5, 9), 8 * rng.randint(1, 40), 64 * rng.randint(1, 32), rng.randint(5, 300)])
+        k, n, hw, s = rng.choice([1, 1, 3, 5, 7]), int(2 ** rng.uniform(0, 7)), rng.randint(1, 112), rng.choice([1, 2])
+        d = desc(N=n, H=hw, W=hw, C_in=ch(), C_out=ch(), KH=k, KW=k, stride=s, pad=k // 2, flags=0)
+        m, w = n * d.Ho * d.Wo, d.C_out * k * k * d.C_in
+        if max(m * d.C_out, n * hw * hw * d.C_in) > 2 ** 31 - 1:
+            continue
+        tiles = -(-k * k * d.C_in // 128) * -(-d.C_out // 128)
+        want = min(-(-(256 if k == 1 and s == 1 else 512) // tiles), (64 << 20) // (4 * w), -(-m // 128))
+        rows = -(-(-(-m // max(want, 1))) // 128) * 128
+        room = -(-m // rows)
+        assert B.sol_block_workspace_bytes(d, B.SOL_PASS_BWD) == up(2 * w) + up(4 * room * w) + up(4 * room * d.C_out), d
+        assert 1 <= _splits(d) <= room, d
+        if d.C_in % 8 or d.C_out % 8:
+            assert _splits(d) == room, d
+        plan = rng.randint(1, 80)
+        B.sol_block_set_plan(d, B.SOL_PLAN_WGRAD, (-1, 0, plan))
+        try:
+            rows = -(-(-(-m // min(plan, -(-m // 128)))) // 128) * 128
+            assert _splits(d) == -(-m // rows), d
+        finally:
+            B.sol_block_set_plan(d, B.SOL_PLAN_WGRAD, None)

@@ -237,6 +237,20 @@ def test_eight_wave_weight_gradient(shape, splits, sol_env):
         assert np.array_equal(got[key], again[key]), key
 
 
+@pytest.mark.parametrize("shape", [
+    dict(N=32, H=56, W=56, C_in=64, C_out=64, K=1, stride=1, pad=0, res=True),        # one tile, four waves
+    dict(N=43, H=56, W=56, C_in=8, C_out=16, K=3, stride=1, pad=1),                   # one tile, eight waves
+])
+def test_narrow_layer_with_more_splits_than_can_ride(shape):
+    """The library's own split of one output tile and a long reduction: more than 64, so with a reduction of its own."""
+    case = pu.make_case(243, **shape)
+    d = case["d"]
+    desc = B.BlockDesc(d.N, d.H, d.W, d.C_in, d.C_out, d.KH, d.KW, d.stride, d.pad, B.SOL_BF16, 0)
+    assert B.sol_block_wgrad_partial_bytes(desc) > 64 * 4 * d.C_out * (d.KH * d.KW * d.C_in + 1)
+    got = pu.gpu_block(case, premasked=True)
+    pu.check_block(case, got, premasked=True)
+
+
 @pytest.mark.parametrize("wide,chains", [(-1, 2), (1, 4)])
 def test_weight_gradient_adds_in_several_chains(wide, chains, sol_env):
     """Error of one split of 2048 steps of 16 pixels against 64-bit sums.  A chain of n fp32 additions of random terms has a
