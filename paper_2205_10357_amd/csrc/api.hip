@@ -128,7 +128,9 @@ int pick_igemm_tile(const long long* class_rows, int ncls, int Nc) {
 // leaves compute units idle, so that the reduction runs beside the tiles instead of after them.  Returns 0 when
 // fewer than 32 are idle (the reduction then stays a launch of its own).  The two smaller tiles run several workgroups
 // per compute unit in many waves: there the riders fill the launch's tail, one per compute unit at most and no more
-// than there are passes over the rows.  SOL_REDUCE_RIDES: 0 never, n > 1 that many.
+// than there are passes over the rows.  So do those of the tiles that split the reduction, whose launches are short: with as
+// many riders as units are idle, i.e. few, the launch waits for them (1x1 1024 -> 512, 196 pixels 20.2 us, 7.3 with 256).
+// SOL_REDUCE_RIDES: 0 never, n > 1 that many.
 int reduce_rider_blocks(int gemm_wgs, bool small_tile, const ReduceParams* rider) {
     const int forced = knob(K_REDUCE_RIDES, 1);
     if (!rider || forced == 0 || gemm_wgs <= 0 || !reduce_can_ride(*rider)) return 0;
@@ -177,7 +179,7 @@ int tiles_of(const IgemmParams& p, const long long* rows, int bp, int bc) {
 // Four- and eight-wave tiles add a reduction in the same order, the other two families in orders of their own: which
 // family a launch takes depends on its sizes only, not on what rides along.  any_order = false (a plan is installed, even
 // one that does not apply to this launch): four- and eight-wave tiles only.
-GemmChoice choose_gemm(IgemmParams& p, const long long* rows, int tile, const ReduceParams* rider, bool any_order) {
+GemmChoice choose_gemm(IgemmParams& p, const long long* rows, int tile, bool data_gradient, const ReduceParams* rider, bool any_order) {
     long long all_rows = 0, work = 0;
     for (int c = 0; c < p.ncls; ++c) {
         all_rows += rows[c];
@@ -246,7 +248,14 @@ GemmChoice choose_gemm(IgemmParams& p, const long long* rows, int tile, const Re
             const long long e = 2500 + rounds(tiles_of(p, rows, bp, bc)) * (1200 + ((nk * (bp + bc) * 328) >> 8));
             ksplit.offer(GemmChoice{GEMM_KSPLIT, k}, e, e);
         }
-    if (ksplit.alone < plain.alone && ksplit.alone < halo.alone) return ksplit.choice;
+    // A tile whose waves split the reduction fills a compute unit's LDS, so a riding reduction runs after the tiles there and
+    // beside them elsewhere: a data gradient (which carries one as a rule, and takes the same kernel when it does not) takes
+    // such tiles where they save the 5 us of that.  Launch with its reduction, us, splitting tiles -> 64 x 64: 3x3 512 -> 512,
+    // 392 pixels 17.4 and 19.0, 49 pixels 14.2 and 17.3; 3x3 256 -> 256, 196 pixels 10.0 and 11.1, 1372 pixels 10.9 and 11.0; 1x1
+    // 1024 -> 512, 196 pixels 7.3 -> 6.4; 2048 -> 512, 49 pixels 8.0 -> 7.0; 3x3 / stride 2 256 -> 256, 784 pixels 10.5 -> 7.3.  In the
+    // forward pass half a microsecond is what the fits are worth (1x1 / stride 2 256 -> 512, 304 pixels 4.4 -> 4.0).
+    const long long lead = data_gradient ? 5000 : 500;
+    if (ksplit.alone < INT64_MAX && ksplit.alone + lead < plain.alone && ksplit.alone + lead < halo.alone) return ksplit.choice;
     return halo.alone < plain.alone ? halo.choice : plain.choice;
 }
 
@@ -255,7 +264,7 @@ GemmChoice choose_gemm(IgemmParams& p, const long long* rows, int tile, const Re
 // forces the general kernel; SOL_FAST_TILE / SOL_FAST_STAGES override the pipelined kernel's tile and ring depth,
 // SOL_WIDE, SOL_HALO, SOL_KSPLIT = n > 0 force tile n - 1 of those families, -1 switches them off (tuning experiments).
 // `rider`: a split reduction the launch may carry along (see above); *rode tells whether it did.
-int run_igemm(IgemmParams& p, const long long* rows, bool mask, const sol_plan& tuned, hipStream_t stream,
+int run_igemm(IgemmParams& p, const long long* rows, bool mask, bool data_gradient, const sol_plan& tuned, hipStream_t stream,
               const ReduceParams* rider = nullptr, bool* rode = nullptr) {
     if (rode) *rode = false;
     auto attach = [&](bool small_tile) {            // p.total_tiles is final
@@ -337,7 +346,7 @@ int run_igemm(IgemmParams& p, const long long* rows, bool mask, const sol_plan& 
             return launch_igemm_panel(p, stream) == hipSuccess ? SOL_OK : SOL_ERR_LAUNCH;
         }
         if (ragged && tile != 2) tile = 1;
-        choice = free_choice ? choose_gemm(p, rows, tile, knob(K_REDUCE_RIDES, 1) != 0 ? rider : nullptr, tuned.tile < 0) : GemmChoice{GEMM_FAST, tile};
+        choice = free_choice ? choose_gemm(p, rows, tile, data_gradient, knob(K_REDUCE_RIDES, 1) != 0 ? rider : nullptr, tuned.tile < 0) : GemmChoice{GEMM_FAST, tile};
         if (choice.family == GEMM_FAST && choice.tile != tile) {
             tile = choice.tile;
             many_tiles = tile != 2 || tiles_of(p, rows, 64, 64) > 512;      // deep rings of 64 x 64 tiles: two per compute unit
@@ -374,7 +383,7 @@ int run_igemm(IgemmParams& p, const long long* rows, bool mask, const sol_plan& 
     }
     p.total_tiles = tiles_p * p.tiles_c;
     hipError_t e;
-    const bool rides = fast_ok && attach((choice.family == GEMM_FAST && (tile == 1 || tile == 2)) ||
+    const bool rides = fast_ok && attach((choice.family == GEMM_FAST && (tile == 1 || tile == 2)) || choice.family == GEMM_KSPLIT ||
                                          (choice.family == GEMM_HALO && choice.tile == HALO_128x64));
     trace_point(stream, rides ? SOL_TRACE_IGEMM_REDUCE : fast_ok ? SOL_TRACE_IGEMM : SOL_TRACE_IGEMM_GENERAL);
     if (!fast_ok) e = launch_igemm(p, tile, (p.Cs % 8) == 0, mask, stream);
@@ -580,7 +589,7 @@ int fwd_bf16(const sol_block_desc* d, const Geometry& g, const void* x, const vo
     c.tile_begin = 0;
     c.b_off = 0;
     const long long rows[1] = {g.M};
-    return run_igemm(p, rows, false, installed_plan(d, SOL_PLAN_FWD), stream);
+    return run_igemm(p, rows, false, false, installed_plan(d, SOL_PLAN_FWD), stream);
 }
 
 int dgrad_bf16(const sol_block_desc* d, const Geometry& g, const void* dy, const void* ymask, const bf16_t* wpack,
@@ -653,7 +662,7 @@ int dgrad_bf16(const sol_block_desc* d, const Geometry& g, const void* dy, const
         launch_untouched_pixels(dx, addend, addend_mask, dx_mask, d->N, d->H, d->W, d->C_in, d->KH, d->KW, s, d->pad,
                                 stream) != hipSuccess)
         return SOL_ERR_LAUNCH;
-    return run_igemm(p, rows, relu, installed_plan(d, SOL_PLAN_DGRAD), stream, rider, rode);
+    return run_igemm(p, rows, relu, true, installed_plan(d, SOL_PLAN_DGRAD), stream, rider, rode);
 }
 
 }  // namespace
