@@ -904,9 +904,11 @@ static int bwd_common(const sol_block_desc* desc, const void* dy, const void* x,
             if (wgrad_pipelined) {
                 int stages = knob(K_WGRAD_STAGES, 0);
                 if (stages < 2 || stages > 4) stages = installed_plan(desc, SOL_PLAN_WGRAD).stages;
-                if (stages < 2 || stages > 4)
-                    stages = wp.splits * wp.tiles_k * wp.tiles_c <= 256 ||       // one workgroup per compute unit
-                             (desc->KH == 1 && desc->KW == 1 && desc->stride == 1 && desc->pad == 0) ? 3 : 2;
+                if (stages < 2 || stages > 4)           // (a third stage has nothing to hold in ranges of two slices, and its LDS
+                                                        // would keep the workgroups that re-pack from running two at a time:
+                                                        // 3x3 512 -> 512, 49 pixels 14.2 -> 11.4 us)
+                    stages = wp.m_per_split > 128 && (wp.splits * wp.tiles_k * wp.tiles_c <= 256 ||   // one workgroup per compute unit
+                                                      (desc->KH == 1 && desc->KW == 1 && desc->stride == 1 && desc->pad == 0)) ? 3 : 2;
                 trace_point(st, SOL_TRACE_WGRAD);
                 if (plan.wide) {
                     // two tiles of the re-pack at a time per workgroup, on the compute units that the products leave idle

@@ -20,6 +20,7 @@ __device__ __forceinline__ void pack_dgrad_weights_tile(const PackParams& p, int
     constexpr int PITCH = kPackTilePitch;
     const int tid = threadIdx.x & 255;
     const bool exists = b < count;
+    b = exists ? b : 0;
     const int tiles_ci = (p.C_in + 63) >> 6, tiles_co = (p.C_out + 63) >> 6;
     const int tci = b % tiles_ci;
     b /= tiles_ci;
@@ -28,16 +29,21 @@ __device__ __forceinline__ void pack_dgrad_weights_tile(const PackParams& p, int
     const int kh = tap / p.KW, kw = tap - kh * p.KW;
     const int co0 = tco * 64, ci0 = tci * 64;
     const int c8 = tid & 7, r0 = tid >> 3;
+    // (pieces beyond a partial tile read its last ones instead, so that all loads go out before the first is waited for)
+    float sc[2];
+    uintx4 w[2];
+    const int ci = min(ci0 + c8 * 8, p.C_in - 8);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const int co = co0 + r0 + 32 * i;
-        if (!exists || co >= p.C_out || ci0 + c8 * 8 >= p.C_in) continue;
-        const float sc = p.scale[co];
-        const uintx4 v = *reinterpret_cast<const uintx4*>(p.W + (((long long)co * p.KH + kh) * p.KW + kw) * p.C_in +
-                                                           ci0 + c8 * 8);
+        const int co = min(co0 + r0 + 32 * i, p.C_out - 1);
+        sc[i] = p.scale[co];
+        w[i] = *reinterpret_cast<const uintx4*>(p.W + (((long long)co * p.KH + kh) * p.KW + kw) * p.C_in + ci);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const uint32_t pk = pack_bf16x2(sc * __uint_as_float(v[e] << 16), sc * __uint_as_float(v[e] & 0xffff0000u));
+            const uint32_t pk = pack_bf16x2(sc[i] * __uint_as_float(w[i][e] << 16), sc[i] * __uint_as_float(w[i][e] & 0xffff0000u));
             tile[(c8 * 8 + 2 * e) * PITCH + r0 + 32 * i] = (bf16_t)(pk & 0xffffu);
             tile[(c8 * 8 + 2 * e + 1) * PITCH + r0 + 32 * i] = (bf16_t)(pk >> 16);
         }
