@@ -166,12 +166,16 @@ int tiles_of(const IgemmParams& p, const long long* rows, int bp, int bc) {
 // of T workgroups with nk 64-deep slices takes, in ns (fits to launches over the benchmark network's layers at 1 .. 128
 // images, inputs not in L2; 256 compute units):
 //   64 x 64, two per compute unit              3600 + nk * max(200, 153 * ceil(T / 256))
-//   128 x 64, three per compute unit           5000 + nk * max(300, 450 T / 256)
+//   128 x 64, three per compute unit           5000 + nk * max(300, 450 T / 256); 320 for 450 in many tiles of at least nine taps
+//                                              where three tiles of channels share a gather and 128-wide tiles pad a quarter
+//                                              (3x3 128 -> 192, 82369 pixels 62.4 with a neighbourhood in LDS, 50.0; 512 -> 176 189 and 173)
 //   128 x 128, eight waves                     ceil(T / 256) * (5100 + 390 nk)
 //   256 x 128 and 128 x 256, eight waves       ceil(T / 256) * (6500 + 900 nk)
 //   neighbourhood in LDS: 256 x 128            ceil(T / 256) * (8000 + 600 nk)
 //                         128 x 128            ceil(T / 256) * (4200 + 370 nk)
-//                         128 x 64             5000 + nk * max(300, 400 T / 256)
+//                         128 x 64             5000 + nk * max(300, 400 T / 256), where two workgroups fit a compute unit (64
+//                                              source channels or narrow images; alone they lose to the gathering 128 x 64
+//                                              tiles: 3x3 512 -> 64, 76176 pixels 70.5 and 74.5 us, 128 -> 64, 117077 pixels 27.9 and 29.9)
 //   reduction split over the waves             2500 + ceil(T / 256) * (1200 + 1.28 nk (bp + bc))
 // Short reductions (nk < 8) in many tiles are bound by HBM, which the fits do not know: they keep the four-wave tiles
 // (1x1, 401408 pixels, 256 -> 128: 72 us with 128 x 64, 76 us with 256 x 128).  The splitting tiles are for launches that
@@ -215,8 +219,9 @@ GemmChoice choose_gemm(IgemmParams& p, const long long* rows, int tile, bool dat
     auto offer_fast = [&](int t) {
         igemm_fast_tile_shape(t, &bp, &bc);
         const long long n = tiles_of(p, rows, bp, bc), r = rounds(n);
+        const int ns = n >= 1024 && p.Nc > 128 && p.Nc <= 192 && p.Cs > 64 && p.ncls == 1 && p.cls[0].Th * p.cls[0].Tw >= 9 ? 320 : 450;
         const long long e = t == 2 ? 3600 + nk * (153 * r > 200 ? 153 * r : 200)
-                          : t == 1 ? 5000 + nk * (n < 171 ? 300 : (450 * n) >> 8)
+                          : t == 1 ? 5000 + nk * (ns * n < 300 * 256 ? 300 : (ns * n) >> 8)
                                    : r * (5100 + 390 * nk);
         plain.offer(GemmChoice{GEMM_FAST, t}, e, with_rider(e, n, t == 1 || t == 2));
     };
@@ -235,7 +240,8 @@ GemmChoice choose_gemm(IgemmParams& p, const long long* rows, int tile, bool dat
     }
     if (!ragged && any_order && knob(K_HALO, 0) >= 0)
         for (int h = 0; h < HALO_TILES; ++h) {
-            if (!plan_igemm_halo(p, h, &bp, &bc)) continue;
+            size_t lds = 0;
+            if (!plan_igemm_halo(p, h, &bp, &bc, &lds) || (h == HALO_128x64 && lds > 80 * 1024)) continue;
             const long long n = tiles_of(p, rows, bp, bc);
             const long long e = h == HALO_256x128 ? rounds(n) * (8000 + 600 * nk)
                               : h == HALO_128x128 ? rounds(n) * (4200 + 370 * nk)

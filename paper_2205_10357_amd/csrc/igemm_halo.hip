@@ -343,8 +343,8 @@ static hipError_t launch_halo_tile(const IgemmParams& p, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// plans the tile (halo fields of p) and returns whether the launch can take it
-bool plan_igemm_halo(IgemmParams& p, int tile, int* bp, int* bc) {
+// plans the tile (halo fields of p) and returns whether the launch can take it; *lds_bytes: of a workgroup
+bool plan_igemm_halo(IgemmParams& p, int tile, int* bp, int* bc, size_t* lds_bytes) {
     static const int shapes[HALO_TILES][3] = {{256, 128, 64}, {128, 128, 64}, {128, 64, 32}};
     const RowClass& rc = p.cls[0];
     *bp = shapes[tile][0];
@@ -366,6 +366,7 @@ bool plan_igemm_halo(IgemmParams& p, int tile, int* bp, int* bc) {
         case HALO_128x128: lds = halo_lds_bytes<128, 128, 4, 2, 4>(p); break;
         default: lds = halo_lds_bytes<128, 64, 4, 1, 4>(p); break;
     }
+    if (lds_bytes) *lds_bytes = lds;
     return lds <= 160 * 1024;
 }
 

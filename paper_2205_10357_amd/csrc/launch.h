@@ -99,7 +99,7 @@ enum KsplitTile { KSPLIT_16x16 = 0, KSPLIT_16x32, KSPLIT_32x32, KSPLIT_32x64, KS
 hipError_t launch_igemm_ksplit(const IgemmParams& p, int tile, hipStream_t stream);
 void igemm_ksplit_tile_shape(int tile, int* bp, int* bc);
 enum HaloTile { HALO_256x128 = 0, HALO_128x128, HALO_128x64, HALO_TILES };
-bool plan_igemm_halo(IgemmParams& p, int tile, int* bp, int* bc);
+bool plan_igemm_halo(IgemmParams& p, int tile, int* bp, int* bc, size_t* lds_bytes = nullptr);
 hipError_t launch_igemm_halo(const IgemmParams& p, int tile, hipStream_t stream);
 bool igemm_panel_eligible(const IgemmParams& p);
 int plan_igemm_panel(IgemmParams& p, int tiles_per_workgroup);
