@@ -276,7 +276,11 @@ static hipError_t launch_smallc_fwd_kh(const SmallCParams& p, hipStream_t stream
     const long long tiles = (long long)p.N * p.Ho * segs;
     const long long cap = 512;                                 // two workgroups per compute unit
     const int grid = (int)(tiles < cap ? tiles : cap);
-    SOL_LAUNCH((smallc_fwd_kernel<KH, CIN>), dim3(grid), dim3(256), smallc_fwd_lds_bytes(KH), stream, p);
+    const size_t smem = smallc_fwd_lds_bytes(KH);
+    auto kern = smallc_fwd_kernel<KH, CIN>;
+    static std::atomic<size_t> granted{0};
+    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), smem, granted); e != hipSuccess) return e;
+    SOL_LAUNCH(kern, dim3(grid), dim3(256), smem, stream, p);
     return hipGetLastError();
 }
 
@@ -626,7 +630,11 @@ size_t smallc_wgrad_partial_bytes(int nparts, int K) { return (size_t)nparts * S
 
 template <int KH, int CIN>
 static hipError_t launch_smallc_wgrad_kh(const SmallCWgradParams& p, hipStream_t stream) {
-    SOL_LAUNCH((smallc_wgrad_kernel<KH, CIN>), dim3(p.nparts), dim3(512), smallc_wgrad_lds_bytes(KH) + SC_CO * KH * p.KW * p.C_in * 2, stream, p);
+    const size_t smem = smallc_wgrad_lds_bytes(KH) + SC_CO * KH * p.KW * p.C_in * 2;
+    auto kern = smallc_wgrad_kernel<KH, CIN>;
+    static std::atomic<size_t> granted{0};
+    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), smem, granted); e != hipSuccess) return e;
+    SOL_LAUNCH(kern, dim3(p.nparts), dim3(512), smem, stream, p);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     const int ranges = (p.KH * p.KW * p.C_in + 31) / 32 + 1;
     SOL_LAUNCH(smallc_wgrad_reduce_kernel, dim3(SC_CO * ranges), dim3(512), 0, stream, p);

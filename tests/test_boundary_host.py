@@ -170,6 +170,23 @@ def test_trace_kind_names_and_stop_without_start():
     assert B.lib().sol_trace_stop(None, 0, C.byref(n)) == -4                  # no trace is running
 
 
+def test_every_launch_with_dynamic_lds_raises_its_limit():
+    """A kernel with more than 64 KiB of dynamic LDS needs its limit raised first; every launcher that asks for any does so for
+    the very kernel and size it launches."""
+    csrc = os.path.join(ROOT, "paper_2205_10357_amd", "csrc")
+    found = 0
+    for name in sorted(f for f in os.listdir(csrc) if f.endswith(".hip") and f != "loop_model.hip"):
+        text = open(os.path.join(csrc, name)).read()
+        for m in re.finditer(r"SOL_LAUNCH\(((?:\([^()]*\)|[\w<>, ])+?), *(?:dim3\([^;]*?\)|grid), *(?:dim3\([^;]*?\)|block), *([^,;]+?), *\w+, \w+", text):
+            kern, smem = m.group(1).strip(), m.group(2).strip()
+            if smem == "0":
+                continue
+            found += 1
+            before = text[:m.start()].rstrip().splitlines()[-3:]
+            assert any(f"ensure_dynamic_lds(reinterpret_cast<const void*>({kern}), {smem}, granted)" in l for l in before), (name, m.group(0))
+    assert found >= 11
+
+
 def _splits(d):
     return B.sol_block_wgrad_partial_bytes(d) // (4 * d.C_out * (d.KH * d.KW * d.C_in + 1))
 
