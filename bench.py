@@ -13,8 +13,9 @@ Prints ONE JSON line.
                         (the library's launch trace) after the timed region: microseconds, flops, bytes every
                         operand read / result written once, and the fraction of the roofline that binds it
                         (bf16 MFMA peak or HBM bandwidth).
-  roofline              the dominant kernel (the pipelined bf16 MFMA implicit-GEMM kernel that serves forward
-                        and data gradient): flops of ALL its launches of a step over the sum of their times.
+  roofline              the pipelined bf16 MFMA implicit-GEMM kernels that serve forward and data gradient: flops of ALL
+                        their launches of a step over the sum of their times; `kernel` names those that ran, the one
+                        with the most time first, `by_kernel` has the figures of each.
   regimes               step time with the loss-gradient kernel taken out, and in the cold regime (buffer sets
                         rotated so that the working set exceeds the 256 MB memory-side cache).
   host_enqueue_us       host time to issue one step (no synchronisation), per launch mode.
@@ -33,6 +34,10 @@ if ROOT not in sys.path:
 
 MFMA_BF16_PEAK_TFLOPS = 2500.0      # MI355X dense bf16 MFMA peak
 HBM_PEAK_GBS = 8000.0               # MI355X HBM3E peak
+# launch-trace kinds of the pipelined implicit GEMMs (with or without a riding reduction) and their kernels
+PIPELINED_KERNELS = {"implicit GEMM (pipelined)": "igemm_fast_kernel", "implicit GEMM (eight waves)": "igemm_wide_kernel",
+                     "implicit GEMM (neighbourhood in LDS)": "igemm_halo_kernel",
+                     "implicit GEMM (waves split the reduction)": "igemm_ksplit_kernel"}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "dominant_kernel_traffic.json")
 
 
@@ -100,17 +105,18 @@ def cpu_baseline(wl_factory, images: int):
     return wl.flops_step() / dt / 1e12, dt, orc.num_threads()
 
 
-def stored_traffic(workload: str, n: int):
-    """HBM bytes per launch of the dominant kernel's largest launch, from the counter passes summarised in
-    profiles/ (written by `python -m paper_2205_10357_amd.profile_summary`), or None when there is no figure for
-    this workload or the kernel sources have changed since it was taken."""
+def stored_traffic(workload: str, n: int, kernel: str):
+    """HBM bytes of the largest pipelined launch, from the counter passes summarised in profiles/ (written by
+    `python -m paper_2205_10357_amd.profile_summary`), or None when there is no figure for this workload and kernel or
+    the kernel sources have changed since it was taken."""
     try:
         with open(TRAFFIC_FILE) as f:
             rec = json.load(f)
     except (OSError, ValueError):
         return None
     from paper_2205_10357_amd.profile_summary import source_digest
-    if rec.get("workload") != workload or rec.get("global_batch") != n or rec.get("source_digest") != source_digest():
+    if rec.get("workload") != workload or rec.get("global_batch") != n or \
+            not str(rec.get("kernel", "")).startswith(kernel) or rec.get("source_digest") != source_digest():
         return None
     return rec.get("hbm_bytes_per_launch")
 
@@ -277,28 +283,32 @@ def main():
     trace = B.sol_trace_stop(points)
     torch.cuda.synchronize()
     table = per_launch_table(trace, wl, seq, B, trace_steps)
-    dom = [r for r in table if r["kernel"].startswith("implicit GEMM (pipelined)")]
+    base = lambda r: r["kernel"].replace(" + split reduction", "")
+    dom = [r for r in table if base(r) in PIPELINED_KERNELS]
     if dom:
-        dom_flops = sum(r["gflop"] for r in dom) * 1e9
-        dom_us = sum(r["us"] for r in dom)
-        achieved = dom_flops / (dom_us * 1e-6) / 1e12
+        def rate(rows):
+            fl, us = sum(r["gflop"] for r in rows) * 1e9, sum(r["us"] for r in rows)
+            return {"launches_per_step": len(rows), "sum_us": round(us, 2), "achieved": round(fl / (us * 1e-6) / 1e12, 2),
+                    "frac": round(fl / (us * 1e-6) / 1e12 / MFMA_BF16_PEAK_TFLOPS, 4)}
+
+        by_kernel = {k: [r for r in dom if base(r) == k] for k in {base(r) for r in dom}}
+        order = sorted(by_kernel, key=lambda k: -sum(r["us"] for r in by_kernel[k]))
+        total = rate(dom)
         big = max(dom, key=lambda r: r["gflop"])
-        roofline = {"bound": "mfma", "achieved": round(achieved, 2), "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
-                    "frac": round(achieved / MFMA_BF16_PEAK_TFLOPS, 4),
-                    "traffic": stored_traffic(wl.name, n), "traffic_unit": "HBM bytes of the largest launch",
-                    "kernel": "igemm_fast_kernel", "launches_per_step": len(dom),
-                    "flop_per_step_in_kernel": dom_flops, "avg_us": round(dom_us / len(dom), 3),
-                    "sum_us": round(dom_us, 2),
-                    "largest_launch": {"launch": big["launch"], "us": big["us"], "algorithmic_bytes": big["bytes"],
-                                       "frac": round(big["pct_mfma_peak"] / 100, 4)}}
+        roofline = {"bound": "mfma", "achieved": total["achieved"], "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
+                    "frac": total["frac"], "traffic": stored_traffic(wl.name, n, PIPELINED_KERNELS[base(big)]),
+                    "traffic_unit": "HBM bytes of the largest launch",
+                    "kernel": " + ".join(PIPELINED_KERNELS[k] for k in order), "launches_per_step": len(dom),
+                    "flop_per_step_in_kernel": sum(r["gflop"] for r in dom) * 1e9,
+                    "avg_us": round(sum(r["us"] for r in dom) / len(dom), 3), "sum_us": total["sum_us"],
+                    "by_kernel": [{"kernel": PIPELINED_KERNELS[k], **rate(by_kernel[k])} for k in order],
+                    "largest_launch": {"launch": big["launch"], "kernel": PIPELINED_KERNELS[base(big)], "us": big["us"],
+                                       "algorithmic_bytes": big["bytes"], "frac": round(big["pct_mfma_peak"] / 100, 4)}}
         # the same figure over the launches that only multiply (the others also carry a split reduction, whose time
         # is in `achieved` above but whose work is bytes, not flops)
-        plain = [r for r in dom if r["kernel"] == "implicit GEMM (pipelined)"]
+        plain = [r for r in dom if not r["kernel"].endswith("+ split reduction")]
         if plain and len(plain) < len(dom):
-            pf, pu = sum(r["gflop"] for r in plain) * 1e9, sum(r["us"] for r in plain)
-            roofline["launches_without_riding_reduction"] = {
-                "launches_per_step": len(plain), "sum_us": round(pu, 2), "achieved": round(pf / (pu * 1e-6) / 1e12, 2),
-                "frac": round(pf / (pu * 1e-6) / 1e12 / MFMA_BF16_PEAK_TFLOPS, 4)}
+            roofline["launches_without_riding_reduction"] = rate(plain)
     else:
         roofline = None
     loss_us = sum(r["us"] for r in table if r["kernel"] == "L1-loss gradient")

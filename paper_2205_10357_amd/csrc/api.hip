@@ -391,7 +391,9 @@ int run_igemm(IgemmParams& p, const long long* rows, bool mask, bool data_gradie
     hipError_t e;
     const bool rides = fast_ok && attach((choice.family == GEMM_FAST && (tile == 1 || tile == 2)) || choice.family == GEMM_KSPLIT ||
                                          (choice.family == GEMM_HALO && choice.tile == HALO_128x64));
-    trace_point(stream, rides ? SOL_TRACE_IGEMM_REDUCE : fast_ok ? SOL_TRACE_IGEMM : SOL_TRACE_IGEMM_GENERAL);
+    static const int kinds[][2] = {{SOL_TRACE_IGEMM, SOL_TRACE_IGEMM_REDUCE}, {SOL_TRACE_IGEMM_WIDE, SOL_TRACE_IGEMM_WIDE_REDUCE},
+                                   {SOL_TRACE_IGEMM_KSPLIT, SOL_TRACE_IGEMM_KSPLIT_REDUCE}, {SOL_TRACE_IGEMM_HALO, SOL_TRACE_IGEMM_HALO_REDUCE}};
+    trace_point(stream, fast_ok ? kinds[choice.family][rides] : SOL_TRACE_IGEMM_GENERAL);
     if (!fast_ok) e = launch_igemm(p, tile, (p.Cs % 8) == 0, mask, stream);
     else if (choice.family == GEMM_WIDE) e = launch_igemm_wide(p, choice.tile, stream);
     else if (choice.family == GEMM_HALO) e = launch_igemm_halo(p, choice.tile, stream);

@@ -114,6 +114,12 @@ SOL_API const char* sol_trace_kind_name(int32_t kind) {
         case SOL_TRACE_IGEMM_PANEL: return "implicit GEMM (pixel panel in LDS)";
         case SOL_TRACE_IGEMM_REDUCE: return "implicit GEMM (pipelined) + split reduction";
         case SOL_TRACE_IGEMM_PANEL_REDUCE: return "implicit GEMM (pixel panel in LDS) + split reduction";
+        case SOL_TRACE_IGEMM_WIDE: return "implicit GEMM (eight waves)";
+        case SOL_TRACE_IGEMM_WIDE_REDUCE: return "implicit GEMM (eight waves) + split reduction";
+        case SOL_TRACE_IGEMM_HALO: return "implicit GEMM (neighbourhood in LDS)";
+        case SOL_TRACE_IGEMM_HALO_REDUCE: return "implicit GEMM (neighbourhood in LDS) + split reduction";
+        case SOL_TRACE_IGEMM_KSPLIT: return "implicit GEMM (waves split the reduction)";
+        case SOL_TRACE_IGEMM_KSPLIT_REDUCE: return "implicit GEMM (waves split the reduction) + split reduction";
         case SOL_TRACE_WGRAD: return "weight-gradient GEMM (pipelined)";
         case SOL_TRACE_WGRAD_GENERAL: return "weight-gradient GEMM (general)";
         case SOL_TRACE_WGRAD_REDUCE: return "split reduction";

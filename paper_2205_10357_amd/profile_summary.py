@@ -14,7 +14,7 @@ e.g. the max-pool of the inference schedule) and summarised per position.  Comma
 
 `traffic` scales the two counters by what they read for the plain 256 MiB device copies that
 `bench.py --copy-calibration` runs first in the same process, and stores the HBM bytes of the
-dominant kernel's largest launch together with a digest of the kernel's sources: bench.py
+largest pipelined implicit-GEMM launch together with a digest of the kernels' sources: bench.py
 quotes the figure only while that digest still matches.
 """
 from __future__ import annotations
@@ -30,15 +30,16 @@ import statistics
 from collections import defaultdict
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCES = ("igemm_fast.hip", "reduce_rows.h", "api.hip", "common.h")
+KERNEL_SOURCES = ("igemm_fast.hip", "igemm_wide.hip", "igemm_halo.hip", "igemm_ksplit.hip", "igemm_gather.h", "reduce_rows.h", "api.hip",
+                  "common.h")
 COPY_KERNEL = "__amd_rocclr_copyBuffer"
 COPY_BYTES = 256 << 20
 ANCHOR = "l1_grad_kernel"
-DOMINANT = "igemm_fast_kernel"
+PIPELINED = ("igemm_fast_kernel", "igemm_wide_kernel", "igemm_halo_kernel", "igemm_ksplit_kernel")
 
 
 def source_digest() -> str:
-    """Digest of the sources that decide what the dominant kernel does and how it is launched."""
+    """Digest of the sources that decide what the pipelined implicit GEMMs do and how they are launched."""
     h = hashlib.sha256()
     for name in KERNEL_SOURCES:
         with open(os.path.join(HERE, "csrc", name), "rb") as f:
@@ -144,10 +145,8 @@ def cmd_traffic(args) -> None:
         fb, wb = f * fscale * 1024, w * wscale * 1024
         tf, tw = tf + fb, tw + wb
         lines.append(f"| {pos + 1} | {k} | {wgs} | {f:.0f} | {fb / 1e6:.1f} | {w:.0f} | {wb / 1e6:.1f} |")
-        # the dominant kernel's largest launch: first launch of that kernel with the most traffic-independent work
-        # is the 3x3 forward = the second launch of the step for the bottleneck; identified as the dominant-kernel
-        # launch at the lowest position among those with the fewest fetched bytes per workgroup is fragile, so the
-        # position is given explicitly
+        # the largest pipelined launch (for the bottleneck the 3x3 forward, the second launch of the step) cannot be told
+        # from the counters: its position is given
         if args.position and pos + 1 == args.position:
             best = (k, fb + wb)
     lines += ["", f"Step total: fetched {tf / 1e6:.0f} MB, written {tw / 1e6:.0f} MB."]
@@ -157,8 +156,8 @@ def cmd_traffic(args) -> None:
             f.write(text + "\n")
     print(text)
     if args.json and best is not None:
-        if DOMINANT not in best[0]:
-            raise SystemExit(f"position {args.position} is {best[0]}, not {DOMINANT}")
+        if not best[0].startswith(PIPELINED):
+            raise SystemExit(f"position {args.position} is {best[0]}, none of {PIPELINED}")
         rec = {"workload": args.workload, "global_batch": args.batch, "kernel": best[0], "step_position": args.position,
                "hbm_bytes_per_launch": round(best[1]), "fetch_scale": round(fscale, 4), "write_scale": round(wscale, 4),
                "step_fetched_bytes": round(tf), "step_written_bytes": round(tw), "source_digest": source_digest()}
@@ -199,7 +198,7 @@ def cmd_bench_table(args) -> None:
     r = rec.get("roofline")
     if r:
         big = r["largest_launch"]
-        lines += ["", f"`roofline` of that bench line: dominant kernel {r['kernel']}, all {r['launches_per_step']} launches of a step "
+        lines += ["", f"`roofline` of that bench line: {r['kernel']}, all {r['launches_per_step']} launches of a step "
                       f"({r['flop_per_step_in_kernel'] / 1e9:.1f} GFLOP in {r['sum_us']} us): achieved {r['achieved']} {r['unit']}, "
                       f"frac {r['frac']}; largest launch {big['launch']}: {big['us']} us, frac {big['frac']}; traffic {r['traffic']}."]
     text = "\n".join(lines)
@@ -235,7 +234,7 @@ def main() -> None:
     m.add_argument("write_dir")
     m.add_argument("--workload", required=True)
     m.add_argument("--batch", type=int, required=True)
-    m.add_argument("--position", type=int, default=0, help="1-based position in the step of the dominant kernel's largest launch")
+    m.add_argument("--position", type=int, default=0, help="1-based position in the step of the largest pipelined implicit-GEMM launch")
     m.add_argument("--out")
     m.add_argument("--json")
     m.set_defaults(fn=cmd_traffic)

@@ -164,6 +164,10 @@ def test_prepared_sequence_records_on_the_host_and_reports_the_failing_call():
 def test_trace_kind_names_and_stop_without_start():
     names = {B.sol_trace_kind_name(k) for k in range(0, 18)}
     assert len(names) == 18 and "unknown" not in names
+    gemms = {B.sol_trace_kind_name(k) for k in range(18, 24)}                 # a kind per family, without and with a reduction
+    assert len(gemms | names) == 24 and "unknown" not in gemms
+    assert sum(g.endswith(" + split reduction") and g.replace(" + split reduction", "") in gemms for g in gemms) == 3
+    assert B.sol_trace_kind_name(24) == "unknown"
     assert B.sol_trace_kind_name(99) == "unknown"
     import ctypes as C
     n = C.c_int32(7)
