@@ -238,7 +238,7 @@ GemmChoice choose_gemm(IgemmParams& p, const long long* rows, int tile, bool dat
             plain.offer(GemmChoice{GEMM_WIDE, w}, e, with_rider(e, n, false));
         }
     }
-    if (!ragged && any_order && knob(K_HALO, 0) >= 0)
+    if (!ragged && any_order && knob(K_HALO, 0) == 0)
         for (int h = 0; h < HALO_TILES; ++h) {
             size_t lds = 0;
             if (!plan_igemm_halo(p, h, &bp, &bc, &lds) || (h == HALO_128x64 && lds > 80 * 1024)) continue;
@@ -268,7 +268,8 @@ GemmChoice choose_gemm(IgemmParams& p, const long long* rows, int tile, bool dat
 // Fills tile-dependent fields of the launch (tile counts, class offsets) and launches either a pipelined kernel (channel
 // counts multiples of 8, no mask on the gathered operand) or the general one.  SOL_IGEMM_FAST=0
 // forces the general kernel; SOL_FAST_TILE / SOL_FAST_STAGES override the pipelined kernel's tile and ring depth,
-// SOL_WIDE, SOL_HALO, SOL_KSPLIT = n > 0 force tile n - 1 of those families, -1 switches them off (tuning experiments).
+// SOL_WIDE, SOL_HALO, SOL_KSPLIT = n > 0 force tile n - 1 of those families, -1 switches them off (tuning experiments); a
+// launch that the forced neighbourhood tile cannot serve takes another family.
 // `rider`: a split reduction the launch may carry along (see above); *rode tells whether it did.
 int run_igemm(IgemmParams& p, const long long* rows, bool mask, bool data_gradient, const sol_plan& tuned, hipStream_t stream,
               const ReduceParams* rider = nullptr, bool* rode = nullptr) {

@@ -22,6 +22,32 @@ SHAPES = {
 }
 
 
+KINDS = {"SOL_WIDE": "eight waves", "SOL_HALO": "neighbourhood in LDS", "SOL_KSPLIT": "waves split the reduction", "SOL_FAST_STAGES": "pipelined"}
+
+
+def halo_serves(tile, W, C, K):
+    """Whether a 3x3 / 5x5 "same" launch over C source channels and rows of W pixels fits the neighbourhood tile: two channel
+    slices of its pixels (one for 64 channels), a ring of four weight slices and a row of zeros in 160 KiB, and the copies of
+    the next slice's pixels done two taps before it, at most two per tap.  (Two per tap occur with 128 x 64 tiles only: eight
+    copies of the others do not fit.)"""
+    bp, bc, per_copy = {1: (256, 128, 64), 2: (128, 128, 64), 3: (128, 64, 32)}[tile]
+    copies = -(-(bp + (K - 1) * (W + 1)) // per_copy)
+    lds = 4 * bc * 128 + 128 + (2 if C > 64 else 1) * copies * per_copy * 128
+    return lds <= 160 * 1024 and (C == 64 or copies <= 2 * (K * K - 2))
+
+
+def check_family(family, n, d, kinds):
+    """The launch trace names the forced family for the forward launch and, where its channels allow, the data gradient."""
+    gemms = [k for k in kinds if k.startswith("implicit GEMM")]
+    assert len(gemms) == 2, kinds
+    for kind, channels in zip(gemms, (d.C_in, d.C_out)):
+        serves = family in ("SOL_KSPLIT", "SOL_FAST_STAGES") or channels % 64 == 0
+        if family == "SOL_HALO":
+            serves = serves and halo_serves(n, d.W, channels, d.KH)
+        assert (f"({KINDS[family]})" in kind) == serves, (kind, channels)
+    return gemms
+
+
 def run_forced(shape, family, n, sol_env, rides=False):
     sol_env(family, n)
     case = pu.make_case(211, **SHAPES[shape])
@@ -31,7 +57,11 @@ def run_forced(shape, family, n, sol_env, rides=False):
     if rides:
         sol_env("SOL_REDUCE_RIDES", 3)
     print(f"[{family}={n}] {shape}", flush=True)
+    B.sol_trace_start(64)
     got = pu.gpu_block(case, addend=ad, dx_mask=dxm, premasked=True)
+    kinds = [B.sol_trace_kind_name(k) for k, _, _, _ in B.sol_trace_stop(64)]
+    if family in KINDS and int(n) > 0:
+        check_family(family, int(n), case["d"], kinds)
     pu.check_block(case, got, addend=ad, dx_mask=dxm, premasked=True)
     return got
 
@@ -65,13 +95,15 @@ HALO_SHAPES = {
     "two_copies_per_slice": dict(N=1, H=6, W=56, C_in=128, C_out=128, K=3, stride=1, pad=1, res=True),
     "wide_rows": dict(N=1, H=4, W=61, C_in=128, C_out=64, K=3, stride=1, pad=1),
     "5x5": dict(N=2, H=9, W=11, C_in=128, C_out=72, K=5, stride=1, pad=2),
+    "widest_rows_of_the_256_pixel_tile": dict(N=2, H=11, W=31, C_in=128, C_out=192, K=3, stride=1, pad=1),
+    "one_pixel_too_wide_for_it": dict(N=1, H=9, W=32, C_in=192, C_out=128, K=3, stride=1, pad=1),
 }
 
 
 @pytest.mark.parametrize("tile", [1, 2, 3])
 @pytest.mark.parametrize("shape", list(HALO_SHAPES), ids=list(HALO_SHAPES))
 def test_tiles_that_keep_the_neighbourhood(shape, tile, sol_env):
-    """Forward and data gradient, again with riding reductions; bits repeat."""
+    """Forward and data gradient, again with riding reductions; bits repeat.  Rows too wide for a tile take another family."""
     SHAPES[shape] = HALO_SHAPES[shape]
     a = run_forced(shape, "SOL_HALO", tile, sol_env)
     b = run_forced(shape, "SOL_HALO", tile, sol_env, rides=True)
