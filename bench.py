@@ -148,8 +148,7 @@ def launch_costs(wl, seq, B):
             per_pixel = 1 + (c["addend"] is not None) + (c["addend"] is not None and c.get("addend_mask") is not None) + \
                 (c["dx_mask"] is not None)
             costs[("fill", b.layer)] = (0, int(frac * x_b * per_pixel), "dx (+ addend) (+ masks) on the untouched pixels")
-        ws = B.sol_block_workspace_bytes(c["desc"], B.SOL_PASS_BWD)
-        part = max(0, ws - w_el * 2)                       # fp32 partial tiles of the split (the rest: packed weights)
+        part = B.sol_block_wgrad_partial_bytes(c["desc"])  # fp32 partial tiles and column sums of the split
         costs[("wgrad", b.layer)] = (fl, y_b + x_read + part + w_el * 4, "dy + x + partials + packed W written")
         costs[("reduce", b.layer)] = (0, part + w_el * 2 + w_el * 4, "partials + W + dW")
     for o in wl.ops:

@@ -140,3 +140,26 @@ def test_backward_visits_a_sparse_strided_reader_after_the_dense_one():
             assert names.index(r.name) < names.index(o.name)
     head = [wl.ConvBlock("head", 256, 256, 1, 1, 0, True, 99, 0, None, 99)]
     assert order_of(head + ops)[1] == [o.name for o in reversed(head + ops)]
+
+
+def test_bench_counts_the_partial_sums_that_move():
+    """Bytes of the weight gradient and its reduction in bench.py's table: the fp32 partial sums of the split that runs, not the
+    room that the workspace keeps for the finest one."""
+    import types
+
+    import bench
+    from paper_2205_10357_amd import binding as B
+    from paper_2205_10357_amd import workloads as wl
+
+    w = wl.bottleneck14_bf16(n=64)
+    shp = w.tensor_shapes()
+    calls = []
+    for o in w.conv_blocks():
+        _, h, wd = shp[o.inp]
+        calls.append(dict(op=o, desc=B.BlockDesc(64, h, wd, o.c_in, o.c_out, o.k, o.k, o.stride, o.pad, B.SOL_BF16, 0), addend=None, dx_mask=None))
+    costs = bench.launch_costs(w, types.SimpleNamespace(_bwd_calls=calls), B)
+    for c in calls:
+        o, n_w = c["op"], c["op"].c_out * c["op"].k ** 2 * c["op"].c_in
+        part = costs[("reduce", o.layer)][1] - 6 * n_w
+        assert part == B.sol_block_wgrad_partial_bytes(c["desc"]) and part % (4 * (n_w + o.c_out)) == 0
+        assert part <= B.sol_block_workspace_bytes(c["desc"], B.SOL_PASS_BWD) - 2 * n_w
