@@ -171,6 +171,14 @@ SOL_API size_t sol_block_wgrad_partial_bytes(const sol_block_desc* desc);
  * data gradient have the same bits under every tile and depth (the library's own choice may be a kernel
  * that adds the fp32 products in another order), the weight gradient differs in the order of its fp32
  * partial sums.  Host-only calls, safe from any thread (a small table behind a mutex).
+ *
+ * Bits and batch sizes.  Left to itself the library also picks, from the size of the whole launch, the
+ * order in which the fp32 products of an output are added (taps outside channels, channels outside taps,
+ * or one partial sum per wave).  Runs repeat bit for bit, and so does a call split in its two branches,
+ * but one image may come out in different bits -- with the same accuracy -- in batches of different size.
+ * A caller that needs an image's forward result and data gradient to be the same bits in every batch
+ * installs a plan with tile >= 0 for each of its shapes and passes, or sets SOL_HALO=-1 and SOL_KSPLIT=-1 in
+ * the environment: every launch then adds in the first of the three orders.
  */
 enum { SOL_PLAN_FWD = 0, SOL_PLAN_DGRAD = 1, SOL_PLAN_WGRAD = 2 };
 typedef struct {

@@ -8,9 +8,12 @@ distinct layer shape is timed with each candidate plan, using the sequencer's ow
 and the fastest is installed with ``sol_block_set_plan`` when it beats the library's choice
 by a margin.  A sweep takes well under a second per layer shape.
 
-Only speed depends on a plan (see the header: forward and data gradient are plan-independent
-bit for bit, the weight gradient differs in the order of its fp32 partial sums).  The timed
-calls overwrite the sequencer's activations and gradients: run a step afterwards.
+Only speed and rounding depend on a plan: forward and data gradient have the same bits under every
+installed tile and depth, while the library's own choice may be a kernel that adds the fp32 products
+in another order (eight-wave, neighbourhood and reduction-splitting tiles are its choice only: a plan
+cannot name them, and an installed tile rules the last two out); the weight gradient differs in the
+order of its fp32 partial sums.  The timed calls overwrite the sequencer's activations and gradients:
+run a step afterwards.
 """
 from __future__ import annotations
 

@@ -336,3 +336,38 @@ def test_pointwise_launches_around_the_resident_tile_lines(shape):
     case = pu.make_case(251, **shape)
     got = pu.gpu_block(case, premasked=True)
     pu.check_block(case, got, premasked=True)
+
+
+@pytest.mark.parametrize("how", ["plan", "environment"])
+@pytest.mark.parametrize("layer", [dict(C_in=256, C_out=256, K=3, stride=1, pad=1), dict(C_in=1024, C_out=256, K=1, stride=1, pad=0),
+                                   dict(C_in=72, C_out=104, K=3, stride=2, pad=1), dict(C_in=64, C_out=256, K=1, stride=1, pad=0)])
+def test_image_has_the_same_bits_in_every_batch_on_request(layer, how, sol_env):
+    """With a plan for the shape, or the two families of other orders switched off, the first image's forward result and data
+    gradient do not depend on the batch it is in."""
+    big = pu.make_case(261, N=33, H=14, W=14, res=True, **layer)
+    if how == "environment":
+        sol_env("SOL_HALO", -1)
+        sol_env("SOL_KSPLIT", -1)
+    out = {}
+    try:
+        for n in (1, 5, 33):
+            case = dict(big, d=pu.orc.Desc(n, 14, 14, layer["C_in"], layer["C_out"], layer["K"], layer["K"], layer["stride"], layer["pad"], True),
+                        **{k: big[k][:n] for k in ("x", "res", "t")})
+            d = case["d"]
+            desc = B.BlockDesc(d.N, d.H, d.W, d.C_in, d.C_out, d.KH, d.KW, d.stride, d.pad, B.SOL_BF16, B.SOL_RELU)
+            if how == "plan":
+                for which in (B.SOL_PLAN_FWD, B.SOL_PLAN_DGRAD):
+                    B.sol_block_set_plan(desc, which, (1 if n == 5 else 2, 0, 0))
+            # (the loss gradient depends on the batch by its 1 / numel: the stored output serves as dy instead)
+            x, w, t = pu.to_dev(case["x"], True), pu.to_dev(case["w"], True), pu.to_dev(case["res"], True)
+            scale, shift = pu.vec_dev(case["scale"]), pu.vec_dev(case["shift"])
+            y, dx = torch.empty_like(t), torch.empty_like(x)
+            ws = torch.empty(B.sol_block_workspace_bytes(desc, B.SOL_PASS_BWD), dtype=torch.uint8, device="cuda")
+            B.sol_block_fwd(desc, x, w, scale, shift, t, y, None)
+            B.sol_block_bwd(desc, y, x, w, y, dx, None, None, None, scale, None, None, None, None, ws)
+            torch.cuda.synchronize()
+            out[n] = (y[0].clone(), dx[0].clone())
+    finally:
+        B.sol_clear_plans()
+    for n in (5, 33):
+        assert torch.equal(out[n][0], out[1][0]) and torch.equal(out[n][1], out[1][1]), n
