@@ -142,7 +142,11 @@ SOL_API size_t sol_block_bwd_noalloc_limit(void);
 /* Bytes of caller-provided scratch the given pass needs for this descriptor (0 if the
  * descriptor is invalid: the pass itself then reports the error).  The answer depends on every
  * field of the descriptor, flags included (a backward pass that masks dy itself keeps the masked
- * gradient in the workspace): ask with the descriptor the call will carry. */
+ * gradient in the workspace): ask with the descriptor the call will carry.  The answer is a bound that
+ * stays where it is when kernels change, so that calls keep their workspaces and stay on their side of
+ * the no-allocation limit; the present kernels leave parts of it unused (all of it in the forward pass
+ * of layers with few channels, an image's worth in their weight gradient, partial sums of splits coarser
+ * than the finest). */
 SOL_API size_t sol_block_workspace_bytes(const sol_block_desc* desc, int pass);
 
 /* Bytes of fp32 partial sums (gradient and column sums of every split) that the weight gradient of this
@@ -266,7 +270,8 @@ SOL_API int sol_sequence_run(const sol_sequence* seq, int32_t first, int32_t cou
  */
 enum {
     SOL_TRACE_OTHER = 0, SOL_TRACE_IGEMM, SOL_TRACE_IGEMM_GENERAL, SOL_TRACE_WGRAD, SOL_TRACE_WGRAD_GENERAL,
-    SOL_TRACE_WGRAD_REDUCE, SOL_TRACE_PACK, SOL_TRACE_UNTOUCHED, SOL_TRACE_MASKED_COPY, SOL_TRACE_SMALLC_PREPARE,
+    SOL_TRACE_WGRAD_REDUCE, SOL_TRACE_PACK, SOL_TRACE_UNTOUCHED, SOL_TRACE_MASKED_COPY,
+    SOL_TRACE_SMALLC_PREPARE,     /* reserved: no launch of this kind any more */
     SOL_TRACE_SMALLC_FWD, SOL_TRACE_SMALLC_WGRAD, SOL_TRACE_DIRECT, SOL_TRACE_L1_GRAD, SOL_TRACE_MAXPOOL,
     SOL_TRACE_IGEMM_PANEL, SOL_TRACE_IGEMM_REDUCE, SOL_TRACE_IGEMM_PANEL_REDUCE,
     SOL_TRACE_IGEMM_WIDE, SOL_TRACE_IGEMM_WIDE_REDUCE,      /* eight waves per workgroup                    */

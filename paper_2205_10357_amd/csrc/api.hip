@@ -226,7 +226,8 @@ GemmChoice choose_gemm(IgemmParams& p, const long long* rows, int tile, bool dat
         plain.offer(GemmChoice{GEMM_FAST, t}, e, with_rider(e, n, t == 1 || t == 2));
     };
     offer_fast(tile);
-    // 64 x 64 beside 128 x 64 where its workgroups are resident at once (1x1 512 -> 2048, 539 pixels 8.0 -> 6.5 us, 1176 pixels
+    // 64 x 64 beside 128 x 64 where its workgroups are resident at once; launches of up to eight slices come here with 64 x 64
+    // already, see run_igemm (1x1 512 -> 2048, 539 pixels 8.0 -> 6.5 us, 1176 pixels
     // 10.4 -> 7.9; 512 -> 128, 12544 pixels 8.2 -> 6.0)
     if (ragged || (tile == 1 && tiles_of(p, rows, 64, 64) <= 640)) offer_fast(3 - tile);
     if (!ragged && knob(K_WIDE, 0) >= 0 && nk >= 8 && p.Nc > 64) {
@@ -327,7 +328,6 @@ int run_igemm(IgemmParams& p, const long long* rows, bool mask, bool data_gradie
             if (many_tiles) tile = 1;
             igemm_fast_tile_shape(tile, &bp, &bc);
             if (tiles_of(p, rows, bp, bc) < 160) tile = 2;
-            // the panel kernel where its launch is one wave of workgroups that fills most of the chip
             // Short reductions whose small tiles are all resident at once pay one latency chain instead of a round after the
             // other.  1x1 with residual, panel kernel or 128 x 64 -> 64 x 64, us: 64 -> 256, 18207 pixels (1140 tiles) 10.4 -> 6.0,
             // 28611 9.2 -> 7.6, 62424 (3904) 14.3 and 13.9; 128 -> 512, 5488 pixels 6.0 -> 4.7, 8624 (1080) 8.7 -> 7.1; 256 -> 1024,
@@ -340,7 +340,7 @@ int run_igemm(IgemmParams& p, const long long* rows, bool mask, bool data_gradie
             } else if (slices <= 4 && t64 <= 1280 && p.Nc > 64) {
                 tile = 1;
                 many_tiles = true;
-            } else if (panel_ok) {
+            } else if (panel_ok) {                  // where its launch is one wave of workgroups that fills most of the chip
                 const long long panels = (rows[0] + 127) / 128;
                 long long groups = 256 / (panels > 0 ? panels : 1);
                 if (groups > p.Nc / 128) groups = p.Nc / 128;

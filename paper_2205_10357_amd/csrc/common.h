@@ -226,7 +226,7 @@ struct WgradParams {
     int M;                      // N*Ho*Wo
     int K;                      // KH*KW*C_in
     int splits;
-    int m_per_split;            // multiple of the reduction tile
+    int m_per_split;            // multiple of 64 (pipelined kernels) or 128 rows
     int tiles_k, tiles_c;
     FastDiv div_howo, div_wo;   // divisors Ho*Wo and Wo
     // pipelined kernels only: pack_blocks > 0 appends that many workgroups to the launch, which re-pack the

@@ -12,9 +12,10 @@
 //  * Region rows are swizzled by (row / 2) & 7, conflict-free for 16 rows from any start, so a tap costs a few vector
 //    instructions per 32-pixel block (address, choice of the zero row) for 4 * TC MFMAs.
 //  * Loop structure, barriers and epilogue are those of igemm_wide.hip.
-// Measured (warm, inputs rotating through HBM; before -> now): 3x3 256 -> 256, 25088 pixels 42.0 -> 30.2 us (979 TFLOP/s;
-// 39.1 with 256 x 128 gathering tiles); 128 -> 128, 100352 pixels 49.5 -> 38.9 (44.3); 256 -> 256, 12544 pixels 18.4 ->
-// 17.3; 512 -> 512, 6272 pixels 31.9 -> 31.2; 128 -> 128, 25088 pixels 12.0 -> 11.0; 64 -> 64, 401408 pixels 53.3 -> 48.5.
+// us on one box, operands rotating through HBM, 128 x 128 gathering tile of four waves / of eight waves (256 x 128 where that
+// is marked) / here: 3x3 256 -> 256, 25088 pixels 44.3 / 33.6 (256 x 128) / 30.6 (970 TFLOP/s); 128 -> 128, 100352 pixels 51.6 / 40.5
+// (256 x 128) / 39.7; 256 -> 256, 12544 pixels 23.4 / 19.0 / 19.2; 512 -> 512, 6272 pixels 46.0 / 34.1 / 34.4; 128 -> 128, 25088 pixels
+// 14.6 / 11.9 / 11.6; 64 -> 64, 401408 pixels (128 x 64 in four waves) 77.5 / - / 47.1.
 #include <type_traits>
 
 #include "igemm_gather.h"

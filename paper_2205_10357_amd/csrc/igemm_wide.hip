@@ -4,12 +4,14 @@
 // slices, one barrier in the middle of a slice, fragments of the next step requested before the MFMAs of this one), same
 // order of the reduction, hence the same bits.  What differs:
 //  * eight waves of (BP / WP) x 64 each, two per SIMD: while one waits for LDS or holds the issue port with a copy, the
-//    other multiplies.  128 x 128: 19.2 -> 18.1 us (3x3, 256 -> 256 channels, 12544 pixels) and 11.4 -> 10.7 us (1x1,
-//    1024 -> 256) against four waves of 64 x 64.
+//    other multiplies.
 //  * The two larger tiles copy 48 KiB per 256 x 128 x 64 slice where two 128 x 128 tiles copy 64 KiB and need one
-//    prologue and epilogue instead of two.  Such a launch costs about 5.9 us + 0.64 us per slice and round of 256
-//    workgroups: 3x3, 25088 pixels, 256 -> 256 channels 37.0 -> 29.0 us (1018 TFLOP/s); 3x3, 100352 pixels, 128 -> 128
-//    43.0 -> 35.0 us; 1x1, 25088 pixels, 1024 -> 512 42.7 -> 34.8 us; 1x1, 2352 pixels, 512 -> 2048 17.6 -> 11.8 us.
+//    prologue and epilogue instead of two.
+//    us on one box, operands that stay in the caches / that rotate through HBM, four waves of 64 x 64 (128 x 128, three stages)
+//    -> here: 128 x 128: 3x3 256 -> 256, 12544 pixels 18.0 / 23.4 -> 17.6 / 19.0; 1x1 1024 -> 256 10.2 / 16.7 -> 9.8 / 13.5.
+//    256 x 128: 3x3 256 -> 256, 25088 pixels 37.0 / 44.3 -> 30.1 / 33.6; 3x3 128 -> 128, 100352 pixels 45.6 / 51.6 -> 36.4 / 40.5;
+//    1x1 1024 -> 512, 25088 pixels 47.9 / 59.1 -> 35.6 / 47.2 (128 x 256 35.2 / 42.1).  The 3x3 layers among them take the tiles
+//    that keep a neighbourhood in LDS, which are up to a tenth faster still (igemm_halo.hip).
 //  * Row r keeps logical chunk c at physical chunk c ^ ((r + r/8) & 7): 32 rows further that is chunk c ^ 4, so four
 //    address registers per operand serve every fragment of every stage, the rest are immediates.
 //  * The epilogue has one barrier (the ring is reused): every wave transposes its own pixels x 64 channels through LDS, a
