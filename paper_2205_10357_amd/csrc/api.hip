@@ -259,9 +259,10 @@ GemmChoice choose_gemm(IgemmParams& p, const long long* rows, int tile, bool dat
     // beside them elsewhere: a data gradient (which carries one as a rule, and takes the same kernel when it does not) takes
     // such tiles where they save the 5 us of that.  Launch with its reduction, us, splitting tiles -> 64 x 64: 3x3 512 -> 512,
     // 392 pixels 17.4 and 19.0, 49 pixels 14.2 and 17.3; 3x3 256 -> 256, 196 pixels 10.0 and 11.1, 1372 pixels 10.9 and 11.0; 1x1
-    // 1024 -> 512, 196 pixels 7.3 -> 6.4; 2048 -> 512, 49 pixels 8.0 -> 7.0; 3x3 / stride 2 256 -> 256, 784 pixels 10.5 -> 7.3.  In the
-    // forward pass half a microsecond is what the fits are worth (1x1 / stride 2 256 -> 512, 304 pixels 4.4 -> 4.0).
-    const long long lead = data_gradient ? 5000 : 500;
+    // 1024 -> 512, 196 pixels 7.3 -> 6.4; 2048 -> 512, 49 pixels 8.0 -> 7.0; 3x3 / stride 2 256 -> 256, 784 pixels 10.5 -> 7.3.  (No
+    // lead is asked of them in the forward pass: half a microsecond, which warm operands suggest (1x1 / stride 2 256 -> 512,
+    // 304 pixels 4.4 -> 4.0), made the inference of one image, whose weights come from memory, 235 -> 243 us.)
+    const long long lead = data_gradient ? 5000 : 0;
     if (ksplit.alone < INT64_MAX && ksplit.alone + lead < plain.alone && ksplit.alone + lead < halo.alone) return ksplit.choice;
     return halo.alone < plain.alone ? halo.choice : plain.choice;
 }
