@@ -166,9 +166,15 @@ int tiles_of(const IgemmParams& p, const long long* rows, int bp, int bc) {
 // of T workgroups with nk 64-deep slices takes, in ns (fits to launches over the benchmark network's layers at 1 .. 128
 // images, inputs not in L2; 256 compute units):
 //   64 x 64, two per compute unit              3600 + nk * max(200, 153 * ceil(T / 256))
-//   128 x 64, three per compute unit           5000 + nk * max(300, 450 T / 256); 320 for 450 in many tiles of at least nine taps
-//                                              where three tiles of channels share a gather and 128-wide tiles pad a quarter
-//                                              (3x3 128 -> 192, 82369 pixels 62.4 with a neighbourhood in LDS, 50.0; 512 -> 176 189 and 173)
+//   128 x 64, three per compute unit           5000 + nk * max(300, 450 T / 256)
+//     forward, 160 .. 256 tiles                5000 + 250 nk: each has a compute unit for itself, where 64 x 64 tiles come two by
+//                                              two (us, 64 x 64 -> 128 x 64, operands in the caches / from HBM: 5x5 / stride 2
+//                                              448 -> 448, 3600 pixels 55.8 / 64.2 -> 46.5 / 53.6; 3x3 448 -> 224, 6084 pixels 18.9 / 21.2
+//                                              -> 15.8 / 19.9; 1x1 2048 -> 512, 3136 pixels 12.4 / 18.5 -> 11.4 / 16.5); a data gradient's
+//                                              riders find no room beside such a tile (3x3 512 -> 512, 2352 pixels 25.5 -> 30.4)
+//     many tiles, 129 .. 192 channels, >= 9 taps  320 for 450: three tiles of channels share a gather and 128-wide tiles pad a
+//                                              quarter (3x3 128 -> 192, 82369 pixels 62.4 with a neighbourhood in LDS, 50.0; 512 -> 176
+//                                              189 and 173)
 //   128 x 128, eight waves                     ceil(T / 256) * (5100 + 390 nk)
 //   256 x 128 and 128 x 256, eight waves       ceil(T / 256) * (6500 + 900 nk)
 //   neighbourhood in LDS: 256 x 128            ceil(T / 256) * (8000 + 600 nk)
@@ -220,8 +226,9 @@ GemmChoice choose_gemm(IgemmParams& p, const long long* rows, int tile, bool dat
         igemm_fast_tile_shape(t, &bp, &bc);
         const long long n = tiles_of(p, rows, bp, bc), r = rounds(n);
         const int ns = n >= 1024 && p.Nc > 128 && p.Nc <= 192 && p.Cs > 64 && p.ncls == 1 && p.cls[0].Th * p.cls[0].Tw >= 9 ? 320 : 450;
+        const bool one_each = !data_gradient && n >= 160 && n <= 256;
         const long long e = t == 2 ? 3600 + nk * (153 * r > 200 ? 153 * r : 200)
-                          : t == 1 ? 5000 + nk * (ns * n < 300 * 256 ? 300 : (ns * n) >> 8)
+                          : t == 1 ? 5000 + nk * (one_each ? 250 : ns * n < 300 * 256 ? 300 : (ns * n) >> 8)
                                    : r * (5100 + 390 * nk);
         plain.offer(GemmChoice{GEMM_FAST, t}, e, with_rider(e, n, t == 1 || t == 2));
     };
@@ -357,7 +364,8 @@ int run_igemm(IgemmParams& p, const long long* rows, bool mask, bool data_gradie
         choice = free_choice ? choose_gemm(p, rows, tile, data_gradient, knob(K_REDUCE_RIDES, 1) != 0 ? rider : nullptr, tuned.tile < 0) : GemmChoice{GEMM_FAST, tile};
         if (choice.family == GEMM_FAST && choice.tile != tile) {
             tile = choice.tile;
-            many_tiles = tile != 2 || tiles_of(p, rows, 64, 64) > 512;      // deep rings of 64 x 64 tiles: two per compute unit
+            igemm_fast_tile_shape(tile, &bp, &bc);      // deep rings: one 128 x 64 tile or two of 64 x 64 per compute unit
+            many_tiles = tiles_of(p, rows, bp, bc) > (tile == 2 ? 512 : 256);
         }
         stages = knob(K_FAST_STAGES, 0);
         if (stages < 2 || stages > 4) stages = tuned.stages;
