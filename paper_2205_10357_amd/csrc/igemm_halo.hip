@@ -4,8 +4,10 @@
 // Tap (th, tw) of output pixel r reads source pixel r + dh * W + dw, counted through the whole tensor.  So the pixels of a
 // tile of BP consecutive rows lie in one contiguous run of BP + 2 W + 2 source pixels (3x3), the region.  A tap is an
 // offset into the region; lanes whose tap lies outside the image read a row of zeros instead.  Per slice and tap a
-// workgroup copies the weights and a ninth of a region: 256 x 128 tile, 28 x 28 image 20 KiB instead of 48 KiB; what a
-// compute unit copies into LDS (about 100 bytes per ns) and the energy of those copies is what bounds the gathering tiles.
+// workgroup copies the weights and a ninth of a region: 256 x 128 tile, 28 x 28 image 20 KiB instead of 48 KiB.  By the
+// counters a 128 x 128 launch (12544 pixels, 256 -> 256) reads 1.06 M lines of 128 bytes from the L2, gathering tiles 1.72 M; its
+// matrix units are busy 44 % of the time that its compute units are, with the four-wave gathering tile 40 %.  That alone makes
+// it no faster than the eight-wave gathering tile; the larger tiles and those of 64 channels are.
 //  * The reduction runs channel slice by channel slice, taps inside (the gathering tiles run taps outside: same products,
 //    other order of the sums).  Weights stream through a ring of NSW slices, regions of two channel slices alternate: the
 //    copies of the next region go out one or two per slice during the taps of this one.

@@ -5,7 +5,7 @@
 // memory latency per slice (0.2 us; 72 slices for a 3x3 over 512 channels).  Here a tile is as small as 16 x 16 (enough
 // workgroups for the chip), and each of the 8 (6) waves takes every eighth (sixth) 64-deep slice of the reduction with a
 // copy ring of its own: no barrier in the loop, every wave waits for its own copies only, and all their copies are in
-// flight together.  What bounds it is the rate at which a compute unit copies into LDS, about 100 bytes per ns.  The
+// flight together.  By the fit of its times a compute unit copies about 100 bytes per ns into LDS, which bounds it.  The
 // partial tiles meet in LDS and are added in the order of the waves (fixed, so runs repeat bit for bit; the sum of a
 // reduction differs from the other kernels' in its last bits).
 // One image, weights not in L2 (before: 64 x 64 tiles): 3x3 512 -> 512, 49 pixels 18.1 -> 6.2 us; 3x3 256 -> 256, 196
