@@ -138,17 +138,10 @@ __global__ __launch_bounds__(256, 2) void wgrad_fast_kernel(const WgradParams p)
         goff[f] = mrow * 256 + (((rg >> 3) ^ sw) << 4) + ((rg >> 2) & 1) * 8;
     }
     const bool do_shift = (tk == 0) && (wk == 0);
-    // even and odd steps add up in accumulators of their own
+    // Even and odd steps add up in accumulators of their own.  The first product of each starts from the constant zero: clearing
+    // 160 registers took 0.3 us (1x1 1024 -> 256, 1372 pixels 8.0 -> 7.7 us).
     floatx16 acc[WGF_SETS][2][2], accs[2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-#pragma unroll
-            for (int s = 0; s < WGF_SETS; ++s) acc[s][a][0][v] = acc[s][a][1][v] = 0.f;
-            accs[a][v] = 0.f;
-        }
-    }
+    const floatx16 zero = {0.f};
     bf16x8 ones;
 #pragma unroll
     for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
@@ -179,52 +172,62 @@ __global__ __launch_bounds__(256, 2) void wgrad_fast_kernel(const WgradParams p)
     auto frag = [](const Frags& fr, int i) {
         return __builtin_bit_cast(bf16x8, uintx4{fr.r[2 * i][0], fr.r[2 * i][1], fr.r[2 * i + 1][0], fr.r[2 * i + 1][1]});
     };
-    auto multiply = [&](Frags& fr, auto set_tag, auto newer_tag, auto shift_tag) {   // newer_tag: reads issued after fr's that may stay in flight
+    auto multiply = [&](Frags& fr, auto set_tag, auto first_tag, auto newer_tag, auto shift_tag) {   // newer_tag: reads issued after fr's that may stay in flight
         lds_tr_wait<decltype(newer_tag)::value>(fr.r[0], fr.r[1], fr.r[2], fr.r[3], fr.r[4], fr.r[5], fr.r[6], fr.r[7]);
         constexpr int S = decltype(set_tag)::value;
+        constexpr bool FIRST = decltype(first_tag)::value;      // the accumulators hold nothing yet
         const bf16x8 x0 = frag(fr, 0), x1 = frag(fr, 1), g0 = frag(fr, 2), g1 = frag(fr, 3);
-        acc[S][0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x0, g0, acc[S][0][0], 0, 0, 0);
-        acc[S][0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x0, g1, acc[S][0][1], 0, 0, 0);
-        acc[S][1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1, g0, acc[S][1][0], 0, 0, 0);
-        acc[S][1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1, g1, acc[S][1][1], 0, 0, 0);
+        acc[S][0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x0, g0, FIRST ? zero : acc[S][0][0], 0, 0, 0);
+        acc[S][0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x0, g1, FIRST ? zero : acc[S][0][1], 0, 0, 0);
+        acc[S][1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1, g0, FIRST ? zero : acc[S][1][0], 0, 0, 0);
+        acc[S][1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1, g1, FIRST ? zero : acc[S][1][1], 0, 0, 0);
         if constexpr (decltype(shift_tag)::value) {
-            accs[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, g0, accs[0], 0, 0, 0);
-            accs[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, g1, accs[1], 0, 0, 0);
+            accs[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, g0, FIRST && S == 0 ? zero : accs[0], 0, 0, 0);
+            accs[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, g1, FIRST && S == 0 ? zero : accs[1], 0, 0, 0);
         }
     };
     const lds_addr_t lds0 = lds_byte_address(lds);
 
     // One slice.  Per step: wait for this step's fragments (requested one step earlier), request
     // the next step's, issue a quarter of the copies for the slice NS-1 ahead, multiply.
-    auto slice = [&](int sl, auto more_tag, auto shift_tag) {
+    auto slice = [&](int sl, auto first_tag, auto more_tag, auto shift_tag) {
         constexpr bool MORE = decltype(more_tag)::value;
         const lds_addr_t xbase = lds0 + (lds_addr_t)((sl % NS) * WGF_STAGE * 16);
         Frags fa, fb;
         issue_frags(fa, xbase, std::integral_constant<int, 0>{});
         issue_frags(fb, xbase, std::integral_constant<int, 1>{});
         if constexpr (MORE) request_part(0);
-        multiply(fa, std::integral_constant<int, 0>{}, std::integral_constant<int, 8>{}, shift_tag);
+        multiply(fa, std::integral_constant<int, 0>{}, first_tag, std::integral_constant<int, 8>{}, shift_tag);
         issue_frags(fa, xbase, std::integral_constant<int, 2>{});
         if constexpr (MORE) request_part(1);
-        multiply(fb, std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{}, shift_tag);
+        multiply(fb, std::integral_constant<int, 1>{}, first_tag, std::integral_constant<int, 8>{}, shift_tag);
         issue_frags(fb, xbase, std::integral_constant<int, 3>{});
         if constexpr (MORE) request_part(2);
-        multiply(fa, std::integral_constant<int, 0>{}, std::integral_constant<int, 8>{}, shift_tag);
+        multiply(fa, std::integral_constant<int, 0>{}, std::false_type{}, std::integral_constant<int, 8>{}, shift_tag);
         if constexpr (MORE) request_part(3);
-        multiply(fb, std::integral_constant<int, 1>{}, std::integral_constant<int, 0>{}, shift_tag);
+        multiply(fb, std::integral_constant<int, 1>{}, std::false_type{}, std::integral_constant<int, 0>{}, shift_tag);
     };
 
     auto run = [&](auto shift_tag) {
-        int sl = 0;
+        if (nsl > NS - 1) {
+            wait_vm_and_lds<(NS - 2) * LPS>();
+            wg_barrier();
+            slice(0, std::true_type{}, std::true_type{}, shift_tag);
+        } else {
+            wait_vm_and_lds<0>();
+            wg_barrier();
+            slice(0, std::true_type{}, std::false_type{}, shift_tag);
+        }
+        int sl = 1;
         for (; sl + NS - 1 < nsl; ++sl) {
             wait_vm_and_lds<(NS - 2) * LPS>();
             wg_barrier();
-            slice(sl, std::true_type{}, shift_tag);
+            slice(sl, std::false_type{}, std::true_type{}, shift_tag);
         }
         for (; sl < nsl; ++sl) {
             wait_vm_and_lds<0>();
             wg_barrier();
-            slice(sl, std::false_type{}, shift_tag);
+            slice(sl, std::false_type{}, std::false_type{}, shift_tag);
         }
     };
     if (do_shift) run(std::true_type{});

@@ -169,11 +169,9 @@ __global__ __launch_bounds__(512) void wgrad_wide_kernel(const WgradParams p) {
     const bool do_shift = (tk == 0) && (wk == 0);
     // A group's two steps of a slice add up in accumulators of their own, which halves the chains of fp32 additions (relative
     // error of 3x3 256 -> 256, 12544 pixels against 64-bit sums 1.76e-7 -> 1.28e-7; 1.70e-7 with four waves and 14 splits).
+    // The first product of each starts from the constant zero instead of cleared registers.
     floatx16 acc[2][2][2], accs[2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[0][a][0][v] = acc[0][a][1][v] = acc[1][a][0][v] = acc[1][a][1][v] = accs[a][v] = 0.f;
+    const floatx16 zero = {0.f};
     bf16x8 ones;
 #pragma unroll
     for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
@@ -204,17 +202,18 @@ __global__ __launch_bounds__(512) void wgrad_wide_kernel(const WgradParams p) {
     auto frag = [](const Frags& fr, int i) {
         return __builtin_bit_cast(bf16x8, uintx4{fr.r[2 * i][0], fr.r[2 * i][1], fr.r[2 * i + 1][0], fr.r[2 * i + 1][1]});
     };
-    auto multiply = [&](Frags& fr, auto set_tag, auto newer_tag, auto shift_tag) {   // newer_tag: reads issued after fr's that may stay in flight
+    auto multiply = [&](Frags& fr, auto set_tag, auto first_tag, auto newer_tag, auto shift_tag) {   // newer_tag: reads issued after fr's that may stay in flight
         lds_tr_wait<decltype(newer_tag)::value>(fr.r[0], fr.r[1], fr.r[2], fr.r[3], fr.r[4], fr.r[5], fr.r[6], fr.r[7]);
         constexpr int S = decltype(set_tag)::value;
+        constexpr bool FIRST = decltype(first_tag)::value;      // the accumulators hold nothing yet
         const bf16x8 x0 = frag(fr, 0), x1 = frag(fr, 1), g0 = frag(fr, 2), g1 = frag(fr, 3);
-        acc[S][0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x0, g0, acc[S][0][0], 0, 0, 0);
-        acc[S][0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x0, g1, acc[S][0][1], 0, 0, 0);
-        acc[S][1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1, g0, acc[S][1][0], 0, 0, 0);
-        acc[S][1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1, g1, acc[S][1][1], 0, 0, 0);
+        acc[S][0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x0, g0, FIRST ? zero : acc[S][0][0], 0, 0, 0);
+        acc[S][0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x0, g1, FIRST ? zero : acc[S][0][1], 0, 0, 0);
+        acc[S][1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1, g0, FIRST ? zero : acc[S][1][0], 0, 0, 0);
+        acc[S][1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1, g1, FIRST ? zero : acc[S][1][1], 0, 0, 0);
         if constexpr (decltype(shift_tag)::value) {
-            accs[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, g0, accs[0], 0, 0, 0);
-            accs[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, g1, accs[1], 0, 0, 0);
+            accs[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, g0, FIRST && S == 0 ? zero : accs[0], 0, 0, 0);
+            accs[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, g1, FIRST && S == 0 ? zero : accs[1], 0, 0, 0);
         }
     };
     const lds_addr_t lds0 = lds_byte_address(lds);
@@ -231,10 +230,10 @@ __global__ __launch_bounds__(512) void wgrad_wide_kernel(const WgradParams p) {
         auto settle = [&](Frags& fr) { lds_tr_wait<0>(fr.r[0], fr.r[1], fr.r[2], fr.r[3], fr.r[4], fr.r[5], fr.r[6], fr.r[7]); };
         settle(fa);
         // slice sl lies in stage st, its first step's fragments are in registers; MORE: slice sl + NS - 1 is requested
-        auto slice = [&](auto next_tag, auto more_tag) {
+        auto slice = [&](auto first_tag, auto next_tag, auto more_tag) {
             constexpr bool NEXT = decltype(next_tag)::value, MORE = decltype(more_tag)::value;
             issue_frags(fb, stage_address(st), std::integral_constant<int, 1>{});
-            multiply(fa, std::integral_constant<int, 0>{}, std::integral_constant<int, 8>{}, shift_tag);
+            multiply(fa, std::integral_constant<int, 0>{}, first_tag, std::integral_constant<int, 8>{}, shift_tag);
             if constexpr (NEXT) {
                 constexpr int left = MORE ? (NS - 3) * LPS : 0;       // copies of slices sl + 2 .. may stay in flight
                 asm volatile("" ::: "memory");
@@ -242,7 +241,7 @@ __global__ __launch_bounds__(512) void wgrad_wide_kernel(const WgradParams p) {
                 wg_barrier();                                         // slice sl + 1 has landed, slice sl - 1 is no longer read
                 st = st + 1 == NS ? 0 : st + 1;
                 issue_frags(fa, stage_address(st), std::integral_constant<int, 0>{});
-                multiply(fb, std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{}, shift_tag);
+                multiply(fb, std::integral_constant<int, 1>{}, first_tag, std::integral_constant<int, 8>{}, shift_tag);
                 if constexpr (MORE) {
                     request_x();
                     request_g();
@@ -255,13 +254,16 @@ __global__ __launch_bounds__(512) void wgrad_wide_kernel(const WgradParams p) {
                 }
                 settle(fa);                                           // under the MFMAs just issued
             } else {
-                multiply(fb, std::integral_constant<int, 1>{}, std::integral_constant<int, 0>{}, shift_tag);
+                multiply(fb, std::integral_constant<int, 1>{}, first_tag, std::integral_constant<int, 0>{}, shift_tag);
             }
         };
-        int sl = 0;
-        for (; sl + NS - 1 < nsl; ++sl) slice(std::true_type{}, std::true_type{});
-        for (; sl + 1 < nsl; ++sl) slice(std::true_type{}, std::false_type{});
-        slice(std::false_type{}, std::false_type{});
+        if (nsl > NS - 1) slice(std::true_type{}, std::true_type{}, std::true_type{});
+        else if (nsl > 1) slice(std::true_type{}, std::true_type{}, std::false_type{});
+        else slice(std::true_type{}, std::false_type{}, std::false_type{});
+        int sl = 1;
+        for (; sl + NS - 1 < nsl; ++sl) slice(std::false_type{}, std::true_type{}, std::true_type{});
+        for (; sl + 1 < nsl; ++sl) slice(std::false_type{}, std::true_type{}, std::false_type{});
+        if (sl < nsl) slice(std::false_type{}, std::false_type{}, std::false_type{});
     };
     if (do_shift) run(std::true_type{});
     else run(std::false_type{});
